@@ -173,6 +173,10 @@ typedef struct {
  * flags: HAB_RENDER_* bits (others: HAB_ERR_INVALID_ARG).  None of these
  * changes any output bit.
  *
+ * A small launch with none of them set (and no statistics asked for) is drawn
+ * without tile lists, in about half the time; a tile size, bin factor, tile
+ * cap or HAB_RENDER_LANE_OWNED_Z always takes the tile lists.
+ *
  * A batch of 32 or more views is rendered as two launch sequences over
  * interleaved halves (views 0, 2, 4, ... and 1, 3, 5, ...): one on the
  * caller's stream, one on a second stream of the context that waits for the
@@ -473,8 +477,10 @@ hab_status hab_server_destroy(hab_server *srv);
 /* Per-phase device time, from HIP events recorded on the launch stream
  * around every kernel while profiling is on (hab_profile_enable).  Phases:
  * 0 reset, 1 setup, 2 bin count, 3 bin scan, 4 bin scatter, 5..7 raster
- * with tile size 8, 16, 32, 8 resolve.  Graph replays (stepper) are not
- * timed. */
+ * with tile size 8, 16, 32, 8 resolve.  A small launch drawn without tile
+ * lists counts its clearing, culling and drawing as reset, setup and the
+ * raster phase of its first view's tile size.  Graph replays (stepper) are
+ * not timed. */
 #define HAB_NUM_PHASES 9
 typedef struct {
     double ms[HAB_NUM_PHASES];        /* summed device time per phase        */

@@ -28,7 +28,7 @@ SAN_OBJDIR = os.path.join(HERE, "_build_san")
 SAN_LIB = os.path.join(SAN_OBJDIR, "libhabmi_san.so")
 SAN_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
              "-Xarch_host", "-fno-omit-frame-pointer", "-Xarch_host", "-fno-sanitize-recover=all", "-g"]
-SOURCES = ["kernels.hip", "actuate.hip", "noalloc.hip", "runtime.cpp", "abi.cpp", "stepper.cpp",
+SOURCES = ["kernels.hip", "draw.hip", "actuate.hip", "noalloc.hip", "runtime.cpp", "abi.cpp", "stepper.cpp",
            "server.cpp", "autotune.cpp"]
 ARCH = os.environ.get("HABMI_ARCH", "gfx950")
 

@@ -55,6 +55,7 @@ void set_table(hab_context *ctx, const std::map<uint32_t, Tuned> &choice)
 hab_status time_batch(hab_context *ctx, std::vector<ViewReq> &req, hipStream_t s, Timer &t, float *ms)
 {
     PlanOpts o;   // tile size 0: every class takes its table entry
+    o.tile_lists = true;   // what it tunes (a small batch draws without them)
     hab_status rc = render_all(ctx, ctx->ws, req.data(), (uint32_t)req.size(), o, s, nullptr);
     if (rc != HAB_OK) return rc;
     float best = 1e30f;

@@ -42,11 +42,11 @@ struct alignas(16) DView {
     uint32_t pair_base;         // first entry of this view's visible-cluster segment
     const float4 *cbox;         // per 64-triangle cluster: (min xyz, -) (max xyz, -)
     uint32_t count_work;        // 1: accumulate bbox tests and covered fragments
-    uint32_t pad;
+    uint32_t zoff_lo;           // direct path: the view's first z-key (low word)
     const uint32_t *inst;       // [T] instance id per triangle (semantic output)
     uint32_t *sem;              // [H][W] or null
     float noise_sigma;          // depth noise in 1/m (0: ideal depth)
-    uint32_t pad2;
+    uint32_t zoff_hi;           //   and high word
     uint64_t noise_seed;        // key of the per-pixel depth noise
     const float *uv;            // [V][2] texture coordinates (textured scenes)
     const uint32_t *tex;        // [tex_h][tex_w] packed RGB texels, or null
@@ -71,6 +71,15 @@ struct alignas(128) DQueue {
     DQueueHead head[3][kQueues];
 };
 
+// A visible cluster of the direct path: its index, the pixel rectangle
+// (i0 | j0 << 16, i1 | j1 << 16) that holds all its triangles can cover and an
+// upper bound of its fragments' 1/w (inf: no rectangle, always drawn).
+struct alignas(16) ClusterRec {
+    uint32_t c, lo, hi;
+    float rho;
+};
+constexpr uint32_t kBuckets = 16;     // distance buckets of a view's visible clusters
+
 // Per-view counters (zeroed at the start of every launch sequence).
 // Each view's counters take two cache lines: the first holds what atomics
 // update, the second what is written once and read by many waves, so
@@ -83,7 +92,8 @@ struct alignas(128) DViewCounters {
     unsigned long long covered;
     uint32_t pad[26];
     uint32_t vis_clusters;      // clusters that passed the view's frustum test
-    uint32_t pad2[31];
+    uint32_t bucket[kBuckets];  // direct path: visible clusters per distance bucket
+    uint32_t pad2[31 - kBuckets];
 };
 static_assert(sizeof(DViewCounters) == 256, "counter lines");
 

@@ -49,6 +49,15 @@ struct LaunchPlan {
     uint32_t bin_grid;
     RasterLaunch raster[3];
     int nraster;
+    // direct path (draw.hip): drawn without tile lists when `direct`
+    bool direct;
+    unsigned long long *zbuf;  // z-keys of every view, [znum]
+    uint64_t znum;
+    ClusterRec *recs;          // visible clusters, kBuckets segments per view
+    const uint32_t *tpre;      // [nl] first tile block of each view of the list
+    uint32_t tile_edge;        // 16, 32 or 64
+    uint32_t shares;           // blocks that share a tile's clusters (1: the block shades it)
+    uint32_t tile_grid;        // tile blocks
     hipEvent_t *prof;          // null, or kProfEvents events recorded around the kernels
     uint32_t prof_mask;        // phases whose start/stop events are recorded
 };
@@ -61,8 +70,9 @@ constexpr int kProfEvents = 2 * kProfPhases;   // start/stop per phase
 // persistent grid).
 int raster_blocks_per_cu(int ts, bool lane_owned);
 
-// Enqueue the whole sequence on stream s.
+// Enqueue the whole sequence on stream s (launch_direct: a direct plan's).
 hipError_t launch_render(const LaunchPlan &L, hipStream_t s);
+hipError_t launch_direct(const LaunchPlan &L, hipStream_t s);
 
 // Compare recip_rn with the IEEE division 1/x for every float whose bits
 // lie in [lo, hi) (lo < hi <= 0x7F800000), adding the number of differing

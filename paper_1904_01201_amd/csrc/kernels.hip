@@ -40,118 +40,15 @@
 
 #include <type_traits>
 
+#include "device_util.h"
 #include "dtypes.h"
 #include "kernels.h"
 #include "raster_math.h"
+#include "shade.h"
 
 #pragma clang fp contract(off)
 
 namespace habmi {
-
-// ------------------------------------------------------------ wave helpers
-__device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
-
-// A value every lane of the wave holds alike, moved to a scalar register so
-// that what it indexes is fetched through the scalar cache.
-__device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-
-__device__ __forceinline__ unsigned long long lanemask_lt()
-{
-    return (1ull << lane_id()) - 1ull;
-}
-
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    return x;
-}
-
-// Exclusive scan over the block (NT threads, wave64); *total gets the sum.
-// wtot: LDS scratch of NT/64 words.  Contains two barriers.
-template <int NT>
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *wtot, uint32_t *total)
-{
-    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
-    uint32_t s = x;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        uint32_t y = __shfl_up(s, off);
-        if (lane >= (uint32_t)off) s += y;
-    }
-    if (lane == 63) wtot[wave] = s;
-    __syncthreads();
-    uint32_t pre = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-        uint32_t v = wtot[w];
-        pre += (w < (int)wave) ? v : 0u;
-        tot += v;
-    }
-    __syncthreads();
-    *total = tot;
-    return pre + s - x;
-}
-
-// Add 1 to counters[key] for every lane with `has`, one atomic per distinct
-// key in the wave.  Returns, per participating lane, the counter's value
-// before the wave's additions plus the lane's rank among the lanes with the
-// same key: a unique slot.
-__device__ __forceinline__ uint32_t wave_aggregated_add(uint32_t *counters, uint32_t key, bool has)
-{
-    unsigned long long pending = __ballot(has);
-    uint32_t mine = 0;
-    const uint32_t lane = lane_id();
-    while (pending) {
-        const int leader = __ffsll((long long)pending) - 1;
-        const uint32_t lk = __shfl(key, leader);
-        const unsigned long long peers = __ballot(has && key == lk);
-        uint32_t base = 0;
-        if (lane == (uint32_t)leader) base = atomicAdd(&counters[lk], (uint32_t)__popcll(peers));
-        base = __shfl(base, leader);
-        if (has && key == lk) mine = base + (uint32_t)__popcll(peers & lanemask_lt());
-        pending &= ~peers;
-    }
-    return mine;
-}
-
-__device__ __forceinline__ uint2 pack_box(const PixBox &b)
-{
-    return make_uint2((uint32_t)b.i0 | ((uint32_t)b.j0 << 16), (uint32_t)b.i1 | ((uint32_t)b.j1 << 16));
-}
-
-// A pointer read out of a view record, known to point into device global
-// memory: loads through it are global (vector memory only), not flat.
-template <typename T>
-__device__ __forceinline__ const __attribute__((address_space(1))) T *gmem(const T *p)
-{
-    return (const __attribute__((address_space(1))) T *)p;
-}
-template <typename T>
-__device__ __forceinline__ __attribute__((address_space(1))) T *gmem_out(T *p)
-{
-    return (__attribute__((address_space(1))) T *)p;
-}
-
-// Triangle t's vertex positions: nine consecutive floats of the
-// per-triangle copy, independent loads (no dependent index -> position
-// load).  With T up to 2^30, 9 t can exceed 32 bits: a 64-bit offset.
-__device__ __forceinline__ void load_pos(const DView &v, uint32_t t, float P[9])
-{
-    const auto *p = gmem(v.tpos) + 9ull * t;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) P[i] = p[i];
-}
-
-// Positions and the vertex indices (for per-vertex attributes).
-__device__ __forceinline__ void load_tri(const DView &v, uint32_t t, float P[9], uint32_t vid[3])
-{
-    const auto *ix = gmem(v.idx) + 3u * t;
-    vid[0] = ix[0];
-    vid[1] = ix[1];
-    vid[2] = ix[2];
-    load_pos(v, t, P);
-}
 
 // ------------------------------------------------------------ k_reset
 __global__ __launch_bounds__(256) void k_reset(DViewCounters *__restrict__ ctr, uint32_t nviews,
@@ -958,125 +855,6 @@ __device__ __forceinline__ long long join64(int hi, int lo)
     return (long long)(((unsigned long long)(uint32_t)hi << 32) | (unsigned long long)(uint32_t)lo);
 }
 
-// Colour, depth and index of the winning sub-triangle at pixel (i, j):
-// the winner's setup is rebuilt with colours, its three edge functions at
-// the pixel centre give the perspective-correct weights.
-// Colour of the winner at pixel (i, j): the triangle's setup rebuilt with
-// the same arithmetic as the raster's (the depth comes from the winning
-// key's 1/w, the same value).
-__device__ __forceinline__ bool resolve(const DView &v, uint32_t key, int i, int j, uint32_t rgb[3])
-{
-    const uint32_t t = key >> 1;
-    const int sub = (int)(key & 1u);
-    float P[9];
-    uint32_t vid[3];
-    load_tri(v, t, P, vid);
-    Vtx<3> c0, c1, c2;
-    cam_xform(v, P[0], P[1], P[2], c0);
-    cam_xform(v, P[3], P[4], P[5], c1);
-    cam_xform(v, P[6], P[7], P[8], c2);
-    const uint32_t k0 = v.col ? gmem(v.col)[vid[0]] : 0xFFFFFFu;
-    const uint32_t k1 = v.col ? gmem(v.col)[vid[1]] : 0xFFFFFFu;
-    const uint32_t k2 = v.col ? gmem(v.col)[vid[2]] : 0xFFFFFFu;
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        c0.a[ch] = (float)unpack_rgb(k0, ch);
-        c1.a[ch] = (float)unpack_rgb(k1, ch);
-        c2.a[ch] = (float)unpack_rgb(k2, ch);
-    }
-    SVtx<3> a = {}, b = {}, c = {};
-    long long A = 1;
-    bool rerr = false;
-    if (!setup_sub(v, c0, c1, c2, sub, a, b, c, A, rerr)) {
-        // unreachable: the key came from a successful setup of the same
-        // arithmetic; report it as a device fault rather than guess
-        rgb[0] = rgb[1] = rgb[2] = 0;
-        return false;
-    }
-    const long long px = 256ll * i + 128, py = 256ll * j + 128;
-    const long long E0 = edge_at(b.X, b.Y, c.X, c.Y, px, py);
-    const long long E1 = edge_at(c.X, c.Y, a.X, a.Y, px, py);
-    const long long E2 = edge_at(a.X, a.Y, b.X, b.Y, px, py);
-    const float w0 = (float)E0 * a.rw, w1 = (float)E1 * b.rw, w2 = (float)E2 * c.rw;
-    const float num = (w0 + w1) + w2;
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        float val = ((w0 * a.a[ch] + w1 * b.a[ch]) + w2 * c.a[ch]) / num;
-        val = rintf(val);
-        val = fminf(fmaxf(val, 0.0f), 255.0f);
-        rgb[ch] = (uint32_t)val;
-    }
-    return true;
-}
-
-// Textured colour: the texture coordinates ride through the clip and the
-// perspective-correct interpolation exactly as colours do (same fp32
-// sequence), then a bilinear fetch with texel centres at (k + 1/2) / size,
-// coordinates repeating.  For a power-of-two size and |u| size < 2^22,
-// u * size - 1/2 and its fraction are exact in fp32, so only the blend's
-// rounding differs from an fp64 evaluation.
-__device__ __forceinline__ void tex_bilinear(const DView &v, float u, float t, uint32_t rgb[3])
-{
-    const float x = u * (float)v.tex_w - 0.5f, y = t * (float)v.tex_h - 0.5f;
-    const float xf = floorf(x), yf = floorf(y);
-    const float fx = x - xf, fy = y - yf;
-    const int xi = (int)xf, yi = (int)yf;
-    const uint32_t wm = v.tex_w - 1u, hm = v.tex_h - 1u;
-    const uint32_t i0 = (uint32_t)xi & wm, i1 = (uint32_t)(xi + 1) & wm;
-    const uint32_t r0 = ((uint32_t)yi & hm) * v.tex_w, r1 = ((uint32_t)(yi + 1) & hm) * v.tex_w;
-    const auto *tex = gmem(v.tex);
-    const uint32_t t00 = tex[r0 + i0], t10 = tex[r0 + i1], t01 = tex[r1 + i0], t11 = tex[r1 + i1];
-    const float gx = 1.0f - fx, gy = 1.0f - fy;
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        const float c00 = (float)unpack_rgb(t00, ch), c10 = (float)unpack_rgb(t10, ch);
-        const float c01 = (float)unpack_rgb(t01, ch), c11 = (float)unpack_rgb(t11, ch);
-        float val = gy * (gx * c00 + fx * c10) + fy * (gx * c01 + fx * c11);
-        val = rintf(val);
-        rgb[ch] = (uint32_t)fminf(fmaxf(val, 0.0f), 255.0f);
-    }
-}
-
-// resolve() for a textured scene: the same rebuild of the winner with the
-// texture coordinates as its two attributes.
-__device__ __forceinline__ bool resolve_tex(const DView &v, uint32_t key, int i, int j,
-                                            uint32_t rgb[3])
-{
-    const uint32_t t = key >> 1;
-    const int sub = (int)(key & 1u);
-    float P[9];
-    uint32_t vid[3];
-    load_tri(v, t, P, vid);
-    Vtx<2> c0, c1, c2;
-    cam_xform(v, P[0], P[1], P[2], c0);
-    cam_xform(v, P[3], P[4], P[5], c1);
-    cam_xform(v, P[6], P[7], P[8], c2);
-    const auto *uv = gmem(v.uv);
-    c0.a[0] = uv[2u * vid[0]];
-    c0.a[1] = uv[2u * vid[0] + 1u];
-    c1.a[0] = uv[2u * vid[1]];
-    c1.a[1] = uv[2u * vid[1] + 1u];
-    c2.a[0] = uv[2u * vid[2]];
-    c2.a[1] = uv[2u * vid[2] + 1u];
-    SVtx<2> a = {}, b = {}, c = {};
-    long long A = 1;
-    bool rerr = false;
-    if (!setup_sub(v, c0, c1, c2, sub, a, b, c, A, rerr)) {
-        rgb[0] = rgb[1] = rgb[2] = 0;
-        return false;
-    }
-    const long long px = 256ll * i + 128, py = 256ll * j + 128;
-    const long long E0 = edge_at(b.X, b.Y, c.X, c.Y, px, py);
-    const long long E1 = edge_at(c.X, c.Y, a.X, a.Y, px, py);
-    const long long E2 = edge_at(a.X, a.Y, b.X, b.Y, px, py);
-    const float w0 = (float)E0 * a.rw, w1 = (float)E1 * b.rw, w2 = (float)E2 * c.rw;
-    const float num = (w0 + w1) + w2;
-    const float u = ((w0 * a.a[0] + w1 * b.a[0]) + w2 * c.a[0]) / num;
-    const float tv = ((w0 * a.a[1] + w1 * b.a[1]) + w2 * c.a[1]) / num;
-    tex_bilinear(v, u, tv, rgb);
-    return true;
-}
-
 // LO: lane-owned pixels with an atomic-free z-test in registers; else
 // balanced steps over (record, block) pairs with the z-keys in LDS.
 template <int TS, bool LO>
@@ -1475,48 +1253,10 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 32
     if (rerr) atomicOr(err, kErrRange);
 }
 
-// Depth noise (the appendix's noise study): a standard normal deviate per
-// pixel, added to the inverse depth times the sensor's sigma.  Philox4x64
-// with 10 rounds (Salmon, Moraes, Dror and Shaw, SC 2011) keyed by (view
-// seed, stream tag), counter (pixel index, 0, 0, 0), so each pixel draws on
-// its own, whatever thread renders it; the top 24 bits of the first two
-// words feed the Box-Muller transform.
-constexpr uint64_t kPhiloxM0 = 0xD2E7470EE14C6C93ull;
-constexpr uint64_t kPhiloxM1 = 0xCA5A826395121157ull;
-constexpr uint64_t kPhiloxW0 = 0x9E3779B97F4A7C15ull;   // Weyl key increments
-constexpr uint64_t kPhiloxW1 = 0xBB67AE8584CAA73Bull;
-constexpr uint64_t kDepthNoiseTag = 0x6465707468ull;    // "depth"
-
-__device__ __forceinline__ float depth_noise_normal(uint64_t seed, uint64_t pixel)
-{
-    uint64_t c0 = pixel, c1 = 0, c2 = 0, c3 = 0;
-    uint64_t k0 = seed, k1 = kDepthNoiseTag;
-#pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        const uint64_t hi0 = __umul64hi(kPhiloxM0, c0), lo0 = kPhiloxM0 * c0;
-        const uint64_t hi1 = __umul64hi(kPhiloxM1, c2), lo1 = kPhiloxM1 * c2;
-        c0 = hi1 ^ c1 ^ k0;
-        c1 = lo1;
-        c2 = hi0 ^ c3 ^ k1;
-        c3 = lo0;
-        k0 += kPhiloxW0;
-        k1 += kPhiloxW1;
-    }
-    const float u1 = (float)((uint32_t)(c0 >> 40) + 1u) * 0x1p-24f;   // (0, 1]
-    const float u2 = (float)(uint32_t)(c1 >> 40) * 0x1p-24f;          // [0, 1)
-    return sqrtf(-2.0f * logf(u1)) * cospif(2.0f * u2);
-}
-
 // Resolve bands: 32 x 2 pixels of one view per wave (one lane per pixel,
 // four 8-pixel tiles side by side).  Each lane merges its pixel's segment
 // winners (largest 1/w, smaller key on a tie: the same order-free rule) and
-// shades it.  A band row is 96 bytes of RGB at a multiple of 96 (three
-// whole 32-byte sectors) and 128 bytes of depth, index or instance (one
-// whole line): the RGB bytes go through LDS so that the wave stores them as
-// words, and every sector the band writes is written once and whole.
-constexpr int kBandW = 32, kBandH = 2;
-constexpr int kBandThreads = kBandW * kBandH;   // one wave
-
+// shades it.
 template <int TS>
 __global__ __launch_bounds__(kBandThreads) void k_resolve(const DView *__restrict__ views,
                                                           const uint32_t *__restrict__ lview,
@@ -1529,7 +1269,7 @@ __global__ __launch_bounds__(kBandThreads) void k_resolve(const DView *__restric
 {
     constexpr int NT = TS * TS;
     constexpr int NS = TS / 8;
-    __shared__ __align__(16) uint8_t s_rgb[kBandH * kBandW * 3];
+    __shared__ __align__(16) uint8_t s_rgb[kBandRgb];
     uint32_t lo = 0, hi = nl - 1;
     const uint32_t blk = blockIdx.x;
     while (lo < hi) {
@@ -1547,7 +1287,8 @@ __global__ __launch_bounds__(kBandThreads) void k_resolve(const DView *__restric
     const uint32_t cx = lane % kBandW, cy = lane / kBandW;   // position in the band
     const int pi = (int)(x0 + cx), pj = (int)(y0 + cy);
     const bool in = pi < (int)W && pj < (int)H;
-    uint32_t rgb[3] = {0, 0, 0};
+    float best_rho = 0.0f;
+    uint32_t best_key = kNone;
     if (in) {
         const uint32_t tile = (uint32_t)(pj / TS) * v.tiles_x + (uint32_t)(pi / TS);
         const uint32_t sub = (uint32_t)(((pj % TS) / 8) * NS + (pi % TS) / 8);
@@ -1555,8 +1296,6 @@ __global__ __launch_bounds__(kBandThreads) void k_resolve(const DView *__restric
         const uint32_t ns = tile_segments(tile_count[tglob], tile_off[tglob], v.ts_log2);
         const uint32_t first = tile_item[tglob];
         const uint32_t slot = sub * 64u + (uint32_t)((pj % 8) * 8 + (pi % 8));
-        float best_rho = 0.0f;
-        uint32_t best_key = kNone;
         for (uint32_t s = 0; s < ns; ++s) {
             const uint2 pr = partial[(size_t)(first + s) * NT + slot];
             const float rho = __uint_as_float(pr.x);
@@ -1565,48 +1304,8 @@ __global__ __launch_bounds__(kBandThreads) void k_resolve(const DView *__restric
                 best_key = pr.y;
             }
         }
-        float depth = 0.0f;
-        if (best_key != kNone) {
-            // the depth is the reciprocal of the winning key's 1/w (the value
-            // a rebuild of the triangle would compute again); colour needs
-            // the rebuild
-            depth = 1.0f / best_rho;
-            if (v.rgb && !(v.tex ? resolve_tex(v, best_key, pi, pj, rgb) : resolve(v, best_key, pi, pj, rgb)))
-                atomicOr(err, kErrResolve);
-        }
-        const size_t p = (size_t)pj * W + (size_t)pi;
-        if (v.noise_sigma > 0.0f && best_key != kNone) {
-            const float rp = best_rho + v.noise_sigma * depth_noise_normal(v.noise_seed, (uint64_t)p);
-            depth = rp > 0.0f ? 1.0f / rp : 0.0f;
-        }
-        if (v.depth) gmem_out(v.depth)[p] = depth;
-        if (v.tri) gmem_out(v.tri)[p] = best_key == kNone ? kNone : (best_key >> 1);
-        if (v.sem) gmem_out(v.sem)[p] = best_key == kNone ? kNone : gmem(v.inst)[best_key >> 1];
     }
-    if (!v.rgb) return;
-    auto *o = gmem_out(v.rgb);
-    const uint32_t wpx = min((uint32_t)kBandW, W - x0), rows = min((uint32_t)kBandH, H - y0);
-    if ((W % 4u) == 0 && (reinterpret_cast<uintptr_t>(v.rgb) % 4u) == 0) {
-        // rows of 3 wpx bytes start on a word (the image does, W and x0 are
-        // multiples of 4): stage the band's bytes, store words
-        constexpr uint32_t kRowWords = kBandW * 3u / 4u;   // 24
-        s_rgb[3 * lane] = (uint8_t)rgb[0];
-        s_rgb[3 * lane + 1] = (uint8_t)rgb[1];
-        s_rgb[3 * lane + 2] = (uint8_t)rgb[2];
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const uint32_t r = lane / kRowWords, d = lane % kRowWords;
-        if (lane < kBandH * kRowWords && r < rows && d < wpx * 3u / 4u) {
-            auto *dst = reinterpret_cast<__attribute__((address_space(1))) uint32_t *>(
-                o + ((size_t)(y0 + r) * W + x0) * 3u);
-            dst[d] = reinterpret_cast<const uint32_t *>(s_rgb)[lane];
-        }
-    } else if (in) {
-        auto *q = o + 3 * ((size_t)pj * W + (size_t)pi);
-        q[0] = (uint8_t)rgb[0];
-        q[1] = (uint8_t)rgb[1];
-        q[2] = (uint8_t)rgb[2];
-    }
+    shade_band<kBandW, kBandH>(v, x0, y0, pi, pj, in, best_rho, best_key, s_rgb, err);
 }
 
 // ------------------------------------------------------------ host side
@@ -1654,6 +1353,7 @@ int raster_blocks_per_cu(int ts, bool lane_owned)
 
 hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
 {
+    if (L.direct) return launch_direct(L, s);
     const uint32_t nreset = L.nviews > L.ntiles ? L.nviews : L.ntiles;
     mark(L, 0, s);
     hipLaunchKernelGGL(k_reset, dim3(cdiv(nreset > 4 ? nreset : 4, 256)), dim3(256), 0, s, L.ctr,

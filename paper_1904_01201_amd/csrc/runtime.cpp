@@ -11,6 +11,9 @@ namespace habmi {
 
 static constexpr float kDefaultBinFactor = 2.0f;
 static constexpr uint32_t kDefaultTile = 16;
+// Pixels + triangles / 8 up to which the direct path draws a launch, and a
+// half of a split batch.
+static constexpr uint64_t kDirectSize = 1200 * 1024, kDirectHalf = 640 * 1024;
 static constexpr uint64_t kIndexLimit = 1ull << 31; // per launch: survivors, bins, tiles
 
 static inline uint32_t cdiv(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
@@ -202,6 +205,7 @@ void Workspace::reserve_planning(uint32_t n, size_t desc_bytes)
 {
     desc.reserve(desc_bytes);
     dv.reserve(n);
+    tpre.reserve(n);
     for (int c = 0; c < 3; ++c) {
         lview[c].reserve(n);
         lpre[c].reserve(n);
@@ -313,6 +317,55 @@ uint32_t choose_tile(hab_context *ctx, const Scene *sc, const hab_sensor *s, con
 // ---------------------------------------------------------------- planning
 static inline uint32_t ts_log2(uint32_t ts) { return ts == 8 ? 3u : ts == 16 ? 4u : 5u; }
 
+// Does the direct path draw this launch?  It serves launches that ask for
+// nothing the tile lists alone provide (a tiling, a list capacity, the
+// lane-owned z-test, work counters), while they are small: the tile lists
+// take eight dependent kernels whatever the size, the direct path four, but it
+// sets up a triangle once per tile its cluster meets.  Measured (us a launch,
+// tile lists against direct): one 128 x 128 view of 2k triangles 58 / 37, one
+// 256 x 256 view of 200k 105 / 56, of 1M 133 / 67, four of 1M 161 / 140, eight
+// of 200k 113 / 108, eight 512 x 384 views of 1M 296 / 348.  The two halves of
+// a split batch overlap, which helps the tile lists more: 40 views of 128 x 128
+// over 75k triangles 144 / 133, 100 of 96 x 72 161 / 215.
+static bool direct_launch(const ViewReq *v, uint32_t n, const PlanOpts &o)
+{
+    if (o.tile_lists || o.tile_size || o.bin_factor > 0.0f || o.tile_cap || o.lane_owned_z || o.count_work) return false;
+    uint64_t size = 0;
+    for (uint32_t k = 0; k < n; ++k)
+        size += (uint64_t)v[k].sensor.width * v[k].sensor.height + v[k].scene->T / 8;
+    return size <= (o.half ? kDirectHalf : kDirectSize);
+}
+
+// Tile edge and shares of a direct launch.  The edge follows the largest
+// scene (finer triangles, larger tiles: fewer clusters meet several), and
+// grows where there are many tiles anyway.  The shares give each wave of a
+// block one or two clusters to draw, up to a round or two of resident blocks:
+// of a view's clusters about a quarter is in sight, each about as large as an
+// equal part of four times the image, and it meets every tile that it touches.
+// (One 256 x 256 view of 200k triangles: 64-pixel tiles with 4 / 16 / 64 shares
+// take 105 / 57 / 66 us, 32-pixel tiles with 16 take 56.)
+static void choose_tiles(const std::vector<DView> &dv, uint32_t max_t, uint32_t *edge, uint32_t *shares)
+{
+    const uint32_t n = (uint32_t)dv.size();
+    uint32_t e = max_t >= 128000 ? 64u : max_t >= 10000 ? 32u : 16u;
+    uint64_t tiles = 0;
+    for (;; e *= 2) {
+        tiles = 0;
+        for (const DView &d : dv) tiles += (uint64_t)cdiv(d.W, e) * cdiv(d.H, e);
+        if (e == 64 || tiles <= (max_t >= 10000 ? 200u : 1024u)) break;
+    }
+    double per_tile = 0.0;   // clusters that meet a tile, over the launch
+    for (const DView &d : dv) {
+        const double seen = std::max(1.0, 0.27 * cdiv(d.T, kCluster));
+        const double across = 1.0 + std::sqrt(4.0 * d.W * d.H / seen) / e;
+        per_tile += std::min(seen * across * across / ((double)cdiv(d.W, e) * cdiv(d.H, e)), seen);
+    }
+    const double want = std::min(1.5 * per_tile / n / (e == 64 ? 8 : 4), 256.0);
+    const double most = (max_t >= 500000 ? 2048.0 : 1024.0) / (double)std::max<uint64_t>(tiles, 1);
+    *edge = e;
+    *shares = (uint32_t)std::max(1.0, std::min(want, most));
+}
+
 hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_t n,
                       const PlanOpts &o, Plan &plan, std::vector<uint8_t> &desc)
 {
@@ -331,6 +384,7 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         lview[c].clear();
         lpre[c].clear();
     }
+    const bool direct = direct_launch(v, n, o);
     uint64_t tile_total = 0, surv_total = 0, bin_total = 0, pair_total = 0;
     for (uint32_t k = 0; k < n; ++k) {
         const ViewReq &r = v[plan.order[k]];
@@ -381,7 +435,8 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         d.count_work = o.count_work ? 1u : 0u;
         d.pair_base = (uint32_t)pair_total;
         pair_total += cdiv(d.T, kCluster);
-        const int c = ts == 8 ? 0 : ts == 16 ? 1 : 2;
+        // one resolve list for a direct launch, under the first view's tile size
+        const int c = (int)(direct ? dv[0].ts_log2 : d.ts_log2) - 3;
         lview[c].push_back(k);
     }
     // Raster blocks are dispatched roughly in block order: put the views of
@@ -402,29 +457,24 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         return HAB_ERR_CAPACITY;
 
     const uint64_t npairs = pair_total;
+    uint32_t max_t = 0;
+    for (uint32_t k = 0; k < n; ++k) max_t = std::max(max_t, dv[k].T);
 
     // descriptor block
+    uint32_t nclass[3] = {0, 0, 0};
+    for (uint32_t k = 0; k < n; ++k) ++nclass[dv[k].ts_log2 - 3];
     size_t off = 0;
     plan.off_views = off;
     off = align256(off + sizeof(DView) * n);
     for (int c = 0; c < 3; ++c) {
         plan.off_lview[c] = off;
-        off = align256(off + 4 * lview[c].size());
+        off = align256(off + 4 * (size_t)nclass[c]);
         plan.off_lpre[c] = off;
-        off = align256(off + 4 * lpre[c].size());
+        off = align256(off + 4 * (size_t)nclass[c]);
     }
     plan.off_ctl = off;          // control slot (the stepper's device-pose pointer)
     off = align256(off + 16);
     plan.desc_bytes = off;
-    desc.resize(off);
-    std::memcpy(desc.data() + plan.off_views, dv.data(), sizeof(DView) * n);
-
-    for (int c = 0; c < 3; ++c) {
-        if (!lview[c].empty()) {
-            std::memcpy(desc.data() + plan.off_lview[c], lview[c].data(), 4 * lview[c].size());
-            std::memcpy(desc.data() + plan.off_lpre[c], lpre[c].data(), 4 * lpre[c].size());
-        }
-    }
     // scratch
     plan.off_ctr = off;
     off = align256(off + sizeof(DViewCounters) * n);
@@ -449,10 +499,11 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
     // raster work items: a tile holds at most one item per kSegPerTile*TS^2
     // list entries (plus one), so a view needs at most tiles + bin_cap / S
     uint64_t item_cap[3] = {0, 0, 0};
+    for (uint32_t k = 0; k < n; ++k) {
+        const uint64_t S = (uint64_t)kSegPerTile << (2 * dv[k].ts_log2);
+        item_cap[dv[k].ts_log2 - 3] += (uint64_t)dv[k].tiles_x * dv[k].tiles_y + (dv[k].bin_cap + S - 1) / S;
+    }
     for (int c = 0; c < 3; ++c) {
-        const uint64_t S = (uint64_t)kSegPerTile << (6 + 2 * c);
-        for (uint32_t k : lview[c])
-            item_cap[c] += (uint64_t)dv[k].tiles_x * dv[k].tiles_y + (dv[k].bin_cap + S - 1) / S;
         plan.off_items[c] = off;
         off = align256(off + 8 * item_cap[c]);
         plan.off_partial[c] = off;
@@ -463,8 +514,58 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
     LaunchPlan &L = plan.L;
     L = LaunchPlan{};
     L.nviews = n;
-    uint32_t max_t = 0;
-    for (uint32_t k = 0; k < n; ++k) max_t = std::max(max_t, dv[k].T);
+    L.direct = direct;
+    std::vector<uint32_t> &tpre = ws.tpre;
+    const int c0 = (int)dv[0].ts_log2 - 3;
+    if (direct) {
+        // its own layout of the same arena, whose size stays the tile lists'
+        // (they take more: 24 B a triangle and 4 KiB a view against 4 B, and
+        // at least as many z-keys), so a launch fits a given scratch or does
+        // not whichever path draws it
+        uint64_t znum = 0;
+        for (uint32_t k = 0; k < n; ++k) {
+            DView &d = dv[k];
+            d.zoff_lo = (uint32_t)znum;
+            d.zoff_hi = (uint32_t)(znum >> 32);
+            znum += ((uint64_t)d.W * d.H + 1) & ~1ull;
+        }
+        choose_tiles(dv, max_t, &L.tile_edge, &L.shares);
+        tpre.clear();
+        uint64_t pre = 0;
+        for (uint32_t k : lview[c0]) {
+            tpre.push_back((uint32_t)pre);
+            pre += (uint64_t)cdiv(dv[k].W, L.tile_edge) * cdiv(dv[k].H, L.tile_edge) * L.shares;
+        }
+        if (pre >= kIndexLimit) return HAB_ERR_CAPACITY;
+        L.tile_grid = (uint32_t)pre;
+        L.znum = znum;
+        size_t x = align256(sizeof(DView) * n);
+        plan.off_lview[c0] = x;
+        x = align256(x + 4 * (size_t)n);
+        plan.off_lpre[c0] = x;
+        x = align256(x + 4 * (size_t)n);
+        plan.off_tpre = x;
+        x = align256(x + 4 * (size_t)n);
+        plan.off_ctl = x;
+        x = align256(x + 16);
+        plan.desc_bytes = x;
+        plan.off_ctr = x;
+        x = align256(x + sizeof(DViewCounters) * n);
+        plan.off_recs = x;
+        x = align256(x + sizeof(ClusterRec) * kBuckets * std::max<uint64_t>(npairs, 1));
+        plan.off_zbuf = x;
+        x = align256(x + 8 * znum);
+        plan.arena_bytes = std::max(plan.arena_bytes, x);
+    }
+    desc.resize(plan.desc_bytes);
+    std::memcpy(desc.data() + plan.off_views, dv.data(), sizeof(DView) * n);
+    for (int c = 0; c < 3; ++c) {
+        if (!lview[c].empty()) {
+            std::memcpy(desc.data() + plan.off_lview[c], lview[c].data(), 4 * lview[c].size());
+            std::memcpy(desc.data() + plan.off_lpre[c], lpre[c].data(), 4 * lpre[c].size());
+        }
+    }
+    if (direct) std::memcpy(desc.data() + plan.off_tpre, tpre.data(), 4 * tpre.size());
     L.cull_blocks = std::max<uint32_t>(1, cdiv(cdiv(max_t, kCluster), 256));
     // one round of resident setup blocks (the waves take static shares of
     // the work, so a second partial round would only add a tail)
@@ -512,6 +613,9 @@ void bind_plan(Plan &plan, void *arena, uint32_t *err)
     L.tile_item = reinterpret_cast<uint32_t *>(b + plan.off_titem);
     L.queue = reinterpret_cast<DQueue *>(b + plan.off_queue);
     L.pairs = reinterpret_cast<uint32_t *>(b + plan.off_pairs);
+    L.recs = reinterpret_cast<ClusterRec *>(b + plan.off_recs);
+    L.tpre = reinterpret_cast<const uint32_t *>(b + plan.off_tpre);
+    L.zbuf = reinterpret_cast<unsigned long long *>(b + plan.off_zbuf);
     L.err = err;
     for (int c = 0; c < 3; ++c) L.items[c] = reinterpret_cast<uint2 *>(b + plan.off_items[c]);
     for (int k = 0; k < L.nraster; ++k) {
@@ -541,8 +645,10 @@ Footprint footprint(const ViewReq *v, uint32_t n, const PlanOpts &o, hab_context
                  items * 8ull * (1 + (uint64_t)ts * ts);
     }
     f.desc_bytes = n * (sizeof(DView) + 32) + 4096;
-    // + the work queues and the padding of the plan's 24 aligned arrays
-    f.arena_bytes = bytes + f.desc_bytes + sizeof(DQueue) + 32 * 256;
+    // + the work queues and the padding of the plan's 24 aligned arrays; a
+    // multiple of 256, so that regions packed one after another in a pool
+    // keep the arena's alignment (64-bit atomics need theirs)
+    f.arena_bytes = align256(bytes + f.desc_bytes + sizeof(DQueue) + 31 * 256);
     (void)tiles;
     return f;
 }
@@ -558,6 +664,7 @@ hab_status render_views(hab_context *ctx, Workspace &ws, const ViewReq *v, uint3
     if (st != HAB_OK) return st;
     st = ws.ensure(plan.arena_bytes);
     if (st != HAB_OK) return st;
+    if (reinterpret_cast<uintptr_t>(ws.arena) % 256) return HAB_ERR_DEVICE;   // a misplaced region: 64-bit atomics would fault
     if (ws.has_done && ws.last_stream != s) HAB_HIP(hipStreamWaitEvent(s, ws.done, 0));
     void *host;
     int slot;
@@ -576,7 +683,7 @@ hab_status render_views(hab_context *ctx, Workspace &ws, const ViewReq *v, uint3
             ctx->prof_sets.push_back(fresh);
         }
         ps = &ctx->prof_sets[ctx->prof_used++];
-        ps->mask = 0x1Fu | (1u << kPhaseResolve);
+        ps->mask = (plan.L.direct ? 0x3u : 0x1Fu) | (1u << kPhaseResolve);
         for (int k = 0; k < plan.L.nraster; ++k)
             if (plan.L.raster[k].blocks)
                 ps->mask |= 1u << (plan.L.raster[k].ts == 8 ? 5 : plan.L.raster[k].ts == 16 ? 6 : 7);
@@ -658,6 +765,8 @@ hab_status render_split(hab_context *ctx, const ViewReq *v, uint32_t n, const Pl
     hab_status st = ensure_aux(ctx);
     if (st != HAB_OK) return st;
     // views 0, 2, 4, ... and 1, 3, 5, ...: halves of like composition
+    PlanOpts oh = o;
+    oh.half = true;
     std::vector<ViewReq> half[2];
     std::vector<hab_view_stats> hs[2];
     for (int h = 0; h < 2; ++h) {
@@ -667,10 +776,10 @@ hab_status render_split(hab_context *ctx, const ViewReq *v, uint32_t n, const Pl
     for (uint32_t k = 0; k < n; ++k) half[k & 1u].push_back(v[k]);
     HAB_HIP(hipEventRecord(ctx->fork_ev, s));
     HAB_HIP(hipStreamWaitEvent(ctx->aux, ctx->fork_ev, 0));
-    st = render_all(ctx, ctx->ws, half[0].data(), (uint32_t)half[0].size(), o, s,
+    st = render_all(ctx, ctx->ws, half[0].data(), (uint32_t)half[0].size(), oh, s,
                     stats ? hs[0].data() : nullptr);
     if (st == HAB_OK)
-        st = render_all(ctx, ctx->ws2, half[1].data(), (uint32_t)half[1].size(), o, ctx->aux,
+        st = render_all(ctx, ctx->ws2, half[1].data(), (uint32_t)half[1].size(), oh, ctx->aux,
                         stats ? hs[1].data() : nullptr);
     // the join is enqueued whatever happened, so that s is ordered after
     // everything the call put on the second stream

@@ -93,6 +93,8 @@ struct PlanOpts {
     bool count_work = false;    // accumulate bbox tests / covered fragments
     bool one_sequence = false;  // never split a batch into two launch sequences
     bool lane_owned_z = false;  // the atomic-free lane-owned z-test
+    bool tile_lists = false;    // never the direct path
+    bool half = false;          // a half of a split batch: its other half runs beside it
 };
 
 // Sizes of one launch sequence; used for memory admission as well.
@@ -125,7 +127,7 @@ struct Workspace {
     // host-side planning buffers, kept to avoid reallocation
     std::vector<uint8_t> desc;
     std::vector<DView> dv;
-    std::vector<uint32_t> lview[3], lpre[3];
+    std::vector<uint32_t> lview[3], lpre[3], tpre;
     ~Workspace();
     hab_status ensure(size_t bytes);
     hab_status staging(size_t bytes, void **host, int *slot);
@@ -151,6 +153,7 @@ struct Plan {
     size_t off_skey = 0, off_sbox = 0, off_bins = 0;
     size_t off_titem = 0, off_queue = 0, off_items[3] = {0, 0, 0}, off_partial[3] = {0, 0, 0};
     size_t off_pairs = 0;
+    size_t off_recs = 0, off_zbuf = 0, off_tpre = 0;   // direct path: visible cluster records, z-keys, tile prefix
     size_t off_ctl = 0;              // 16 B control slot in the descriptor block
     std::vector<uint32_t> order;     // sorted position -> caller index
     uint32_t n = 0;

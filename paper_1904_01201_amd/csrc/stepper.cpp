@@ -128,6 +128,7 @@ hab_status hab_stepper_create(hab_context *ctx, const hab_view *views, uint32_t 
             s = to_view_req(views[k], h.req.back());
         }
         PlanOpts o;
+        o.half = st->nh == 2;
         if (opts) {
             o.tile_size = opts->tile_size;
             o.bin_factor = opts->bin_factor;

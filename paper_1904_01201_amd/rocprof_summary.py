@@ -80,7 +80,7 @@ def copy_scale(d: str, counter: str) -> float:
 
 # the sources the render kernels are compiled from: a change to any of them
 # invalidates recorded traffic
-KERNEL_SOURCES = ("kernels.hip", "kernels.h", "raster_math.h", "dtypes.h")
+KERNEL_SOURCES = ("kernels.hip", "draw.hip", "kernels.h", "device_util.h", "shade.h", "raster_math.h", "dtypes.h")
 
 
 def source_hash() -> str:
