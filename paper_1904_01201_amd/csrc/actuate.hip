@@ -6,14 +6,13 @@
 //
 // Layout: each obstacle set carries a uniform grid built at upload (cells
 // of 0.1-0.5 m sized to the segments; a cell lists every segment whose
-// bounding box overlaps it).  A
-// group of G lanes moves one agent (G = 64 for small batches, where one
-// lane per agent would leave the chip idle and expose the dependent
-// cell -> list -> segment loads; fewer for large ones): per pass each lane
-// takes every G-th entry of the cells under the box swept by the disc
-// (grown by the radius and a 0.1 mm margin), runs the fp64 contact test on
-// the segments whose own box meets the swept box, and the group reduces
-// the lanes' earliest contacts with shuffles.
+// bounding box overlaps it, as a copy of its coordinates, so that the cells
+// of a grid row are one contiguous run).  A group of G lanes moves one agent:
+// per pass its lanes load the runs under the box swept by the disc (grown by
+// the radius and a 0.1 mm margin) together, one entry each per step, list the
+// segments whose own box meets the swept box in LDS, run the fp64 contact
+// test on the listed ones with every lane at work, and reduce the earliest
+// contact with shuffles.
 // A segment outside that box cannot be touched during the move, and the
 // winning contact is chosen by an explicit order (time, then segment index,
 // then interior before first before second endpoint), so the result is the
@@ -43,6 +42,7 @@ struct alignas(16) NavDesc {
     const float4 *seg;          // [n] (x0, z0, x1, z1)
     const uint32_t *cell_start; // [gx * gz + 1]
     const uint32_t *items;      // segment indices, per cell
+    const float4 *iseg;         // their segments, per cell
     float ox, oz;               // grid origin
     float inv_h, h;             // 1 / cell edge, cell edge
     uint32_t gx, gz;            // cells per axis (0: no segments)
@@ -61,6 +61,7 @@ namespace habmi {
 namespace {
 
 constexpr int kActBlock = 256;
+constexpr int kActList = 96;      // segments a group lists before it tests them (at least 64 + 1)
 constexpr int kSlidePasses = 4;
 constexpr double kSkin = 1e-6;
 
@@ -143,28 +144,157 @@ __device__ __forceinline__ int cell_of(float q, float o, float inv_h, uint32_t g
     return (int)fminf(fmaxf(c, 0.0f), (float)(g - 1u));
 }
 
+// This group's part of a wave's ballot.
+template <int G>
+__device__ __forceinline__ uint64_t group_bits(uint64_t m)
+{
+    if constexpr (G == 64) return m;
+    return (m >> (__lane_id() & ~(uint32_t)(G - 1))) & ((1ull << G) - 1ull);
+}
+
 // Lexicographic minimum of the group's contacts (found first, then t, then
 // code): every lane ends with the group's winner.
 template <int G>
 __device__ __forceinline__ void group_min(bool &found, double &bt, uint32_t &bcode, double &bnx, double &bnz)
 {
+    double t = found ? bt : INFINITY;
+    uint32_t code = found ? bcode : 0xFFFFFFFFu;
+    const double mt = t;
+    const uint32_t mcode = code;
 #pragma unroll
     for (int off = G / 2; off > 0; off >>= 1) {
-        const int of = __shfl_xor((int)found, off, G);
-        const double ot = __shfl_xor(bt, off, G);
-        const uint32_t oc = (uint32_t)__shfl_xor((int)bcode, off, G);
-        const double ox = __shfl_xor(bnx, off, G), oz = __shfl_xor(bnz, off, G);
-        if (of && (!found || ot < bt || (ot == bt && oc < bcode))) {
-            found = true;
-            bt = ot;
-            bcode = oc;
-            bnx = ox;
-            bnz = oz;
+        const double ot = __shfl_xor(t, off, G);
+        const uint32_t oc = (uint32_t)__shfl_xor((int)code, off, G);
+        if (ot < t || (ot == t && oc < code)) {
+            t = ot;
+            code = oc;
         }
     }
+    const uint64_t won = group_bits<G>(__ballot(found && mt == t && mcode == code));
+    found = won != 0;
+    if (!found) return;
+    const int w = __ffsll((long long)won) - 1;
+    bt = t;
+    bcode = code;
+    bnx = __shfl(bnx, w, G);
+    bnz = __shfl(bnz, w, G);
 }
 
+// First contact of the disc at p moving by d (a = |d|^2 > 0) with the segments
+// of D, by a group of G lanes; false: none.
 template <int G>
+__device__ __forceinline__ bool first_contact(const NavDesc &D, uint32_t *list, uint32_t lane, double radius, double px,
+                                              double pz, double dx, double dz, double a, double &bt, double &bnx,
+                                              double &bnz)
+{
+    bool found = false;
+    uint32_t bcode = 0;
+    const float grow = (float)radius + 1e-4f;
+    const float qx0 = (float)fmin(px, px + dx) - grow, qx1 = (float)fmax(px, px + dx) + grow;
+    const float qz0 = (float)fmin(pz, pz + dz) - grow, qz1 = (float)fmax(pz, pz + dz) + grow;
+    if (!(D.gx && qx1 >= D.ox && qz1 >= D.oz && qx0 <= D.ox + D.h * (float)D.gx && qz0 <= D.oz + D.h * (float)D.gz))
+        return false;
+    const int cx0 = cell_of(qx0, D.ox, D.inv_h, D.gx), cx1 = cell_of(qx1, D.ox, D.inv_h, D.gx);
+    const int cz0 = cell_of(qz0, D.oz, D.inv_h, D.gz), cz1 = cell_of(qz1, D.oz, D.inv_h, D.gz);
+    // the motion's unit vector, and how far from it a touched point can lie
+    // (a motion too short to normalise excludes nothing)
+    const double len_d = sqrt(a), ux = dx / len_d, uz = dz / len_d;
+    const double reach = a > 1e-290 ? radius + 1e-4 : (double)INFINITY;
+    uint32_t count = 0;
+    // test the listed segments, G at a time
+    auto test = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        for (uint32_t e = lane; e < count; e += G) {
+            const uint32_t i = list[e];
+            seg_contact(D.iseg[i], D.items[i], radius, px, pz, dx, dz, a, found, bt, bcode, bnx, bnz);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        count = 0;
+    };
+    // up to G grid rows at once: lane r holds row r's run and where it starts
+    // among the rows' entries
+    for (int zb = cz0; zb <= cz1; zb += G) {
+        const int rows = min(cz1 - zb + 1, G);
+        uint32_t begin = 0, len = 0;
+        if ((int)lane < rows) {
+            const uint32_t c = (uint32_t)(zb + (int)lane) * D.gx;
+            begin = D.cell_start[c + (uint32_t)cx0];
+            len = D.cell_start[c + (uint32_t)cx1 + 1u] - begin;
+        }
+        uint32_t end = len;
+#pragma unroll
+        for (int off = 1; off < G; off <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)end, off, G);
+            if ((int)lane >= off) end += y;
+        }
+        const uint32_t total = (uint32_t)__shfl((int)end, G - 1, G);
+        const uint32_t first = begin - (end - len);   // entry e of the row is at first + e
+        for (uint32_t e0 = 0; e0 < total; e0 += G) {
+            const uint32_t e = e0 + lane;
+            uint32_t at = (uint32_t)__shfl((int)first, 0, G);
+            for (int r = 1; r < rows; ++r) {
+                const uint32_t re = (uint32_t)__shfl((int)(end - len), r, G);
+                const uint32_t rf = (uint32_t)__shfl((int)first, r, G);
+                if (e >= re) at = rf;
+            }
+            bool near = false;
+            if (e < total) {
+                // a segment wholly beyond one side of the strip that the disc
+                // sweeps, or before its start or past its end, cannot be touched
+                const float4 sg = D.iseg[at + e];
+                const double gx = sg.x - px, gz = sg.y - pz, hx = sg.z - px, hz = sg.w - pz;
+                const double gu = gx * ux + gz * uz, gv = gx * uz - gz * ux;
+                const double hu = hx * ux + hz * uz, hv = hx * uz - hz * ux;
+                near = !(fmin(gu, hu) > reach + len_d || fmax(gu, hu) < -reach || fmin(gv, hv) > reach ||
+                         fmax(gv, hv) < -reach);
+            }
+            const uint64_t m = group_bits<G>(__ballot(near));
+            if (near) list[count + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = at + e;
+            count += (uint32_t)__popcll(m);
+            if (count > (uint32_t)(kActList - G)) test();
+        }
+    }
+    if (count) test();
+    group_min<G>(found, bt, bcode, bnx, bnz);
+    return found;
+}
+
+// Agent k's state after its action, and its camera pose.
+__device__ __forceinline__ void put_agent(uint32_t k, const hab_agent &g, bool hit, hab_agent *__restrict__ agents,
+                                          uint8_t *__restrict__ collided, float *__restrict__ poses, float cam_h)
+{
+    agents[k] = g;
+    if (collided) collided[k] = hit ? 1 : 0;
+    if (!poses) return;
+    float *o = poses + 12ull * k;
+    const float fx = (float)g.fx, fz = (float)g.fz;
+    o[0] = (float)g.x;
+    o[1] = cam_h;
+    o[2] = (float)g.z;
+    o[3] = -fz;
+    o[4] = 0.0f;
+    o[5] = -fx;
+    o[6] = 0.0f;
+    o[7] = 1.0f;
+    o[8] = 0.0f;
+    o[9] = fx;
+    o[10] = 0.0f;
+    o[11] = -fz;
+}
+
+// A block serves A agents: those that stop or turn are done by a lane each,
+// the others are listed and its groups take them one by one, a pass of
+// collide-and-slide per step, so that a wave's groups stay at work whatever
+// the actions and however often each agent slides.
+//
+// Bound by fp64 issue at many agents (23 M wave instructions for 65,536, 42%
+// of the wave cycles at work, 35% of the lanes) and by the chain cell runs ->
+// segments -> contact -> reduction at few (about 5 us a pass).  65,536 agents
+// against the bench meshes' cross-sections: 1,810 us with one lane per agent
+// that walked cell by cell through index lists, 184 us with 16 lanes over
+// contiguous runs and LDS lists, 166 us with the strip test in front, 135 us
+// with the list of forward agents; 64 agents 55 -> 24 us.
+template <int G, int A>
 __global__ __launch_bounds__(kActBlock) void k_actuate(const NavDesc *__restrict__ navs,
                                                        const uint32_t *__restrict__ nav_of,
                                                        uint32_t n, hab_agent *__restrict__ agents,
@@ -172,92 +302,79 @@ __global__ __launch_bounds__(kActBlock) void k_actuate(const NavDesc *__restrict
                                                        uint8_t *__restrict__ collided,
                                                        float *__restrict__ poses, ActParams P)
 {
-    const uint32_t gid = blockIdx.x * kActBlock + threadIdx.x;
-    const uint32_t k = gid / G, lane = gid % G;
-    // whole groups leave together (n agents fill n * G lanes; groups never
-    // straddle a wave), so the shuffles below see only live lanes
-    if (k >= n) return;
-    hab_agent g = agents[k];
-    const uint32_t act = actions[k];
-    if (act == HAB_ACT_LEFT || act == HAB_ACT_RIGHT) {
-        const double s = act == HAB_ACT_LEFT ? P.ts : -P.ts;
-        const double fx = g.fx * P.tc + g.fz * s;
-        const double fz = g.fz * P.tc - g.fx * s;
-        g.fx = fx;
-        g.fz = fz;
-    }
-    bool hit = false;
-    if (act == HAB_ACT_FORWARD) {
-        const NavDesc D = navs[nav_of[k]];
-        double px = g.x, pz = g.z;
-        double dx = P.step * g.fx, dz = P.step * g.fz;
-        const float grow = (float)P.radius + 1e-4f;
-        for (int pass = 0; pass < kSlidePasses; ++pass) {
-            const double a = dx * dx + dz * dz;
-            if (!(a > 0.0)) break;
-            bool found = false;
-            double bt = 0.0, bnx = 0.0, bnz = 0.0;
-            uint32_t bcode = 0;
-            const float qx0 = (float)fmin(px, px + dx) - grow, qx1 = (float)fmax(px, px + dx) + grow;
-            const float qz0 = (float)fmin(pz, pz + dz) - grow, qz1 = (float)fmax(pz, pz + dz) + grow;
-            const bool inside = D.gx && qx1 >= D.ox && qz1 >= D.oz && qx0 <= D.ox + D.h * (float)D.gx &&
-                                qz0 <= D.oz + D.h * (float)D.gz;
-            if (inside) {
-                const int cx0 = cell_of(qx0, D.ox, D.inv_h, D.gx), cx1 = cell_of(qx1, D.ox, D.inv_h, D.gx);
-                const int cz0 = cell_of(qz0, D.oz, D.inv_h, D.gz), cz1 = cell_of(qz1, D.oz, D.inv_h, D.gz);
-                for (int cz = cz0; cz <= cz1; ++cz)
-                    for (int cx = cx0; cx <= cx1; ++cx) {
-                        const uint32_t c = (uint32_t)cz * D.gx + (uint32_t)cx;
-                        const uint32_t i1 = D.cell_start[c + 1];
-                        for (uint32_t i = D.cell_start[c] + lane; i < i1; i += G) {
-                            const uint32_t j = D.items[i];
-                            const float4 sg = D.seg[j];
-                            if (fminf(sg.x, sg.z) > qx1 || fmaxf(sg.x, sg.z) < qx0 ||
-                                fminf(sg.y, sg.w) > qz1 || fmaxf(sg.y, sg.w) < qz0)
-                                continue;
-                            seg_contact(sg, j, P.radius, px, pz, dx, dz, a, found, bt, bcode, bnx, bnz);
-                        }
-                    }
+    // per group: the segments to test (places in iseg)
+    __shared__ uint32_t lists[kActBlock / G][kActList];
+    __shared__ uint32_t todo[A], ntodo, cursor;
+    const uint32_t lane = threadIdx.x % G;
+    uint32_t *const list = lists[threadIdx.x / G];
+    if (threadIdx.x == 0) ntodo = cursor = 0;
+    __syncthreads();
+    if (threadIdx.x < A) {
+        const uint32_t k = blockIdx.x * A + threadIdx.x;
+        const uint32_t act = k < n ? actions[k] : (uint32_t)HAB_ACT_STOP;
+        if (act == HAB_ACT_FORWARD) {
+            todo[atomicAdd(&ntodo, 1u)] = k;
+        } else if (k < n) {
+            hab_agent g = agents[k];
+            if (act == HAB_ACT_LEFT || act == HAB_ACT_RIGHT) {
+                const double s = act == HAB_ACT_LEFT ? P.ts : -P.ts;
+                const double fx = g.fx * P.tc + g.fz * s;
+                const double fz = g.fz * P.tc - g.fx * s;
+                g.fx = fx;
+                g.fz = fz;
             }
-            if (G > 1) group_min<G>(found, bt, bcode, bnx, bnz);
-            if (!found) {
-                px += dx;
-                pz += dz;
-                break;
-            }
-            hit = true;
-            double ts = bt - kSkin / sqrt(a);
-            if (ts < 0.0) ts = 0.0;
-            px += ts * dx;
-            pz += ts * dz;
-            double rx = (1.0 - ts) * dx, rz = (1.0 - ts) * dz;
-            const double dn = rx * bnx + rz * bnz;
-            rx -= dn * bnx;
-            rz -= dn * bnz;
-            dx = rx;
-            dz = rz;
+            put_agent(k, g, false, agents, collided, poses, P.cam_h);
         }
-        g.x = px;
-        g.z = pz;
     }
-    if (lane != 0) return;
-    agents[k] = g;
-    if (collided) collided[k] = hit ? 1 : 0;
-    if (poses) {
-        float *o = poses + 12ull * k;
-        const float fx = (float)g.fx, fz = (float)g.fz;
-        o[0] = (float)g.x;
-        o[1] = P.cam_h;
-        o[2] = (float)g.z;
-        o[3] = -fz;
-        o[4] = 0.0f;
-        o[5] = -fx;
-        o[6] = 0.0f;
-        o[7] = 1.0f;
-        o[8] = 0.0f;
-        o[9] = fx;
-        o[10] = 0.0f;
-        o[11] = -fz;
+    __syncthreads();
+    // whole groups take and leave agents together, so the shuffles see only
+    // live lanes
+    uint32_t k = 0;
+    int pass = kSlidePasses;   // no agent in hand
+    hab_agent g = {};
+    NavDesc D = {};
+    double dx = 0.0, dz = 0.0;
+    bool hit = false;
+    for (;;) {
+        if (pass == kSlidePasses) {
+            uint32_t e = 0;
+            if (lane == 0) e = atomicAdd(&cursor, 1u);
+            e = (uint32_t)__shfl((int)e, 0, G);
+            if (e >= ntodo) break;
+            k = todo[e];
+            g = agents[k];
+            D = navs[nav_of[k]];
+            dx = P.step * g.fx;
+            dz = P.step * g.fz;
+            hit = false;
+            pass = 0;
+        }
+        const double a = dx * dx + dz * dz;
+        bool done = !(a > 0.0);
+        if (!done) {
+            double bt = 0.0, bnx = 0.0, bnz = 0.0;
+            if (!first_contact<G>(D, list, lane, P.radius, g.x, g.z, dx, dz, a, bt, bnx, bnz)) {
+                g.x += dx;
+                g.z += dz;
+                done = true;
+            } else {
+                hit = true;
+                double ts = bt - kSkin / sqrt(a);
+                if (ts < 0.0) ts = 0.0;
+                g.x += ts * dx;
+                g.z += ts * dz;
+                double rx = (1.0 - ts) * dx, rz = (1.0 - ts) * dz;
+                const double dn = rx * bnx + rz * bnz;
+                rx -= dn * bnx;
+                rz -= dn * bnz;
+                dx = rx;
+                dz = rz;
+            }
+        }
+        if (done || ++pass == kSlidePasses) {
+            pass = kSlidePasses;
+            if (lane == 0) put_agent(k, g, hit, agents, collided, poses, P.cam_h);
+        }
     }
 }
 
@@ -378,15 +495,20 @@ __global__ __launch_bounds__(kSliceBlock) void k_slice_write(const float *__rest
 }
 
 // Free-space query: is a disc of radius r at (x, z) clear of every segment
-// (each at least r away)?  One lane per point, over the grid cells under
-// the disc's box grown by a 0.1 mm margin (a segment that comes within r
-// has its box meet the disc's, so it is listed in one of those cells);
-// the per-segment test is the fp64 point-segment distance with the
-// parameter clamped to the segment.
+// (each at least r away)?  A group of G lanes per point, over the grid cells
+// under the disc's box grown by a 0.1 mm margin (a segment that comes within r
+// has its box meet the disc's, so it is listed in one of those cells), a grid
+// row's cells as one run; the per-segment test is the fp64 point-segment
+// distance with the parameter clamped to the segment.  Bound by the address
+// unit (a lane's 16-byte loads lie where its point does): 1M points took 151 us
+// with one lane and index lists, 87 us with one lane and contiguous runs, 71 us
+// with four lanes, which share a 64-byte piece of a run.
+template <int G>
 __global__ __launch_bounds__(kActBlock) void k_nav_free(NavDesc D, const double2 *__restrict__ pts, uint32_t n,
                                                         double r, uint8_t *__restrict__ out)
 {
-    const uint32_t i = blockIdx.x * kActBlock + threadIdx.x;
+    const uint32_t gid = blockIdx.x * kActBlock + threadIdx.x;
+    const uint32_t i = gid / G, lane = gid % G;
     if (i >= n) return;
     const double2 p = pts[i];
     const double px = p.x, pz = p.y, r2 = r * r;
@@ -399,15 +521,22 @@ __global__ __launch_bounds__(kActBlock) void k_nav_free(NavDesc D, const double2
     if (inside) {
         const int cx0 = cell_of(qx0, D.ox, D.inv_h, D.gx), cx1 = cell_of(qx1, D.ox, D.inv_h, D.gx);
         const int cz0 = cell_of(qz0, D.oz, D.inv_h, D.gz), cz1 = cell_of(qz1, D.oz, D.inv_h, D.gz);
-        for (int cz = cz0; cz <= cz1 && !blocked; ++cz)
-            for (int cx = cx0; cx <= cx1 && !blocked; ++cx) {
-                const uint32_t c = (uint32_t)cz * D.gx + (uint32_t)cx;
-                const uint32_t i1 = D.cell_start[c + 1];
-                for (uint32_t k = D.cell_start[c]; k < i1; ++k) {
-                    const float4 sg = D.seg[D.items[k]];
-                    if (fminf(sg.x, sg.z) > qx1 || fmaxf(sg.x, sg.z) < qx0 || fminf(sg.y, sg.w) > qz1 ||
-                        fmaxf(sg.y, sg.w) < qz0)
-                        continue;
+        // the rows' runs as one sequence: the groups of a wave step through
+        // theirs together, whatever the rows hold
+        int cz = cz0;
+        uint32_t k = D.cell_start[(uint32_t)cz * D.gx + (uint32_t)cx0];
+        uint32_t k1 = D.cell_start[(uint32_t)cz * D.gx + (uint32_t)cx1 + 1u];
+        for (;;) {
+            while (k >= k1 && cz < cz1) {
+                ++cz;
+                k = D.cell_start[(uint32_t)cz * D.gx + (uint32_t)cx0];
+                k1 = D.cell_start[(uint32_t)cz * D.gx + (uint32_t)cx1 + 1u];
+            }
+            if (k >= k1) break;
+            if (k + lane < k1) {
+                const float4 sg = D.iseg[k + lane];
+                if (!(fminf(sg.x, sg.z) > qx1 || fmaxf(sg.x, sg.z) < qx0 || fminf(sg.y, sg.w) > qz1 ||
+                      fmaxf(sg.y, sg.w) < qz0)) {
                     const double ax = sg.x, az = sg.y;
                     const double ex = (double)sg.z - ax, ez = (double)sg.w - az;
                     const double L2 = ex * ex + ez * ez;
@@ -418,14 +547,15 @@ __global__ __launch_bounds__(kActBlock) void k_nav_free(NavDesc D, const double2
                         s = s > 1.0 ? 1.0 : s;
                     }
                     const double qx = ax + s * ex - px, qz = az + s * ez - pz;
-                    if (qx * qx + qz * qz < r2) {
-                        blocked = true;
-                        break;
-                    }
+                    blocked = qx * qx + qz * qz < r2;
                 }
             }
+            k += G;
+            if (G > 1) blocked = group_bits<G>(__ballot(blocked)) != 0;
+            if (blocked) break;
+        }
     }
-    out[i] = blocked ? 0 : 1;
+    if (lane == 0) out[i] = blocked ? 0 : 1;
 }
 
 }  // namespace
@@ -502,20 +632,24 @@ static hab_status nav_build(hab_context *ctx, const float *segments, uint32_t nu
         }
         const size_t bseg = 16ull * num_segments, bstart = 4ull * start.size(), bitems = 4ull * items.size();
         const size_t o_start = (bseg + 255) & ~(size_t)255, o_items = (o_start + bstart + 255) & ~(size_t)255;
+        const size_t o_iseg = (o_items + bitems + 255) & ~(size_t)255, biseg = 16ull * items.size();
+        std::vector<float> iseg(4 * items.size());
+        for (size_t i = 0; i < items.size(); ++i) std::memcpy(&iseg[4 * i], segments + 4ull * items[i], 16);
         DeviceGuard g(ctx->device);
         if (!g.ok) return HAB_ERR_DEVICE;
         hab_nav *n = new hab_nav();
         n->device = ctx->device;
         n->n = num_segments;
         if (num_segments) {
-            if (!dev_alloc(&n->mem, o_items + bitems)) {
+            if (!dev_alloc(&n->mem, o_iseg + biseg)) {
                 delete n;
                 return HAB_ERR_OUT_OF_MEMORY;
             }
             char *m = static_cast<char *>(n->mem);
             if (hipMemcpy(m, segments, bseg, hipMemcpyHostToDevice) != hipSuccess ||
                 hipMemcpy(m + o_start, start.data(), bstart, hipMemcpyHostToDevice) != hipSuccess ||
-                (bitems && hipMemcpy(m + o_items, items.data(), bitems, hipMemcpyHostToDevice) != hipSuccess)) {
+                (bitems && (hipMemcpy(m + o_items, items.data(), bitems, hipMemcpyHostToDevice) != hipSuccess ||
+                            hipMemcpy(m + o_iseg, iseg.data(), biseg, hipMemcpyHostToDevice) != hipSuccess))) {
                 dev_free(n->mem);
                 delete n;
                 return HAB_ERR_DEVICE;
@@ -523,6 +657,7 @@ static hab_status nav_build(hab_context *ctx, const float *segments, uint32_t nu
             d.seg = reinterpret_cast<const float4 *>(m);
             d.cell_start = reinterpret_cast<const uint32_t *>(m + o_start);
             d.items = reinterpret_cast<const uint32_t *>(m + o_items);
+            d.iseg = reinterpret_cast<const float4 *>(m + o_iseg);
         }
         n->d = d;
         ctx->navs.push_back(n);
@@ -616,21 +751,17 @@ hab_status hab_actuate(hab_context *ctx, const hab_nav *const *navs, uint32_t n,
         ActParams P{params->radius, params->forward_m, params->turn_cos, params->turn_sin, camera_height};
         const NavDesc *dt = static_cast<const NavDesc *>(ws.arena);
         const uint32_t *di = reinterpret_cast<const uint32_t *>(static_cast<char *>(ws.arena) + ctx->act_last_off);
-        // lanes per agent: enough groups to fill the chip (~64k lanes)
-        const uint32_t G = n <= 1024 ? 64u : n <= 4096 ? 16u : n <= 16384 ? 4u : 1u;
-        const dim3 grid((uint32_t)((uint64_t(n) * G + kActBlock - 1) / kActBlock));
-        if (G == 64)
-            hipLaunchKernelGGL(k_actuate<64>, grid, dim3(kActBlock), 0, stream, dt, di, n, agents, actions,
-                               collided, poses, P);
-        else if (G == 16)
-            hipLaunchKernelGGL(k_actuate<16>, grid, dim3(kActBlock), 0, stream, dt, di, n, agents, actions,
-                               collided, poses, P);
-        else if (G == 4)
-            hipLaunchKernelGGL(k_actuate<4>, grid, dim3(kActBlock), 0, stream, dt, di, n, agents, actions,
-                               collided, poses, P);
-        else
-            hipLaunchKernelGGL(k_actuate<1>, grid, dim3(kActBlock), 0, stream, dt, di, n, agents, actions,
-                               collided, poses, P);
+        // Few agents: a wave each, the shortest way through a pass; many: fewer
+        // lanes each, so that one round of waves serves them all.  us a call at
+        // 64 / 8,192 / 16,384 / 65,536 agents: <64, 4> 24 / 46 / 69 / 202,
+        // <32, 16> 32 / 51 / 60 / 141, <16, 32> 45 / 71 / 76 / 135.
+        auto go = [&](auto kernel, uint32_t per_block) {
+            hipLaunchKernelGGL(kernel, dim3((n + per_block - 1) / per_block), dim3(kActBlock), 0, stream, dt, di, n,
+                               agents, actions, collided, poses, P);
+        };
+        if (n <= 8192) go(k_actuate<64, 4>, 4u);
+        else if (n <= 32768) go(k_actuate<32, 16>, 16u);
+        else go(k_actuate<16, 32>, 32u);
         HAB_HIP(hipGetLastError());
         HAB_HIP(hipEventRecord(ws.done, stream));
         ws.has_done = true;
@@ -724,8 +855,17 @@ hab_status hab_nav_free(hab_context *ctx, const hab_nav *nav, const double *poin
         if (std::find(ctx->navs.begin(), ctx->navs.end(), nav) == ctx->navs.end()) return HAB_ERR_INVALID_ARG;
         DeviceGuard g(ctx->device);
         if (!g.ok) return HAB_ERR_DEVICE;
-        hipLaunchKernelGGL(k_nav_free, dim3((n + kActBlock - 1) / kActBlock), dim3(kActBlock), 0, stream, nav->d,
-                           reinterpret_cast<const double2 *>(points), n, radius, out_free);
+        // Few points: more lanes each, for the shortest way through the runs;
+        // many: as many as still share a cache line.  us a call at 1,000 /
+        // 100,000 / 1M points: one lane 27 / 42 / 87, 4 lanes 10 / 18 / 71, 16
+        // lanes 9 / 13 / 92.
+        auto go = [&](auto kernel, uint32_t lanes) {
+            hipLaunchKernelGGL(kernel, dim3((uint32_t)(((uint64_t)n * lanes + kActBlock - 1) / kActBlock)),
+                               dim3(kActBlock), 0, stream, nav->d, reinterpret_cast<const double2 *>(points), n, radius,
+                               out_free);
+        };
+        if (n <= 131072) go(k_nav_free<16>, 16u);
+        else go(k_nav_free<4>, 4u);
         HAB_HIP(hipGetLastError());
         return HAB_OK;
     });
