@@ -42,7 +42,7 @@ struct alignas(16) DView {
     uint32_t pair_base;         // first entry of this view's visible-cluster segment
     const float4 *cbox;         // per 64-triangle cluster: (min xyz, -) (max xyz, -)
     uint32_t count_work;        // 1: accumulate bbox tests and covered fragments
-    uint32_t zoff_lo;           // direct path: the view's first z-key (low word)
+    uint32_t zoff_lo;           // the view's first z-key (direct path, k_raster_wave; low word)
     const uint32_t *inst;       // [T] instance id per triangle (semantic output)
     uint32_t *sem;              // [H][W] or null
     float noise_sigma;          // depth noise in 1/m (0: ideal depth)

@@ -9,6 +9,8 @@ namespace habmi {
 
 constexpr uint32_t kMaxViews = 4096;   // views per launch sequence
 constexpr uint32_t kSegPerTile = 4;    // a work item covers <= 4 * TS^2 list entries
+constexpr uint32_t kWaveSeg = 256;      // list entries of a work item of k_raster_wave
+constexpr int kWaveWavesPerSimd = 6;    // its register budget
 constexpr uint32_t kMaxSegments = 1u << 14;
 
 // One raster + resolve launch pair: all views of a batch that use the same
@@ -21,6 +23,7 @@ struct RasterLaunch {
     uint32_t blocks;           // total tiles
     uint32_t bands;            // total resolve bands (resolve grid)
     uint32_t grid;             // persistent raster blocks
+    bool wave;                 // 16-pixel tiles, a wave each (k_raster_wave)
     bool lane_owned;           // atomic-free lane-owned z-test (else balanced steps, z-keys in LDS)
     uint64_t item_cap;         // work items the scratch below can hold
     uint2 *items;              // [item_cap] (view, tile | segment << 18)
@@ -47,11 +50,12 @@ struct LaunchPlan {
     uint2 *items[3];           // per tile size (null when unused)
     uint32_t *err;
     uint32_t bin_grid;
+    bool wave16;               // 16-pixel tiles go to k_raster_wave, their z-keys to zbuf
     RasterLaunch raster[3];
     int nraster;
     // direct path (draw.hip): drawn without tile lists when `direct`
     bool direct;
-    unsigned long long *zbuf;  // z-keys of every view, [znum]
+    unsigned long long *zbuf;  // z-keys: of every view, [znum]; or of the 16-pixel tiles (wave16)
     uint64_t znum;
     ClusterRec *recs;          // visible clusters, kBuckets segments per view
     const uint32_t *tpre;      // [nl] first tile block of each view of the list

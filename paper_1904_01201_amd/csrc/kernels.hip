@@ -28,6 +28,8 @@
 //                and keep the nearest candidate (largest 1/w, smaller key on
 //                ties) by an LDS atomic max per pixel; the segment's
 //                per-pixel winner goes to scratch
+//   k_raster_wave the same for 16-pixel tiles, a wave per work item; its
+//                z-keys stay in one place per tile (k_resolve_wave reads them)
 //   k_resolve<TS> per band of 32 x 2 pixels (one wave): merge the segments'
 //                winners with the same rule, rebuild the winner, write
 //                colour (through LDS, as words), planar depth and index:
@@ -512,17 +514,28 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(const DView *__restrict__ vie
     }
 }
 
-__device__ __forceinline__ uint32_t seg_size(uint32_t ts_log2) { return kSegPerTile << (2 * ts_log2); }
+// List entries of one work item: kSegPerTile * TS^2, or kWaveSeg where a wave
+// rasterises a 16-pixel tile by itself (k_raster_wave).
+__device__ __forceinline__ uint32_t seg_size(uint32_t ts_log2, bool wave16)
+{
+    return wave16 && ts_log2 == 4 ? kWaveSeg : kSegPerTile << (2 * ts_log2);
+}
 
 // Number of (tile, segment) work items of a tile: none when empty, one for
 // an overflow tile (it scans the whole survivor list), else one per
-// segment of at most kSegPerTile * TS^2 list entries.
-__device__ __forceinline__ uint32_t tile_segments(uint32_t c, uint32_t off, uint32_t ts_log2)
+// segment of at most seg_size list entries.
+__device__ __forceinline__ uint32_t tile_segments(uint32_t c, uint32_t off, uint32_t ts_log2, bool wave16)
 {
     if (c == 0) return 0;
     if (off == kOverflow) return 1;
-    const uint32_t S = seg_size(ts_log2);
+    const uint32_t S = seg_size(ts_log2, wave16);
     return (c + S - 1) / S;
+}
+
+// First z-key of a view's 16-pixel tile (k_raster_wave): 256 keys per tile.
+__device__ __forceinline__ size_t wave_tile(const DView &v, uint32_t tile)
+{
+    return (((size_t)v.zoff_hi << 32) | v.zoff_lo) + 256u * (size_t)tile;
 }
 
 // Per view: exclusive scan of tile counts into list offsets.  A tile whose
@@ -538,7 +551,8 @@ __global__ __launch_bounds__(kScanBlock) void k_bin_scan(const DView *__restrict
                                                          DQueue *__restrict__ q,
                                                          uint2 *__restrict__ items8,
                                                          uint2 *__restrict__ items16,
-                                                         uint2 *__restrict__ items32)
+                                                         uint2 *__restrict__ items32, bool wave16,
+                                                         unsigned long long *__restrict__ zt)
 {
     __shared__ uint32_t wtot[kScanBlock / 64];
     __shared__ uint32_t sbase;
@@ -557,9 +571,9 @@ __global__ __launch_bounds__(kScanBlock) void k_bin_scan(const DView *__restrict
         // a tile with more segments than the item encoding holds also takes
         // the (single-item) overflow path
         const bool over = c > v.tile_cap || P + e > v.bin_cap ||
-                          c > (kMaxSegments - 1) * seg_size(v.ts_log2);
+                          c > (kMaxSegments - 1) * seg_size(v.ts_log2, wave16);
         const uint32_t off = (c == 0) ? 0u : (over ? kOverflow : (uint32_t)P);
-        const uint32_t ns = tile_segments(c, off, v.ts_log2);
+        const uint32_t ns = tile_segments(c, off, v.ts_log2, wave16);
         uint32_t stot;
         const uint32_t sex = block_excl_scan<kScanBlock>(ns, wtot, &stot);
         if (i < n) {
@@ -578,10 +592,23 @@ __global__ __launch_bounds__(kScanBlock) void k_bin_scan(const DView *__restrict
     uint2 *items = cls == 0 ? items8 : cls == 1 ? items16 : items32;
     for (uint32_t i = threadIdx.x; i < n; i += kScanBlock) {
         const uint32_t c = tile_count[v.tile_base + i];
-        const uint32_t ns = tile_segments(c, tile_off[v.tile_base + i], v.ts_log2);
+        const uint32_t ns = tile_segments(c, tile_off[v.tile_base + i], v.ts_log2, wave16);
         const uint32_t first = qb + tile_item[v.tile_base + i];
         tile_item[v.tile_base + i] = first;
         for (uint32_t sgm = 0; sgm < ns; ++sgm) items[first + sgm] = make_uint2(vi, i | (sgm << 18));
+    }
+    if (!(wave16 && cls == 1)) return;
+    // the tiles whose segments merge by atomic max start from cleared keys
+    for (uint32_t base = 0; base < n; base += kScanBlock) {
+        const uint32_t i = base + threadIdx.x;
+        const uint32_t c = i < n ? tile_count[v.tile_base + i] : 0u;
+        unsigned long long m = __ballot(i < n && tile_segments(c, tile_off[v.tile_base + i], v.ts_log2, wave16) > 1);
+        for (; m; m &= m - 1) {
+            const uint32_t tile = base + (threadIdx.x & ~63u) + (uint32_t)__ffsll((long long)m) - 1u;
+            uint4 *z = reinterpret_cast<uint4 *>(zt + wave_tile(v, tile));
+            z[lane_id()] = make_uint4(0, 0, 0, 0);
+            z[lane_id() + 64] = make_uint4(0, 0, 0, 0);
+        }
     }
 }
 
@@ -677,9 +704,12 @@ static_assert(kPairZ<16> == 0x120u && kPairQP<16> == 0x04000400u, "pair bits, la
 static_assert(((kPairZ<8> | kPairQP<8>) & 0x00FFF000u) == 0 && ((kPairZ<32> | kPairQP<32>) & 0x00FFF000u) == 0,
               "record offset bits");
 
+// The record of sub-triangle `key` relative to the TS-pixel tile at (ti0, tj0),
+// with its edges (dx, dy), its owned flags and its pixel box in the tile; false
+// if there is none.
 template <int TS>
-__device__ __forceinline__ bool build_rec(const DView &v, uint32_t key, int ti0, int tj0, LRec &r, LExt &x,
-                                          QMask<TS> &qm, bool &rerr)
+__device__ __forceinline__ bool edge_rec(const DView &v, uint32_t key, int ti0, int tj0, LRec &r, LExt &x, int box[4],
+                                         int dx[3], int dy[3], uint32_t &notown, bool &packed, bool &rerr)
 {
     const uint32_t t = key >> 1;
     const int sub = (int)(key & 1u);
@@ -716,30 +746,28 @@ __device__ __forceinline__ bool build_rec(const DView &v, uint32_t key, int ti0,
         return false;
     }
     const PixBox pb = pix_box(v, a, b, c);
-    const int bi0 = max(pb.i0 - ti0, 0), bi1 = min(pb.i1 - ti0, TS - 1);
-    const int bj0 = max(pb.j0 - tj0, 0), bj1 = min(pb.j1 - tj0, TS - 1);
-    if (bi0 > bi1 || bj0 > bj1) return false;
-    using B = Blk<TS>;
-    using Q = QMask<TS>;
-    const int qx0 = bi0 >> B::WL, qx1 = bi1 >> B::WL, qy0 = bj0 >> B::HL, qy1 = bj1 >> B::HL;
-    const Q row = (Q)(((Q)2 << qx1) - ((Q)1 << qx0));
-    qm = 0;
-#pragma unroll
-    for (int qy = 0; qy < B::NY; ++qy)
-        if (qy >= qy0 && qy <= qy1) qm |= row << (qy * B::NX);
-
+    box[0] = max(pb.i0 - ti0, 0);
+    box[1] = min(pb.i1 - ti0, TS - 1);
+    box[2] = max(pb.j0 - tj0, 0);
+    box[3] = min(pb.j1 - tj0, TS - 1);
+    if (box[0] > box[1] || box[2] > box[3]) return false;
     // edge k runs from vertex k+1 to vertex k+2
-    const int dx[3] = {c.X - b.X, a.X - c.X, b.X - a.X};
-    const int dy[3] = {c.Y - b.Y, a.Y - c.Y, b.Y - a.Y};
+    dx[0] = c.X - b.X;
+    dx[1] = a.X - c.X;
+    dx[2] = b.X - a.X;
+    dy[0] = c.Y - b.Y;
+    dy[1] = a.Y - c.Y;
+    dy[2] = b.Y - a.Y;
     const int ax[3] = {b.X, c.X, a.X};
     const int ay[3] = {b.Y, c.Y, a.Y};
-    uint32_t notown = 0;
+    notown = 0;
 #pragma unroll
     for (int k = 0; k < 3; ++k)
         if (!owned(dx[k], dy[k])) notown |= 1u << (8 * k);
     // C_k = E_k at the tile's first pixel centre, as low and high words
     int clo[3], chi[3];
-    bool fast = true, packed = true;
+    bool fast = true;
+    packed = true;
     // edge start points relative to that centre (|X| < 2^29: fits int32)
     const int Ox = 256 * ti0 + 128, Oy = 256 * tj0 + 128;
     const int rx[3] = {ax[0] - Ox, ax[1] - Ox, ax[2] - Ox};
@@ -800,6 +828,37 @@ __device__ __forceinline__ bool build_rec(const DView &v, uint32_t key, int ti0,
     x.ny0 = -dy[0];
     x.ny1 = -dy[1];
     x.ny2 = -dy[2];
+    // (float)A: from int32 when A fits (always for small records), which is
+    // the same rounding as the int64 conversion
+    float fA;
+    if (A == (long long)(int)A) fA = (float)(int)A;
+    else fA = (float)A;
+    r.invA = recip_rn(fA);
+    r.rw0 = a.rw;
+    r.rw1 = b.rw;
+    r.rw2 = c.rw;
+    r.nkey = ~key;
+    r.flags = notown | (fast ? 0u : kSlow) | (packed ? kPacked : 0u);
+    return true;
+}
+
+template <int TS>
+__device__ __forceinline__ bool build_rec(const DView &v, uint32_t key, int ti0, int tj0, LRec &r, LExt &x,
+                                          QMask<TS> &qm, bool &rerr)
+{
+    int box[4], dx[3], dy[3];
+    uint32_t notown;
+    bool packed;
+    if (!edge_rec<TS>(v, key, ti0, tj0, r, x, box, dx, dy, notown, packed, rerr)) return false;
+    using B = Blk<TS>;
+    using Q = QMask<TS>;
+    const int qx0 = box[0] >> B::WL, qx1 = box[1] >> B::WL, qy0 = box[2] >> B::HL, qy1 = box[3] >> B::HL;
+    const Q row = (Q)(((Q)2 << qx1) - ((Q)1 << qx0));
+    qm = 0;
+#pragma unroll
+    for (int qy = 0; qy < B::NY; ++qy)
+        if (qy >= qy0 && qy <= qy1) qm |= row << (qy * B::NX);
+
     if constexpr (TS == 8) {
         // Drop the blocks that hold no pixel centre the triangle can cover:
         // an edge whose largest value over a block's centres is below its
@@ -815,7 +874,7 @@ __device__ __forceinline__ bool build_rec(const DView &v, uint32_t key, int ti0,
             int g[3], sp[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                g[k] = clo[k] + (dx[k] > 0 ? __mul24(dx[k], QH) : 0) - (dy[k] < 0 ? __mul24(dy[k], PW) : 0) -
+                g[k] = (k == 0 ? r.c0 : k == 1 ? r.c1 : r.c2) + (dx[k] > 0 ? __mul24(dx[k], QH) : 0) - (dy[k] < 0 ? __mul24(dy[k], PW) : 0) -
                        (int)((notown >> (8 * k)) & 1u);
                 sp[k] = dy[k] * (256 * B::W);
             }
@@ -836,23 +895,218 @@ __device__ __forceinline__ bool build_rec(const DView &v, uint32_t key, int ti0,
             if (!qm) return false;
         }
     }
-    // (float)A: from int32 when A fits (always for small records), which is
-    // the same rounding as the int64 conversion
-    float fA;
-    if (A == (long long)(int)A) fA = (float)(int)A;
-    else fA = (float)A;
-    r.invA = recip_rn(fA);
-    r.rw0 = a.rw;
-    r.rw1 = b.rw;
-    r.rw2 = c.rw;
-    r.nkey = ~key;
-    r.flags = notown | (fast ? 0u : kSlow) | (packed ? kPacked : 0u);
     return true;
 }
 
 __device__ __forceinline__ long long join64(int hi, int lo)
 {
     return (long long)(((unsigned long long)(uint32_t)hi << 32) | (unsigned long long)(uint32_t)lo);
+}
+
+// ------------------------------------------------------------ k_raster_wave
+// A wave rasterises a work item of a 16-pixel tile by itself: the balanced
+// form of k_raster (which see) over the tile's 32 blocks of 4 x 2 pixels, the
+// tile's 256 z-keys in LDS block by block.  Against 8-pixel tiles a survivor
+// meets 1.4 tiles instead of 1.9, and lists are long enough to fill the staging
+// lanes; against a 256-thread block per 16-pixel tile no wave tests another's
+// records and nothing waits at barriers.
+//
+// Records whose edges do not fit the packed form (a vertex far from the tile)
+// are tested one after another by the whole wave.
+//
+// Bound by VALU issue (about 80% busy): 99 M wave instructions for the 64 bench
+// views, 885 per 64 list entries, half of them rebuilding the entries' setup;
+// 0.203 ms alone, against 0.222 ms with 8-pixel tiles (112 M) and 0.289 ms with
+// a 256-thread block per 16-pixel tile; eight 512 x 384 views of 1M triangles
+// 0.111 ms (0.156 ms in blocks).
+constexpr uint32_t kWavePairs = 512;   // (record, block) pairs listed at once: eight blocks a record
+
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPerSimd))) void k_raster_wave(
+    const DView *__restrict__ views, const uint2 *__restrict__ items, DQueue *__restrict__ q,
+    DViewCounters *__restrict__ ctr, const uint32_t *__restrict__ skey, const uint2 *__restrict__ sbox,
+    const uint32_t *__restrict__ tile_count, const uint32_t *__restrict__ tile_off, const uint32_t *__restrict__ bins,
+    unsigned long long *__restrict__ zt, uint32_t *__restrict__ err)
+{
+    constexpr int TS = 16;
+    constexpr uint32_t cls = 1;
+    __shared__ LRec srec[64];
+    __shared__ __align__(16) unsigned long long zk[256];
+    __shared__ __align__(8) uint32_t slist[kWavePairs + 16];   // padded for the last double step's read
+    const uint32_t lane = lane_id();
+    const unsigned long long lt = lanemask_lt();
+    for (uint32_t i = lane; i < kWavePairs + 16; i += 64) slist[i] = 0;
+    // the lane's place (pxl, pyl) in its group's block; its packed (Q, P) pair
+    // in block 0 and its byte offset among the block's z-keys
+    const uint32_t gi = lane >> 3, pxl = lane & 3u, pyl = (lane >> 2) & 1u;
+    const uint32_t QPl = (256u * pyl) | ((256u * pxl) << 16), zl = (lane & 7u) * 8u;
+    const uint32_t total = q->total[cls];
+    const uint32_t nq = min(kQueues, gridDim.x), x = blockIdx.x % nq;
+    const char *const rb = reinterpret_cast<const char *>(srec);
+    bool rerr = false;
+    for (;;) {
+        uint32_t k = 0;
+        if (lane == 0) k = atomicAdd(&q->head[cls][x].next, 1u);
+        k = uniform(k);
+        const uint32_t item = ((k / kQueueGroup) * nq + x) * kQueueGroup + k % kQueueGroup;
+        if (item >= total) break;
+        const uint2 it = items[item];
+        const uint32_t vi = uniform(it.x), itile = uniform(it.y);
+        const uint32_t tile = itile & 0x3FFFFu, sgm = itile >> 18;
+        const DView &v = views[vi];
+        const int ti0 = (int)(tile % v.tiles_x) * TS, tj0 = (int)(tile / v.tiles_x) * TS;
+        const bool count = v.count_work != 0;
+        const uint32_t cnt = uniform(tile_count[v.tile_base + tile]);
+        const uint32_t off = uniform(tile_off[v.tile_base + tile]);
+        const bool over = off == kOverflow;
+        const uint32_t begin = over ? 0u : sgm * kWaveSeg;
+        const uint32_t end = over ? uniform(ctr[vi].surv_count) : min(begin + kWaveSeg, cnt);
+        const uint32_t *list = bins + v.bin_base + (over ? 0u : off);
+        uint4 *const z4 = reinterpret_cast<uint4 *>(zk);
+        z4[lane] = make_uint4(0, 0, 0, 0);
+        z4[lane + 64] = make_uint4(0, 0, 0, 0);
+        uint32_t ncov = 0;
+        // merge a covered fragment's key at byte offset zo of the tile's keys
+        auto put = [&](uint32_t zo, float num, float invA, uint32_t nkey) {
+            const float rho = num * invA;
+            atomicMax(reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(zk) + zo),
+                      ((unsigned long long)__float_as_uint(rho) << 32) | (unsigned long long)nkey);
+        };
+        for (uint32_t base = begin; base < end; base += 64) {
+            const uint32_t e = base + lane;
+            LRec r;
+            LExt rx;
+            int box[4], dx[3], dy[3];
+            uint32_t notown = 0, m = 0, key = 0;
+            bool packed = true, have = e < end;
+            if (have) {
+                if (over) {
+                    const uint2 bb = sbox[v.surv_base + e];
+                    have = (int)(bb.y & 0xFFFFu) >= ti0 && (int)(bb.x & 0xFFFFu) < ti0 + TS &&
+                           (int)(bb.y >> 16) >= tj0 && (int)(bb.x >> 16) < tj0 + TS;
+                    key = skey[v.surv_base + e];
+                } else {
+                    key = list[e];
+                }
+                have = have && edge_rec<TS>(v, key, ti0, tj0, r, rx, box, dx, dy, notown, packed, rerr);
+            }
+            if (have && packed) {
+                srec[lane] = r;
+                // the blocks that the box touches, less those that an edge
+                // excludes: E_k peaks at the block corner that dx_k and -dy_k
+                // favour, g_k is that peak in block (0, 0) less the threshold
+                const int qx0 = box[0] >> 2, qx1 = box[1] >> 2, qy0 = box[2] >> 1, qy1 = box[3] >> 1;
+                const uint32_t row = (2u << qx1) - (1u << qx0);
+                const uint32_t hi8 = 0x11111111u >> (28 - 4 * qy1), lo8 = 0x11111111u << (4 * qy0);
+                m = (hi8 & lo8) * row;
+                int g[3];
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    g[j] = (j == 0 ? r.c0 : j == 1 ? r.c1 : r.c2) + (dx[j] > 0 ? dx[j] * 256 : 0) -
+                           (dy[j] < 0 ? dy[j] * 768 : 0) - (int)((notown >> (8 * j)) & 1u);
+                for (uint32_t t = m; t; t &= t - 1) {
+                    const int b = __ffs((int)t) - 1, bx = b & 3, by = b >> 2;
+                    const int e0 = g[0] + __mul24(dx[0], by << 9) - __mul24(dy[0], bx << 10);
+                    const int e1 = g[1] + __mul24(dx[1], by << 9) - __mul24(dy[1], bx << 10);
+                    const int e2 = g[2] + __mul24(dx[2], by << 9) - __mul24(dy[2], bx << 10);
+                    if ((e0 | e1 | e2) < 0) m &= ~(1u << b);
+                }
+            }
+            // the packed records' pairs, up to eight a record at a time: entry =
+            // block, record offset (16-byte units, bits 12..19), the block's
+            // (Q, P) in 1/256 pixel (bits 9..11 and 26..27)
+            const uint32_t eb = (lane * (uint32_t)(sizeof(LRec) / 16)) << 12;
+            while (__ballot(m != 0)) {
+                const uint32_t np = min((uint32_t)__popc(m), kWavePairs / 64);
+                uint32_t pos = 0, tot = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const unsigned long long bk = __ballot((np >> j) & 1u);
+                    pos += (uint32_t)__popcll(bk & lt) << j;
+                    tot += (uint32_t)__popcll(bk) << j;
+                }
+                tot = uniform(tot);
+                for (uint32_t j = 0; j < np; ++j) {
+                    const uint32_t b = (uint32_t)__ffs((int)m) - 1u;
+                    m &= m - 1;
+                    slist[pos + j] = eb | b | ((b >> 2) << 9) | ((b & 3u) << 26);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                auto visit = [&](uint32_t en, bool act) {
+                    const LRec R = lds_rec_at(rb, ((en >> 12) & 0xFFu) << 4);
+                    const uint32_t qp = (en & 0x0C000E00u) | QPl;
+                    const short2_t QPq = __builtin_bit_cast(short2_t, qp);
+                    const uint32_t fl = R.flags;
+                    const int n0 = (int)(fl & 0xFFu), n1 = (int)((fl >> 8) & 0xFFu), n2 = (int)((fl >> 16) & 0xFFu);
+                    const int F0 = __builtin_amdgcn_sdot2(__builtin_bit_cast(short2_t, R.e0), QPq, R.c0, false);
+                    const int F1 = __builtin_amdgcn_sdot2(__builtin_bit_cast(short2_t, R.e1), QPq, R.c1, false);
+                    const int F2 = __builtin_amdgcn_sdot2(__builtin_bit_cast(short2_t, R.e2), QPq, R.c2, false);
+                    const bool cov = act && F0 >= n0 && F1 >= n1 && F2 >= n2;
+                    if (!__ballot(cov)) return;
+                    if (count) {
+                        // pixels outside the view do not count
+                        const bool inv =
+                            ti0 + (int)(qp >> 24) < (int)v.W && tj0 + (int)((qp & 0xFFFFu) >> 8) < (int)v.H;
+                        ncov += (uint32_t)__popcll(__ballot(cov && inv));
+                    }
+                    const float w0 = (float)F0 * R.rw0, w1 = (float)F1 * R.rw1, w2 = (float)F2 * R.rw2;
+                    if (cov) put(((en & 31u) << 6) | zl, (w0 + w1) + w2, R.invA, R.nkey);
+                };
+                uint32_t p = 0;
+                // two steps per list read (one 8-byte LDS load) while more
+                // than eight pairs remain
+                for (; p + 8 < tot; p += 16) {
+                    const uint32_t pi = p + 2 * gi;
+                    const uint2 e2 = *reinterpret_cast<const uint2 *>(slist + pi);
+                    visit(e2.x, pi < tot);
+                    visit(e2.y, pi + 1 < tot);
+                }
+                if (p < tot) visit(slist[p + gi], p + gi < tot);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            }
+            // the other records, one at a time: 64 pixels a step, block by block
+            for (unsigned long long u = __ballot(have && !packed); u; u &= u - 1) {
+                const int l = __ffsll((long long)u) - 1;
+                auto from = [&](int y) { return __builtin_amdgcn_readlane(y, l); };
+                auto fromf = [&](float y) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y), l)); };
+                const long long C0 = join64(from(rx.hi0), from(r.c0)), C1 = join64(from(rx.hi1), from(r.c1)),
+                                C2 = join64(from(rx.hi2), from(r.c2));
+                const int x0 = from(dx[0]), x1 = from(dx[1]), x2 = from(dx[2]);
+                const int y0 = from(dy[0]), y1 = from(dy[1]), y2 = from(dy[2]);
+                const uint32_t no = (uint32_t)from((int)notown), nkey = (uint32_t)from((int)r.nkey);
+                const float w0 = fromf(r.rw0), w1 = fromf(r.rw1), w2 = fromf(r.rw2), ia = fromf(r.invA);
+                const int j0 = from(box[2]), j1 = from(box[3]);
+#pragma unroll 1
+                for (int s = j0 >> 2; s <= j1 >> 2; ++s) {   // four rows: eight blocks
+                    const int px = (int)((gi & 3u) * 4u + pxl), py = 4 * s + (int)((gi >> 2) * 2u + pyl);
+                    const long long E0 = C0 + (long long)x0 * (256 * py) - (long long)y0 * (256 * px);
+                    const long long E1 = C1 + (long long)x1 * (256 * py) - (long long)y1 * (256 * px);
+                    const long long E2 = C2 + (long long)x2 * (256 * py) - (long long)y2 * (256 * px);
+                    const bool cov = E0 >= (long long)(no & 0xFFu) && E1 >= (long long)((no >> 8) & 0xFFu) &&
+                                     E2 >= (long long)((no >> 16) & 0xFFu);
+                    if (count)
+                        ncov += (uint32_t)__popcll(__ballot(cov && ti0 + px < (int)v.W && tj0 + py < (int)v.H));
+                    if (cov)
+                        put((uint32_t)s * 512u + lane * 8u, ((float)E0 * w0 + (float)E1 * w1) + (float)E2 * w2, ia, nkey);
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        unsigned long long *const z = zt + wave_tile(v, tile);
+        if (over || cnt <= kWaveSeg) {
+            uint4 *const zo = reinterpret_cast<uint4 *>(z);
+            zo[lane] = z4[lane];
+            zo[lane + 64] = z4[lane + 64];
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                const unsigned long long b = zk[64 * j + lane];
+                if (b) (void)__hip_atomic_fetch_max(z + 64 * j + lane, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (count && lane == 0 && ncov) atomicAdd(&ctr[vi].covered, (unsigned long long)ncov);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    }
+    if (rerr) atomicOr(err, kErrRange);
 }
 
 // LO: lane-owned pixels with an atomic-free z-test in registers; else
@@ -1293,7 +1547,7 @@ __global__ __launch_bounds__(kBandThreads) void k_resolve(const DView *__restric
         const uint32_t tile = (uint32_t)(pj / TS) * v.tiles_x + (uint32_t)(pi / TS);
         const uint32_t sub = (uint32_t)(((pj % TS) / 8) * NS + (pi % TS) / 8);
         const uint32_t tglob = v.tile_base + tile;
-        const uint32_t ns = tile_segments(tile_count[tglob], tile_off[tglob], v.ts_log2);
+        const uint32_t ns = tile_segments(tile_count[tglob], tile_off[tglob], v.ts_log2, false);
         const uint32_t first = tile_item[tglob];
         const uint32_t slot = sub * 64u + (uint32_t)((pj % 8) * 8 + (pi % 8));
         for (uint32_t s = 0; s < ns; ++s) {
@@ -1308,6 +1562,45 @@ __global__ __launch_bounds__(kBandThreads) void k_resolve(const DView *__restric
     shade_band<kBandW, kBandH>(v, x0, y0, pi, pj, in, best_rho, best_key, s_rgb, err);
 }
 
+// As k_resolve, from the tiles' z-keys that k_raster_wave left (a tile without
+// entries has none).
+__global__ __launch_bounds__(kBandThreads) void k_resolve_wave(const DView *__restrict__ views,
+                                                               const uint32_t *__restrict__ lview,
+                                                               const uint32_t *__restrict__ bpre, uint32_t nl,
+                                                               const uint32_t *__restrict__ tile_count,
+                                                               const unsigned long long *__restrict__ zt,
+                                                               uint32_t *__restrict__ err)
+{
+    __shared__ __align__(16) uint8_t s_rgb[kBandRgb];
+    uint32_t lo = 0, hi = nl - 1;
+    const uint32_t blk = blockIdx.x;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1) >> 1;
+        if (bpre[mid] <= blk) lo = mid;
+        else hi = mid - 1;
+    }
+    const DView &v = views[uniform(lview[uniform(lo)])];
+    const uint32_t W = v.W, H = v.H;
+    const uint32_t nbx = (W + kBandW - 1) / kBandW;
+    const uint32_t band = blk - bpre[lo];
+    const uint32_t x0 = (band % nbx) * kBandW, y0 = (band / nbx) * kBandH;
+    const uint32_t lane = lane_id();
+    const uint32_t pi = x0 + lane % kBandW, pj = y0 + lane / kBandW;
+    const bool in = pi < W && pj < H;
+    float best_rho = 0.0f;
+    uint32_t best_key = kNone;
+    if (in) {
+        const uint32_t tile = (pj >> 4) * v.tiles_x + (pi >> 4);
+        if (tile_count[v.tile_base + tile]) {
+            const uint32_t b = ((pj & 15u) >> 1) * 4u + ((pi & 15u) >> 2);
+            const unsigned long long z = zt[wave_tile(v, tile) + b * 8u + (pj & 1u) * 4u + (pi & 3u)];
+            best_rho = __uint_as_float((uint32_t)(z >> 32));
+            best_key = ~(uint32_t)z;
+        }
+    }
+    shade_band<kBandW, kBandH>(v, x0, y0, (int)pi, (int)pj, in, best_rho, best_key, s_rgb, err);
+}
+
 // ------------------------------------------------------------ host side
 static inline uint32_t cdiv(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
 
@@ -1319,10 +1612,15 @@ static inline void mark(const LaunchPlan &L, int ev, hipStream_t s)
 template <int TS>
 static void launch_raster(const LaunchPlan &L, const RasterLaunch &R, hipStream_t s)
 {
+    if (R.wave) {
+        hipLaunchKernelGGL(k_raster_wave, dim3(R.grid), dim3(64), 0, s, L.views, R.items, L.queue, L.ctr, L.skey,
+                           L.sbox, L.tile_count, L.tile_off, L.bins, L.zbuf, L.err);
+        return;
+    }
     if (R.lane_owned)
         hipLaunchKernelGGL((k_raster<TS, true>), dim3(R.grid), dim3(TS * TS), 0, s, L.views, R.items, L.queue,
                            L.ctr, L.skey, L.sbox, L.tile_count, L.tile_off, L.bins, R.partial, L.err);
-    else
+    else if constexpr (TS != 16)
         hipLaunchKernelGGL((k_raster<TS, false>), dim3(R.grid), dim3(TS * TS), 0, s, L.views, R.items, L.queue,
                            L.ctr, L.skey, L.sbox, L.tile_count, L.tile_off, L.bins, R.partial, L.err);
 }
@@ -1330,6 +1628,11 @@ static void launch_raster(const LaunchPlan &L, const RasterLaunch &R, hipStream_
 template <int TS>
 static void launch_resolve(const LaunchPlan &L, const RasterLaunch &R, hipStream_t s)
 {
+    if (R.wave) {
+        hipLaunchKernelGGL(k_resolve_wave, dim3(R.bands), dim3(kBandThreads), 0, s, L.views, R.lview, R.bpre, R.nl,
+                           L.tile_count, L.zbuf, L.err);
+        return;
+    }
     hipLaunchKernelGGL(k_resolve<TS>, dim3(R.bands), dim3(kBandThreads), 0, s, L.views, R.lview, R.bpre,
                        R.nl, L.tile_count, L.tile_off, L.tile_item, R.partial, L.err);
 }
@@ -1341,7 +1644,7 @@ int raster_blocks_per_cu(int ts, bool lane_owned)
     switch (ts * 2 + (lane_owned ? 1 : 0)) {
     case 16: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_raster<8, false>, 64, 0); break;
     case 17: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_raster<8, true>, 64, 0); break;
-    case 32: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_raster<16, false>, 256, 0); break;
+    case 32: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_raster_wave, 64, 0); break;
     case 33: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_raster<16, true>, 256, 0); break;
     case 64: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_raster<32, false>, 1024, 0); break;
     case 65: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_raster<32, true>, 1024, 0); break;
@@ -1372,7 +1675,7 @@ hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
     mark(L, 6, s);
     hipLaunchKernelGGL(k_bin_scan, dim3(L.nviews), dim3(kScanBlock), 0, s, L.views, L.ctr,
                        L.tile_count, L.tile_off, L.tile_item, L.queue, L.items[0], L.items[1],
-                       L.items[2]);
+                       L.items[2], L.wave16, L.zbuf);
     mark(L, 7, s);
     mark(L, 8, s);
     hipLaunchKernelGGL(k_bin<true>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s, L.views, L.nviews,

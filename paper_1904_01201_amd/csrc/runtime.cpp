@@ -503,11 +503,30 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         const uint64_t S = (uint64_t)kSegPerTile << (2 * dv[k].ts_log2);
         item_cap[dv[k].ts_log2 - 3] += (uint64_t)dv[k].tiles_x * dv[k].tiles_y + (dv[k].bin_cap + S - 1) / S;
     }
+    // a wave per 16-pixel tile: smaller work items, but one set of z-keys per
+    // tile whatever its items; both fit the space the block form takes
+    const bool wave16 = !o.lane_owned_z;
+    uint64_t wave_tiles = 0, wave_items = 0;
     for (int c = 0; c < 3; ++c) {
         plan.off_items[c] = off;
+        if (c == 1 && wave16) {
+            for (uint32_t k = 0; k < n; ++k) {
+                DView &d = dv[k];
+                if (d.ts_log2 != 4) continue;
+                d.zoff_lo = (uint32_t)(wave_tiles * 256);
+                d.zoff_hi = (uint32_t)((wave_tiles * 256) >> 32);
+                wave_tiles += (uint64_t)d.tiles_x * d.tiles_y;
+                wave_items += (uint64_t)d.tiles_x * d.tiles_y + (d.bin_cap + kWaveSeg - 1) / kWaveSeg;
+            }
+            plan.off_zbuf = align256(off + 8 * wave_items);
+        }
         off = align256(off + 8 * item_cap[c]);
         plan.off_partial[c] = off;
         off = align256(off + 8 * item_cap[c] * (64ull << (2 * c)));
+        if (c == 1 && wave16) {
+            off = std::max(off, align256((size_t)(plan.off_zbuf + 8 * 256 * wave_tiles)));
+            item_cap[1] = wave_items;
+        }
     }
     plan.arena_bytes = off;
 
@@ -515,6 +534,7 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
     L = LaunchPlan{};
     L.nviews = n;
     L.direct = direct;
+    L.wave16 = wave16;
     std::vector<uint32_t> &tpre = ws.tpre;
     const int c0 = (int)dv[0].ts_log2 - 3;
     if (direct) {
@@ -594,6 +614,7 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         R.item_cap = item_cap[c];
         R.grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(item_cap[c], (uint64_t)cus * kBlocksPerCu[c]));
         R.lane_owned = o.lane_owned_z;
+        R.wave = c == 1 && wave16;
     }
     return HAB_OK;
 }
