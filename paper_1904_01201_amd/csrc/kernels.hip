@@ -75,8 +75,47 @@ __global__ __launch_bounds__(256) void k_reset(DViewCounters *__restrict__ ctr, 
 }
 
 // ------------------------------------------------------------ k_setup
+// True if the triangle a, b, c (either orientation, less than 8 px wide and
+// high, not degenerate) covers none of the n <= 4 pixel centres of its box,
+// decided exactly: the centres lie inside the triangle's bounding box, so every
+// difference is below 2^11 and every edge value below 2^23 in magnitude.  A is
+// twice its area.
+__device__ __forceinline__ bool misses_centres(const SVtx<0> &a, const SVtx<0> &b, const SVtx<0> &c, int A,
+                                               const PixBox &pb, int w, int n)
+{
+    const int ox = 256 * pb.i0 + 128, oy = 256 * pb.j0 + 128;
+    const int bX = A < 0 ? c.X : b.X, bY = A < 0 ? c.Y : b.Y, cX = A < 0 ? b.X : c.X, cY = A < 0 ? b.Y : c.Y;
+    const int dx[3] = {cX - bX, a.X - cX, bX - a.X}, dy[3] = {cY - bY, a.Y - cY, bY - a.Y};
+    const int rx[3] = {bX - ox, cX - ox, a.X - ox}, ry[3] = {bY - oy, cY - oy, a.Y - oy};
+    int e[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        e[k] = __mul24(dy[k], rx[k]) - __mul24(dx[k], ry[k]) - (owned(dx[k], dy[k]) ? 0 : 1);
+    if ((e[0] | e[1] | e[2]) >= 0) return false;
+    int p = 0, q = 0;
+    for (int s = 1; s < n; ++s) {
+        p += 256;
+        if (p == 256 * w) {
+            p = 0;
+            q += 256;
+        }
+        const int f0 = e[0] + __mul24(dx[0], q) - __mul24(dy[0], p);
+        const int f1 = e[1] + __mul24(dx[1], q) - __mul24(dy[1], p);
+        const int f2 = e[2] + __mul24(dx[2], q) - __mul24(dy[2], p);
+        if ((f0 | f1 | f2) >= 0) return false;
+    }
+    return true;
+}
+
 // Survival of sub-triangles 0 and 1 of one triangle in view v, with their
 // pixel boxes.  Deterministic: calling it twice gives the same answer.
+//
+// Unless the view's work is counted, a small sub-triangle that covers no pixel
+// does not survive.  Of the 64 bench views' 5.9 M survivors 5.1 M are less than
+// 8 px in extent and 4.2 M have at most four centres in their box; the test
+// drops 1.6 M of these (boxes of five to nine centres would give 0.05 M more).
+// It takes 10 us of setup (setup is bound by VALU issue) and saves 6 of the
+// count, 11 of the scatter and 22 of the raster: 0.445 -> 0.415 ms.
 __device__ __forceinline__ void survive(const DView &v, const float P[9], bool valid, bool &s0,
                                         bool &s1, PixBox &b0, PixBox &b1, bool &rerr)
 {
@@ -106,12 +145,34 @@ __device__ __forceinline__ void survive(const DView &v, const float P[9], bool v
             return;
     }
     SVtx<0> a, bb, c;
+    if (allin) {
+        // no clipping and no second sub-triangle
+        bool ok = snap(v, c0, a);
+        ok &= snap(v, c1, bb);
+        ok &= snap(v, c2, c);
+        if (!ok) {
+            rerr = true;
+            return;
+        }
+        b0 = pix_box(v, a, bb, c);
+        if (b0.i0 > b0.i1 || b0.j0 > b0.j1) return;
+        const uint32_t ext = (uint32_t)(max(a.X, max(bb.X, c.X)) - min(a.X, min(bb.X, c.X))) |
+                             (uint32_t)(max(a.Y, max(bb.Y, c.Y)) - min(a.Y, min(bb.Y, c.Y)));
+        if (ext < 2048u) {
+            const int A = __mul24(bb.X - a.X, c.Y - a.Y) - __mul24(bb.Y - a.Y, c.X - a.X);
+            const int w = b0.i1 - b0.i0 + 1, n = w * (b0.j1 - b0.j0 + 1);
+            s0 = A != 0 && (n > 4 || v.count_work || !misses_centres(a, bb, c, A, b0, w, n));
+        } else {
+            s0 = area2(a, bb, c) != 0;
+        }
+        return;
+    }
     long long A;
     if (setup_sub(v, c0, c1, c2, 0, a, bb, c, A, rerr)) {
         b0 = pix_box(v, a, bb, c);
         s0 = b0.i0 <= b0.i1 && b0.j0 <= b0.j1;
     }
-    if (!allin && setup_sub(v, c0, c1, c2, 1, a, bb, c, A, rerr)) {
+    if (setup_sub(v, c0, c1, c2, 1, a, bb, c, A, rerr)) {
         b1 = pix_box(v, a, bb, c);
         s1 = b1.i0 <= b1.i1 && b1.j0 <= b1.j1;
     }
