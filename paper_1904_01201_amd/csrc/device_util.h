@@ -105,14 +105,4 @@ __device__ __forceinline__ void load_pos(const DView &v, uint32_t t, float P[9])
     for (int i = 0; i < 9; ++i) P[i] = p[i];
 }
 
-// Positions and the vertex indices (for per-vertex attributes).
-__device__ __forceinline__ void load_tri(const DView &v, uint32_t t, float P[9], uint32_t vid[3])
-{
-    const auto *ix = gmem(v.idx) + 3u * t;
-    vid[0] = ix[0];
-    vid[1] = ix[1];
-    vid[2] = ix[2];
-    load_pos(v, t, P);
-}
-
 }  // namespace habmi

@@ -18,6 +18,19 @@ constexpr int kCluster = 64;                  // triangles per culling cluster (
 constexpr uint32_t kErrRange = 1u;            // a vertex snapped outside |X|,|Y| < 2^29
 constexpr uint32_t kErrResolve = 2u;          // a winning key could not be rebuilt
 
+// What shading needs of a triangle in one 64-byte record, half a cache line: the
+// nine coordinates of its vertices as in tpos, then their colours (packed
+// R | G << 8 | B << 16) or, in a textured scene, their texture coordinates.
+struct alignas(64) TriRec {
+    float pos[9];
+    union {
+        uint32_t col[3];
+        float uv[6];
+    };
+    uint32_t pad;
+};
+static_assert(sizeof(TriRec) == 64, "TriRec layout");
+
 // One view of a launch.  16-byte aligned; 240 bytes.
 struct alignas(16) DView {
     float p[3];
@@ -27,8 +40,7 @@ struct alignas(16) DView {
     uint32_t T;                 // triangles of the scene
     uint32_t ts_log2;           // tile size 8/16/32 -> 3/4/5
     const float *tpos;          // [T][3][3] vertex positions per triangle
-    const uint32_t *col;        // [V] packed R | G<<8 | B<<16
-    const uint32_t *idx;        // [T][3]
+    const TriRec *rec;          // [T] records of the shading
     uint8_t *rgb;               // [H][W][3] or null
     float *depth;               // [H][W] or null
     uint32_t *tri;              // [H][W] or null
@@ -48,9 +60,9 @@ struct alignas(16) DView {
     float noise_sigma;          // depth noise in 1/m (0: ideal depth)
     uint32_t zoff_hi;           //   and high word
     uint64_t noise_seed;        // key of the per-pixel depth noise
-    const float *uv;            // [V][2] texture coordinates (textured scenes)
     const uint32_t *tex;        // [tex_h][tex_w] packed RGB texels, or null
     uint32_t tex_w, tex_h;      // powers of two
+    uint32_t pad[4];            // the size is part of every scratch limit
 };
 static_assert(sizeof(DView) == 240, "DView layout");
 

@@ -18,10 +18,11 @@ constexpr uint32_t kMaxSegments = 1u << 14;
 struct RasterLaunch {
     int ts;                    // 8, 16 or 32
     const uint32_t *lview;     // [nl] view index (resolve: block -> view)
-    const uint32_t *bpre;      // [nl] first resolve band of each view (32 x 2 pixels each)
+    const uint32_t *bpre;      // [nl] first resolve block of each view (32 x 2 * stack pixels each)
     uint32_t nl;
     uint32_t blocks;           // total tiles
-    uint32_t bands;            // total resolve bands (resolve grid)
+    uint32_t bands;            // total resolve blocks (resolve grid)
+    uint32_t stack;            // bands of 32 x 2 pixels a resolve block shades one after another
     uint32_t grid;             // persistent raster blocks
     bool wave;                 // 16-pixel tiles, a wave each (k_raster_wave)
     bool lane_owned;           // atomic-free lane-owned z-test (else balanced steps, z-keys in LDS)
@@ -77,6 +78,19 @@ int raster_blocks_per_cu(int ts, bool lane_owned);
 // Enqueue the whole sequence on stream s (launch_direct: a direct plan's).
 hipError_t launch_render(const LaunchPlan &L, hipStream_t s);
 hipError_t launch_direct(const LaunchPlan &L, hipStream_t s);
+
+// A mesh as it was uploaded: positions [V][3], indices [T][3], colours [V][3]
+// bytes or null, texture coordinates [V][2] or null (they win over colours).
+struct MeshSource {
+    const float *pos;
+    const uint32_t *idx;
+    const uint8_t *col;
+    const float *uv;
+};
+
+// Write a scene's triangles out on stream s: positions, shading records and the
+// bounding box of every kCluster consecutive ones.
+hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, TriRec *rec, float4 *cbox, hipStream_t s);
 
 // Compare recip_rn with the IEEE division 1/x for every float whose bits
 // lie in [lo, hi) (lo < hi <= 0x7F800000), adding the number of differing

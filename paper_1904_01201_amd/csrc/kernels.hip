@@ -52,6 +52,51 @@
 
 namespace habmi {
 
+// ------------------------------------------------------------ k_scene
+// A wave per cluster, a lane per triangle.  Each triangle's positions go out
+// twice: alone (tpos, what setup and raster read) and in its shading record.
+__global__ __launch_bounds__(256) void k_scene(MeshSource m, uint32_t T, float *__restrict__ tpos,
+                                               TriRec *__restrict__ rec, float4 *__restrict__ cbox)
+{
+    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
+    if (uniform(t & ~63u) >= T) return;
+    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
+    if (t < T) {
+        TriRec r = {};
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const size_t vid = m.idx[3ull * t + k];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float x = m.pos[3 * vid + a];
+                r.pos[3 * k + a] = x;
+                tpos[9ull * t + 3 * k + a] = x;
+                mn[a] = fminf(mn[a], x);
+                mx[a] = fmaxf(mx[a], x);
+            }
+            if (m.uv) {
+                r.uv[2 * k] = m.uv[2 * vid];
+                r.uv[2 * k + 1] = m.uv[2 * vid + 1];
+            } else {
+                const uint8_t *c = m.col ? m.col + 3 * vid : nullptr;
+                r.col[k] = c ? (uint32_t)c[0] | ((uint32_t)c[1] << 8) | ((uint32_t)c[2] << 16) : 0xFFFFFFu;
+            }
+        }
+        rec[t] = r;
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int d = 1; d < 64; d *= 2) {
+            mn[a] = fminf(mn[a], __shfl_xor(mn[a], d));
+            mx[a] = fmaxf(mx[a], __shfl_xor(mx[a], d));
+        }
+    if (lane_id() == 0) {
+        cbox[2 * (t / kCluster)] = make_float4(mn[0], mn[1], mn[2], 0.0f);
+        cbox[2 * (t / kCluster) + 1] = make_float4(mx[0], mx[1], mx[2], 0.0f);
+    }
+}
+
 // ------------------------------------------------------------ k_reset
 __global__ __launch_bounds__(256) void k_reset(DViewCounters *__restrict__ ctr, uint32_t nviews,
                                                uint32_t *__restrict__ tile_count,
@@ -1624,7 +1669,13 @@ __global__ __launch_bounds__(kBandThreads) void k_resolve(const DView *__restric
 }
 
 // As k_resolve, from the tiles' z-keys that k_raster_wave left (a tile without
-// entries has none).
+// entries has none).  A wave shades STACK bands, one below the other: STACK is
+// 1, 2 or 4, so they lie in one row of tiles.  256 mixed 128 / 256 / 512 px
+// views, 29 M pixels: 1.25 ms a step with one band a wave and the winner read
+// as index, positions and three colours, 1.13 with four and the 64-byte record.
+// Bound by the latency of the record's read and by VALU issue (280 instructions
+// a band, 70 % busy).
+template <int STACK>
 __global__ __launch_bounds__(kBandThreads) void k_resolve_wave(const DView *__restrict__ views,
                                                                const uint32_t *__restrict__ lview,
                                                                const uint32_t *__restrict__ bpre, uint32_t nl,
@@ -1644,22 +1695,29 @@ __global__ __launch_bounds__(kBandThreads) void k_resolve_wave(const DView *__re
     const uint32_t W = v.W, H = v.H;
     const uint32_t nbx = (W + kBandW - 1) / kBandW;
     const uint32_t band = blk - bpre[lo];
-    const uint32_t x0 = (band % nbx) * kBandW, y0 = (band / nbx) * kBandH;
+    const uint32_t x0 = (band % nbx) * kBandW, y0 = (band / nbx) * (kBandH * STACK);
     const uint32_t lane = lane_id();
-    const uint32_t pi = x0 + lane % kBandW, pj = y0 + lane / kBandW;
-    const bool in = pi < W && pj < H;
-    float best_rho = 0.0f;
-    uint32_t best_key = kNone;
-    if (in) {
-        const uint32_t tile = (pj >> 4) * v.tiles_x + (pi >> 4);
-        if (tile_count[v.tile_base + tile]) {
-            const uint32_t b = ((pj & 15u) >> 1) * 4u + ((pi & 15u) >> 2);
-            const unsigned long long z = zt[wave_tile(v, tile) + b * 8u + (pj & 1u) * 4u + (pi & 3u)];
-            best_rho = __uint_as_float((uint32_t)(z >> 32));
-            best_key = ~(uint32_t)z;
-        }
+    const uint32_t pi = x0 + lane % kBandW, dj = lane / kBandW;
+    // the stack lies in one row of tiles: all its keys are in flight at once
+    const uint32_t tile = (y0 >> 4) * v.tiles_x + (pi >> 4);
+    unsigned long long z[STACK] = {};
+    if (pi < W && tile_count[v.tile_base + tile]) {
+        const unsigned long long *zp =
+            zt + wave_tile(v, tile) + ((y0 & 15u) >> 1) * 32u + ((pi & 15u) >> 2) * 8u + dj * 4u + (pi & 3u);
+#pragma unroll
+        for (int k = 0; k < STACK; ++k) z[k] = zp[32 * k];
     }
-    shade_band<kBandW, kBandH>(v, x0, y0, (int)pi, (int)pj, in, best_rho, best_key, s_rgb, err);
+#pragma unroll 1
+    for (int k = 0; k < STACK; ++k) {
+        const uint32_t y = y0 + kBandH * (uint32_t)k, pj = y + dj;
+        if (y >= H) break;
+        const unsigned long long zz = z[0];
+#pragma unroll
+        for (int n = 1; n < STACK; ++n) z[n - 1] = z[n];
+        shade_band<kBandW, kBandH>(v, x0, y, (int)pi, (int)pj, pi < W && pj < H, __uint_as_float((uint32_t)(zz >> 32)),
+                                   ~(uint32_t)zz, s_rgb, err);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    }
 }
 
 // ------------------------------------------------------------ host side
@@ -1690,12 +1748,19 @@ template <int TS>
 static void launch_resolve(const LaunchPlan &L, const RasterLaunch &R, hipStream_t s)
 {
     if (R.wave) {
-        hipLaunchKernelGGL(k_resolve_wave, dim3(R.bands), dim3(kBandThreads), 0, s, L.views, R.lview, R.bpre, R.nl,
-                           L.tile_count, L.zbuf, L.err);
+        auto *const k = R.stack == 4 ? k_resolve_wave<4> : R.stack == 2 ? k_resolve_wave<2> : k_resolve_wave<1>;
+        hipLaunchKernelGGL(k, dim3(R.bands), dim3(kBandThreads), 0, s, L.views, R.lview, R.bpre, R.nl, L.tile_count,
+                           L.zbuf, L.err);
         return;
     }
     hipLaunchKernelGGL(k_resolve<TS>, dim3(R.bands), dim3(kBandThreads), 0, s, L.views, R.lview, R.bpre,
                        R.nl, L.tile_count, L.tile_off, L.tile_item, R.partial, L.err);
+}
+
+hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, TriRec *rec, float4 *cbox, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_scene, dim3(cdiv(T, 256)), dim3(256), 0, s, m, T, tpos, rec, cbox);
+    return hipGetLastError();
 }
 
 int raster_blocks_per_cu(int ts, bool lane_owned)

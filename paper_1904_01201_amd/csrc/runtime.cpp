@@ -14,6 +14,12 @@ static constexpr uint32_t kDefaultTile = 16;
 // Pixels + triangles / 8 up to which the direct path draws a launch, and a
 // half of a split batch.
 static constexpr uint64_t kDirectSize = 1200 * 1024, kDirectHalf = 640 * 1024;
+// Resolve waves that a launch keeps when a wave shades two or four bands one
+// after another (its search and start paid once): two rounds of the 8192 that
+// are resident.  1024 depth frames of 64 x 64 resolve in 32 us with one band a
+// wave and 22 with four; 32 textured 256 x 256 views, 33 k bands, in 40 with
+// one, 42 with two and 47 with four, which leaves one round of long waves.
+static constexpr uint64_t kStackWaves = 16384;
 static constexpr uint64_t kIndexLimit = 1ull << 31; // per launch: survivors, bins, tiles
 
 static inline uint32_t cdiv(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
@@ -404,8 +410,7 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         d.T = r.scene->T;
         d.ts_log2 = ts_log2(ts);
         d.tpos = r.scene->tpos;
-        d.col = r.scene->col;
-        d.idx = r.scene->idx;
+        d.rec = r.scene->rec;
         d.cbox = r.scene->cbox;
         d.rgb = r.rgb;
         d.depth = r.depth;
@@ -414,7 +419,6 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         d.sem = r.sem;
         d.noise_sigma = r.sensor.depth_noise_sigma;
         d.noise_seed = r.noise_seed;
-        d.uv = r.scene->uv;
         d.tex = r.scene->tex;
         d.tex_w = r.scene->tw;
         d.tex_h = r.scene->th;
@@ -439,17 +443,22 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         const int c = (int)(direct ? dv[0].ts_log2 : d.ts_log2) - 3;
         lview[c].push_back(k);
     }
+    uint32_t stack[3] = {1, 1, 1};   // bands a resolve block shades
     // Raster blocks are dispatched roughly in block order: put the views of
     // the largest scenes (the longest tile lists) first so that their tiles
     // do not form the tail of the launch.
     for (int c = 0; c < 3; ++c) {
         stable_sort_views(lview[c].begin(), lview[c].end(),
                           [&](uint32_t a, uint32_t b) { return dv[a].T > dv[b].T; });
-        // lpre: each view's first resolve band (32 x 2 pixels)
+        uint64_t bands = 0;
+        for (uint32_t k : lview[c]) bands += (uint64_t)cdiv(dv[k].W, 32u) * cdiv(dv[k].H, 2u);
+        if (!direct && c == 1 && !o.lane_owned_z)
+            stack[c] = bands >= 4 * kStackWaves ? 4u : bands >= 2 * kStackWaves ? 2u : 1u;
+        // lpre: each view's first resolve block
         uint32_t pre = 0;
         for (uint32_t k : lview[c]) {
             lpre[c].push_back(pre);
-            pre += cdiv(dv[k].W, 32u) * cdiv(dv[k].H, 2u);
+            pre += cdiv(dv[k].W, 32u) * cdiv(dv[k].H, 2 * stack[c]);
         }
     }
     if (tile_total >= kIndexLimit || surv_total >= kIndexLimit || bin_total >= kIndexLimit ||
@@ -610,7 +619,8 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         const DView &last = dv[lview[c].back()];
         R.blocks = 0;
         for (uint32_t k : lview[c]) R.blocks += dv[k].tiles_x * dv[k].tiles_y;
-        R.bands = lpre[c].back() + cdiv(last.W, 32u) * cdiv(last.H, 2u);
+        R.bands = lpre[c].back() + cdiv(last.W, 32u) * cdiv(last.H, 2 * stack[c]);
+        R.stack = stack[c];
         R.item_cap = item_cap[c];
         R.grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(item_cap[c], (uint64_t)cus * kBlocksPerCu[c]));
         R.lane_owned = o.lane_owned_z;

@@ -62,11 +62,10 @@ hab_status guarded(F &&f)
 struct Scene {
     int device = 0;
     float *tpos = nullptr;      // [T][3][3] vertex positions per triangle
-    uint32_t *col = nullptr;    // [V] packed
-    uint32_t *idx = nullptr;    // [T][3]
+    TriRec *rec = nullptr;      // [T] records of the shading
+    void *src = nullptr;        // the mesh as uploaded (MeshSource)
     float4 *cbox = nullptr;     // [ceil(T/64)][2] cluster bounding boxes
     uint32_t *inst = nullptr;   // [T] instance id per triangle, or null
-    float *uv = nullptr;        // [V][2] texture coordinates, or null
     uint32_t *tex = nullptr;    // [th][tw] packed RGB texels, or null
     uint32_t tw = 0, th = 0;
     uint32_t V = 0, T = 0;

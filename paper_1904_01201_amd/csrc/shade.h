@@ -10,54 +10,142 @@
 
 namespace habmi {
 
-// Colour, depth and index of the winning sub-triangle at pixel (i, j):
-// the winner's setup is rebuilt with colours, its three edge functions at
-// the pixel centre give the perspective-correct weights.
-// Colour of the winner at pixel (i, j): the triangle's setup rebuilt with
-// the same arithmetic as the raster's (the depth comes from the winning
-// key's 1/w, the same value).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// The first N 16-byte words of triangle t's record.
+template <int N>
+__device__ __forceinline__ void load_rec(const DView &v, uint32_t t, u32x4 (&q)[N])
+{
+    const auto *p = gmem(reinterpret_cast<const u32x4 *>(v.rec + t));
+#pragma unroll
+    for (int k = 0; k < N; ++k) q[k] = p[k];
+}
+
+__device__ __forceinline__ float f32(uint32_t x) { return __uint_as_float(x); }
+
+// x / num for num > 0, correctly rounded as the division is: from r, the
+// correctly rounded 1/num, by two steps of the exact remainder (Markstein: the
+// second starts within an ulp of x / num).  Holds while no step under- or
+// overflows: 2^-60 <= num <= 2^60, and x zero or of magnitude 2^-60 to 2^68.
+// Callers with x below that range use it only where x / num < 2^-40 rounds away.
+constexpr float kDivLo = 0x1p-60f, kDivHi = 0x1p60f;
+__device__ __forceinline__ float div_by(float x, float num, float r)
+{
+    const float q = x * r;
+    const float q1 = __builtin_fmaf(__builtin_fmaf(-q, num, x), r, q);
+    return __builtin_fmaf(__builtin_fmaf(-q1, num, x), r, q1);
+}
+
+// Perspective-correct weights of pixel (i, j), which the triangle covers, for a
+// triangle in front of the near plane (false: it is not, or leaves the
+// fixed-point domain).  Vertices are snapped as the raster does; at a covered
+// pixel the three edge functions have the sign of the area, so their magnitudes
+// are those of the oriented triangle, and the orientation (swapped: vertices 1
+// and 2 change places) is that sign.  w0, w1, w2 are in oriented order.
+__device__ __forceinline__ bool pixel_weights(const DView &v, const float P[9], int i, int j, float &w0, float &w1,
+                                              float &w2, bool &swapped)
+{
+    Vtx<0> c0, c1, c2;
+    cam_xform(v, P[0], P[1], P[2], c0);
+    cam_xform(v, P[3], P[4], P[5], c1);
+    cam_xform(v, P[6], P[7], P[8], c2);
+    if (!(c0.w >= v.zn && c1.w >= v.zn && c2.w >= v.zn)) return false;
+    SVtx<0> a, b, c;
+    bool ok = snap(v, c0, a);
+    ok &= snap(v, c1, b);
+    ok &= snap(v, c2, c);
+    if (!ok) return false;
+    const int px = 256 * i + 128, py = 256 * j + 128;
+    const int ax = a.X - px, ay = a.Y - py, bx = b.X - px, by = b.Y - py, cx = c.X - px, cy = c.Y - py;
+    constexpr int kNear = 1 << 14;
+    float fa, fb, fc;
+    if (abs(ax) < kNear && abs(ay) < kNear && abs(bx) < kNear && abs(by) < kNear && abs(cx) < kNear &&
+        abs(cy) < kNear) {
+        // within 64 px: 24-bit products, |E| < 2^30
+        const int ea = __mul24(bx, cy) - __mul24(by, cx), eb = __mul24(cx, ay) - __mul24(cy, ax),
+                  ec = __mul24(ax, by) - __mul24(ay, bx);
+        swapped = (ea | eb | ec) < 0;
+        fa = (float)abs(ea);
+        fb = (float)abs(eb);
+        fc = (float)abs(ec);
+    } else {
+        const long long ea = (long long)bx * cy - (long long)by * cx, eb = (long long)cx * ay - (long long)cy * ax,
+                        ec = (long long)ax * by - (long long)ay * bx;
+        swapped = (ea | eb | ec) < 0;
+        fa = fabsf((float)ea);
+        fb = fabsf((float)eb);
+        fc = fabsf((float)ec);
+    }
+    w0 = fa * a.rw;
+    const float ub = fb * b.rw, uc = fc * c.rw;
+    w1 = swapped ? uc : ub;
+    w2 = swapped ? ub : uc;
+    return true;
+}
+
+// Colour of the winner at pixel (i, j): the triangle's setup rebuilt with the
+// same arithmetic as the raster's, its three edge functions at the pixel
+// centre give the perspective-correct weights (the depth comes from the
+// winning key's 1/w, the same value).
 __device__ __forceinline__ bool resolve(const DView &v, uint32_t key, int i, int j, uint32_t rgb[3])
 {
     const uint32_t t = key >> 1;
     const int sub = (int)(key & 1u);
-    float P[9];
-    uint32_t vid[3];
-    load_tri(v, t, P, vid);
-    Vtx<3> c0, c1, c2;
-    cam_xform(v, P[0], P[1], P[2], c0);
-    cam_xform(v, P[3], P[4], P[5], c1);
-    cam_xform(v, P[6], P[7], P[8], c2);
-    const uint32_t k0 = v.col ? gmem(v.col)[vid[0]] : 0xFFFFFFu;
-    const uint32_t k1 = v.col ? gmem(v.col)[vid[1]] : 0xFFFFFFu;
-    const uint32_t k2 = v.col ? gmem(v.col)[vid[2]] : 0xFFFFFFu;
+    u32x4 q[3];
+    load_rec(v, t, q);
+    const float P[9] = {f32(q[0].x), f32(q[0].y), f32(q[0].z), f32(q[0].w), f32(q[1].x),
+                        f32(q[1].y), f32(q[1].z), f32(q[1].w), f32(q[2].x)};
+    const uint32_t k0 = q[2].y, k1 = q[2].z, k2 = q[2].w;
+    float w0, w1, w2, x[3], num;
+    bool swapped;
+    if (sub == 0 && pixel_weights(v, P, i, j, w0, w1, w2, swapped)) {
+        const uint32_t kb = swapped ? k2 : k1, kc = swapped ? k1 : k2;
+        num = (w0 + w1) + w2;
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        c0.a[ch] = (float)unpack_rgb(k0, ch);
-        c1.a[ch] = (float)unpack_rgb(k1, ch);
-        c2.a[ch] = (float)unpack_rgb(k2, ch);
-    }
-    SVtx<3> a = {}, b = {}, c = {};
-    long long A = 1;
-    bool rerr = false;
-    if (!setup_sub(v, c0, c1, c2, sub, a, b, c, A, rerr)) {
-        // unreachable: the key came from a successful setup of the same
-        // arithmetic; report it as a device fault rather than guess
-        rgb[0] = rgb[1] = rgb[2] = 0;
-        return false;
-    }
-    const long long px = 256ll * i + 128, py = 256ll * j + 128;
-    const long long E0 = edge_at(b.X, b.Y, c.X, c.Y, px, py);
-    const long long E1 = edge_at(c.X, c.Y, a.X, a.Y, px, py);
-    const long long E2 = edge_at(a.X, a.Y, b.X, b.Y, px, py);
-    const float w0 = (float)E0 * a.rw, w1 = (float)E1 * b.rw, w2 = (float)E2 * c.rw;
-    const float num = (w0 + w1) + w2;
+        for (int ch = 0; ch < 3; ++ch)
+            x[ch] = (w0 * (float)unpack_rgb(k0, ch) + w1 * (float)unpack_rgb(kb, ch)) + w2 * (float)unpack_rgb(kc, ch);
+    } else {
+        Vtx<3> c0, c1, c2;
+        cam_xform(v, P[0], P[1], P[2], c0);
+        cam_xform(v, P[3], P[4], P[5], c1);
+        cam_xform(v, P[6], P[7], P[8], c2);
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-        float val = ((w0 * a.a[ch] + w1 * b.a[ch]) + w2 * c.a[ch]) / num;
-        val = rintf(val);
-        val = fminf(fmaxf(val, 0.0f), 255.0f);
-        rgb[ch] = (uint32_t)val;
+        for (int ch = 0; ch < 3; ++ch) {
+            c0.a[ch] = (float)unpack_rgb(k0, ch);
+            c1.a[ch] = (float)unpack_rgb(k1, ch);
+            c2.a[ch] = (float)unpack_rgb(k2, ch);
+        }
+        SVtx<3> a = {}, b = {}, c = {};
+        long long A = 1;
+        bool rerr = false;
+        if (!setup_sub(v, c0, c1, c2, sub, a, b, c, A, rerr)) {
+            // unreachable: the key came from a successful setup of the same
+            // arithmetic; report it as a device fault rather than guess
+            rgb[0] = rgb[1] = rgb[2] = 0;
+            return false;
+        }
+        const long long px = 256ll * i + 128, py = 256ll * j + 128;
+        const long long E0 = edge_at(b.X, b.Y, c.X, c.Y, px, py);
+        const long long E1 = edge_at(c.X, c.Y, a.X, a.Y, px, py);
+        const long long E2 = edge_at(a.X, a.Y, b.X, b.Y, px, py);
+        w0 = (float)E0 * a.rw;
+        w1 = (float)E1 * b.rw;
+        w2 = (float)E2 * c.rw;
+        num = (w0 + w1) + w2;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) x[ch] = (w0 * a.a[ch] + w1 * b.a[ch]) + w2 * c.a[ch];
     }
+    float val[3];
+    if (__builtin_expect(num >= kDivLo && num <= kDivHi, 1)) {
+        const float r = recip_rn(num);
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) val[ch] = div_by(x[ch], num, r);
+    } else {
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) val[ch] = x[ch] / num;
+    }
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) rgb[ch] = (uint32_t)fminf(fmaxf(rintf(val[ch]), 0.0f), 255.0f);
     return true;
 }
 
@@ -96,36 +184,61 @@ __device__ __forceinline__ bool resolve_tex(const DView &v, uint32_t key, int i,
 {
     const uint32_t t = key >> 1;
     const int sub = (int)(key & 1u);
-    float P[9];
-    uint32_t vid[3];
-    load_tri(v, t, P, vid);
-    Vtx<2> c0, c1, c2;
-    cam_xform(v, P[0], P[1], P[2], c0);
-    cam_xform(v, P[3], P[4], P[5], c1);
-    cam_xform(v, P[6], P[7], P[8], c2);
-    const auto *uv = gmem(v.uv);
-    c0.a[0] = uv[2u * vid[0]];
-    c0.a[1] = uv[2u * vid[0] + 1u];
-    c1.a[0] = uv[2u * vid[1]];
-    c1.a[1] = uv[2u * vid[1] + 1u];
-    c2.a[0] = uv[2u * vid[2]];
-    c2.a[1] = uv[2u * vid[2] + 1u];
-    SVtx<2> a = {}, b = {}, c = {};
-    long long A = 1;
-    bool rerr = false;
-    if (!setup_sub(v, c0, c1, c2, sub, a, b, c, A, rerr)) {
-        rgb[0] = rgb[1] = rgb[2] = 0;
-        return false;
+    u32x4 q[4];
+    load_rec(v, t, q);
+    const float P[9] = {f32(q[0].x), f32(q[0].y), f32(q[0].z), f32(q[0].w), f32(q[1].x),
+                        f32(q[1].y), f32(q[1].z), f32(q[1].w), f32(q[2].x)};
+    const float a0[2] = {f32(q[2].y), f32(q[2].z)}, a1[2] = {f32(q[2].w), f32(q[3].x)},
+                a2[2] = {f32(q[3].y), f32(q[3].z)};
+    float w0, w1, w2, x[2], num;
+    bool swapped;
+    if (sub == 0 && pixel_weights(v, P, i, j, w0, w1, w2, swapped)) {
+        num = (w0 + w1) + w2;
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            x[k] = (w0 * a0[k] + w1 * (swapped ? a2[k] : a1[k])) + w2 * (swapped ? a1[k] : a2[k]);
+    } else {
+        Vtx<2> c0, c1, c2;
+        cam_xform(v, P[0], P[1], P[2], c0);
+        cam_xform(v, P[3], P[4], P[5], c1);
+        cam_xform(v, P[6], P[7], P[8], c2);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            c0.a[k] = a0[k];
+            c1.a[k] = a1[k];
+            c2.a[k] = a2[k];
+        }
+        SVtx<2> a = {}, b = {}, c = {};
+        long long A = 1;
+        bool rerr = false;
+        if (!setup_sub(v, c0, c1, c2, sub, a, b, c, A, rerr)) {
+            rgb[0] = rgb[1] = rgb[2] = 0;
+            return false;
+        }
+        const long long px = 256ll * i + 128, py = 256ll * j + 128;
+        const long long E0 = edge_at(b.X, b.Y, c.X, c.Y, px, py);
+        const long long E1 = edge_at(c.X, c.Y, a.X, a.Y, px, py);
+        const long long E2 = edge_at(a.X, a.Y, b.X, b.Y, px, py);
+        w0 = (float)E0 * a.rw;
+        w1 = (float)E1 * b.rw;
+        w2 = (float)E2 * c.rw;
+        num = (w0 + w1) + w2;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) x[k] = (w0 * a.a[k] + w1 * b.a[k]) + w2 * c.a[k];
     }
-    const long long px = 256ll * i + 128, py = 256ll * j + 128;
-    const long long E0 = edge_at(b.X, b.Y, c.X, c.Y, px, py);
-    const long long E1 = edge_at(c.X, c.Y, a.X, a.Y, px, py);
-    const long long E2 = edge_at(a.X, a.Y, b.X, b.Y, px, py);
-    const float w0 = (float)E0 * a.rw, w1 = (float)E1 * b.rw, w2 = (float)E2 * c.rw;
-    const float num = (w0 + w1) + w2;
-    const float u = ((w0 * a.a[0] + w1 * b.a[0]) + w2 * c.a[0]) / num;
-    const float tv = ((w0 * a.a[1] + w1 * b.a[1]) + w2 * c.a[1]) / num;
-    tex_bilinear(v, u, tv, rgb);
+    float uvp[2];
+    const float m0 = fabsf(x[0]), m1 = fabsf(x[1]);
+    if (__builtin_expect(num >= kDivLo && num <= kDivHi && (m0 == 0.0f || (m0 >= kDivLo && m0 <= kDivHi)) &&
+                             (m1 == 0.0f || (m1 >= kDivLo && m1 <= kDivHi)),
+                         1)) {
+        const float r = recip_rn(num);
+        uvp[0] = div_by(x[0], num, r);
+        uvp[1] = div_by(x[1], num, r);
+    } else {
+        uvp[0] = x[0] / num;
+        uvp[1] = x[1] / num;
+    }
+    tex_bilinear(v, uvp[0], uvp[1], rgb);
     return true;
 }
 
@@ -186,14 +299,14 @@ __device__ __forceinline__ void shade_band(const DView &v, uint32_t x0, uint32_t
             // the depth is the reciprocal of the winning key's 1/w (the value
             // a rebuild of the triangle would compute again); colour needs
             // the rebuild
-            depth = 1.0f / best_rho;
+            depth = recip_rn(best_rho);
             if (v.rgb && !(v.tex ? resolve_tex(v, best_key, pi, pj, rgb) : resolve(v, best_key, pi, pj, rgb)))
                 atomicOr(err, kErrResolve);
         }
         const size_t p = (size_t)pj * W + (size_t)pi;
         if (v.noise_sigma > 0.0f && best_key != kNone) {
             const float rp = best_rho + v.noise_sigma * depth_noise_normal(v.noise_seed, (uint64_t)p);
-            depth = rp > 0.0f ? 1.0f / rp : 0.0f;
+            depth = rp > 0.0f ? recip_rn(rp) : 0.0f;
         }
         if (v.depth) gmem_out(v.depth)[p] = depth;
         if (v.tri) gmem_out(v.tri)[p] = best_key == kNone ? kNone : (best_key >> 1);
