@@ -8,9 +8,10 @@ namespace habmi {
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr uint32_t kOverflow = 0xFFFFFFFFu;   // tile offset marker: list not stored
 constexpr int kSetupBlock = 256;              // threads per block in setup
-constexpr int kSetupWavesPerSimd = 5;         // setup's register budget; its grid is one round of it
+constexpr int kSetupWavesPerSimd = 6;         // setup's register budget; its grid is one round of it
 constexpr int kBinBlock = 256;                // threads per block in count/scatter
-constexpr int kBinItems = 4;                  // survivors per thread in count/scatter
+constexpr int kRun = 4;                       // visible clusters a setup wave takes at a time
+constexpr int kBinRuns = 8;                   // runs per block in count/scatter
 constexpr int kScanBlock = 1024;
 constexpr int kCluster = 64;                  // triangles per culling cluster (one wave)
 
@@ -46,7 +47,7 @@ struct alignas(16) DView {
     uint32_t *tri;              // [H][W] or null
     uint32_t tiles_x, tiles_y;
     uint32_t tile_base;         // first entry in the per-tile arrays
-    uint32_t surv_base;         // first entry in the survivor arrays
+    uint32_t surv_base;         // first entry in the survivor arrays: two slots a triangle, by run
     uint32_t surv_cap;          // 2 T
     uint32_t bin_base;          // first entry in the bin array
     uint32_t bin_cap;           // entries available to this view
@@ -98,14 +99,15 @@ constexpr uint32_t kBuckets = 16;     // distance buckets of a view's visible cl
 // those reads never queue behind the atomics (nor do different views'
 // atomics meet on one line).
 struct alignas(128) DViewCounters {
-    uint32_t surv_count;        // survivors appended by setup
+    uint32_t surv_count;        // survivors of the setup (views whose work is counted)
     uint32_t bin_used;          // entries the scan assigned
     unsigned long long bbox_tests;
     unsigned long long covered;
     uint32_t pad[26];
     uint32_t vis_clusters;      // clusters that passed the view's frustum test
+    uint32_t vis_tail;          // 1: the last, partial cluster did too (tile lists; not in the list)
     uint32_t bucket[kBuckets];  // direct path: visible clusters per distance bucket
-    uint32_t pad2[31 - kBuckets];
+    uint32_t pad2[30 - kBuckets];
 };
 static_assert(sizeof(DViewCounters) == 256, "counter lines");
 

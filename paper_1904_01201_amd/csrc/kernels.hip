@@ -7,16 +7,16 @@
 //                of the cluster's box; the visible clusters are listed
 //   k_setup      per (view, run of visible clusters): fetch each triangle,
 //                transform, clip, snap, orient and cull it; survivors (key,
-//                pixel bbox) are appended to the view's list with
-//                wave-level prefix-sum compaction (the views of a scene are
-//                consecutive, so its triangles are re-read from L2/MALL)
-//   k_bin<count> per chunk of survivors: LDS histogram of the screen tiles
+//                pixel bbox) go to the run's slots with wave-level
+//                compaction (the views of a scene are consecutive, so its
+//                triangles are re-read from L2/MALL)
+//   k_bin<count> per chunk of runs: LDS histogram of the screen tiles
 //                their boxes touch, one global add per touched tile
 //   k_bin_scan   per view: exclusive scans of the tile counts (list offsets;
 //                tiles over capacity take the lossless overflow path) and of
 //                the tiles' segment counts; the (tile, segment) work items
 //                are appended to the queue of the view's tile size
-//   k_bin<scatter> per chunk of survivors: write each key into every touched
+//   k_bin<scatter> per chunk of runs: write each key into every touched
 //                tile's list (LDS ranks, one global reservation per tile)
 //   k_raster<TS> persistent blocks pull (tile, segment) items from the queue
 //                (an atomic counter used for work distribution only).  The
@@ -106,6 +106,7 @@ __global__ __launch_bounds__(256) void k_reset(DViewCounters *__restrict__ ctr, 
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     if (i < nviews) {
         ctr[i].vis_clusters = 0;
+        ctr[i].vis_tail = 0;
         ctr[i].surv_count = 0;
         ctr[i].bin_used = 0;
         ctr[i].bbox_tests = 0;
@@ -285,6 +286,10 @@ __global__ __launch_bounds__(kCullBlock) void k_cull(const DView *__restrict__ v
         const auto *b = gmem(reinterpret_cast<const float *>(v.cbox)) + 8ull * c;
         vis = !box_outside(v, make_float4(b[0], b[1], b[2], b[3]), make_float4(b[4], b[5], b[6], b[7]));
     }
+    if (vis && c == ncl - 1 && v.T % kCluster) {
+        ctr[vi].vis_tail = 1;
+        vis = false;
+    }
     uint32_t tot;
     const uint32_t ex = block_excl_scan<kCullBlock>(vis ? 1u : 0u, wtot, &tot);
     if (threadIdx.x == 0) sbase = tot ? atomicAdd(&ctr[vi].vis_clusters, tot) : 0u;
@@ -293,176 +298,47 @@ __global__ __launch_bounds__(kCullBlock) void k_cull(const DView *__restrict__ v
 }
 
 // Work items of k_setup: (view, run of kRun visible clusters).  Each block
-// builds the prefix of item counts over the views in LDS; each wave then
-// takes a contiguous range of items.  A wave sets up one triangle of each
-// of the run's clusters per lane (independent loads in flight together),
-// appends the survivors (key, box) to its LDS buffer, and copies the buffer
-// out behind one slot reservation when the view changes or the buffer is
-// full: device-wide atomics, not the arithmetic, bound this stage.
-constexpr uint32_t kRun = 4;
-constexpr uint32_t kSetupBuf = 2 * kRun * kCluster;   // survivors one wave buffers in LDS
+// builds the prefix of item counts over the views in LDS; the waves stride over
+// the items.  A wave sets up one triangle of each of the run's clusters per lane
+// (independent loads in flight together).
+//
+// A run's survivors (key, box) go to slots of their own, two per triangle of a
+// full run, and their number into the run's first list entry (which held its
+// first cluster).  Only a view's last run can hold the scene's last, partial
+// cluster, so its runs' slots fit two per triangle of the scene.
+constexpr uint32_t kSlots = 2 * kRun * kCluster;
 
-// 5 waves per SIMD (at most 96 VGPRs; 85 used, none spilled): the four
-// clusters' loads per lane are in flight together, and at 6 waves the
-// spills cost about what the extra wave hides
-__global__ __launch_bounds__(kSetupBlock) __attribute__((amdgpu_waves_per_eu(kSetupWavesPerSimd))) void k_setup(const DView *__restrict__ views,
-                                                       uint32_t nviews,
-                                                       DViewCounters *__restrict__ ctr,
-                                                       const uint32_t *__restrict__ vis_clusters,
-                                                       uint32_t *__restrict__ skey,
-                                                       uint2 *__restrict__ sbox,
-                                                       uint32_t *__restrict__ err)
+// A view's visible clusters.  The list leaves out the scene's last cluster if
+// that is partial; it comes after the others.
+__device__ __forceinline__ uint32_t visible_clusters(const DViewCounters &c) { return c.vis_clusters + c.vis_tail; }
+
+// Place `at` of survivor s (counting kSlots per run) of view v; false if there
+// is none.
+__device__ __forceinline__ bool survivor_slot(const DView &v, const uint32_t *__restrict__ vis_clusters, uint32_t s,
+                                              uint32_t &at)
 {
-    extern __shared__ uint32_t pre[];      // [nviews]: sized at launch
-    __shared__ uint32_t bkey[kSetupBlock / 64][kSetupBuf];
-    __shared__ uint2 bbox[kSetupBlock / 64][kSetupBuf];
-    // the prologue scan's per-wave totals live in the first survivor buffer
-    // (dead until the barrier below): 40 KiB per block, four blocks per CU
-    uint32_t *const wtot = bkey[0];
-    uint32_t total;
-    {
-        const uint32_t seg = (nviews + kSetupBlock - 1) / kSetupBlock;
-        const uint32_t i0 = threadIdx.x * seg, i1 = min(i0 + seg, nviews);
-        uint32_t local = 0;
-        for (uint32_t i = i0; i < i1; ++i) local += (ctr[i].vis_clusters + kRun - 1) / kRun;
-        uint32_t run = block_excl_scan<kSetupBlock>(local, wtot, &total);
-        for (uint32_t i = i0; i < i1; ++i) {
-            pre[i] = run;
-            run += (ctr[i].vis_clusters + kRun - 1) / kRun;
-        }
-        __syncthreads();
-    }
-    const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
-    const unsigned long long lt = lanemask_lt();
-    // each wave takes a contiguous range of items (mostly of one view)
-    const uint32_t wave0 = uniform((blockIdx.x * kSetupBlock + threadIdx.x) >> 6);
-    const uint32_t nwaves = (gridDim.x * kSetupBlock) >> 6;
-    const uint32_t per = (total + nwaves - 1) / nwaves;
-    const uint32_t i0 = min(total, wave0 * per), i1 = min(total, i0 + per);
-    uint32_t *const wkey = bkey[w];
-    uint2 *const wbox = bbox[w];
-    uint32_t nbuf = 0, bview = 0;
-    unsigned long long barea = 0;   // bbox pixels of the buffered survivors (lane 0)
-    bool rerr = false;
-    // copy the wave's buffered survivors of view bview out with one atomic
-    auto flush = [&]() {
-        if (!nbuf) return;
-        uint32_t base = 0;
-        if (lane == 0) {
-            base = atomicAdd(&ctr[bview].surv_count, nbuf);
-            if (barea) atomicAdd(&ctr[bview].bbox_tests, barea);
-        }
-        base = __shfl(base, 0) + views[bview].surv_base;
-        __threadfence_block();
-        for (uint32_t i = lane; i < nbuf; i += 64) {
-            skey[base + i] = wkey[i];
-            sbox[base + i] = wbox[i];
-        }
-        __threadfence_block();
-        nbuf = 0;
-        barea = 0;
-    };
-    for (uint32_t item = i0; item < i1; ++item) {
-        uint32_t lo = 0, hi = nviews - 1;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi + 1) >> 1;
-            if (pre[mid] <= item) lo = mid;
-            else hi = mid - 1;
-        }
-        const uint32_t vi = uniform(lo);
-        if (vi != bview) {
-            flush();
-            bview = vi;
-        }
-        const DView &v = views[vi];
-        const uint32_t first = (item - pre[vi]) * kRun;
-        const uint32_t nrun = min(kRun, ctr[vi].vis_clusters - first);
-        uint32_t t[kRun];
-        bool valid[kRun];
-        float P[kRun][9];
-#pragma unroll
-        for (uint32_t j = 0; j < kRun; ++j) {
-            t[j] = j < nrun ? vis_clusters[v.pair_base + first + j] * kCluster + lane : 0xFFFFFFFFu;
-            valid[j] = j < nrun && t[j] < v.T;
-        }
-#pragma unroll
-        for (uint32_t j = 0; j < kRun; ++j) {
-            if (valid[j]) {
-                load_pos(v, t[j], P[j]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 9; ++k) P[j][k] = 0.0f;
-            }
-        }
-        // set up the runs' triangles one cluster at a time, appending the
-        // survivors in (cluster, sub, lane) order: only one cluster's boxes
-        // are live at once
-#pragma unroll
-        for (uint32_t j = 0; j < kRun; ++j) {
-            bool s0, s1;
-            PixBox b0, b1;
-            survive(v, P[j], valid[j], s0, s1, b0, b1, rerr);
-            const unsigned long long m0 = __ballot(s0), m1 = __ballot(s1);
-            const uint32_t c0 = (uint32_t)__popcll(m0), cnt = c0 + (uint32_t)__popcll(m1);
-            if (!cnt) continue;
-            if (nbuf + cnt > kSetupBuf) flush();   // cnt <= 2 * 64 <= kSetupBuf
-            if (v.count_work) {
-                uint32_t area = 0;
-                if (s0) area += (uint32_t)(b0.i1 - b0.i0 + 1) * (uint32_t)(b0.j1 - b0.j0 + 1);
-                if (s1) area += (uint32_t)(b1.i1 - b1.i0 + 1) * (uint32_t)(b1.j1 - b1.j0 + 1);
-                // two boxes of at most 2^24 pixels per lane: the two halves
-                // of the wave sum cannot overflow
-                const uint32_t alo = wave_sum_u32(area & 0xFFFFu);
-                const uint32_t ahi = wave_sum_u32(area >> 16);
-                barea += (unsigned long long)alo + ((unsigned long long)ahi << 16);
-            }
-            if (s0) {
-                const uint32_t k = nbuf + (uint32_t)__popcll(m0 & lt);
-                wkey[k] = 2u * t[j];
-                wbox[k] = pack_box(b0);
-            }
-            if (s1) {
-                const uint32_t k = nbuf + c0 + (uint32_t)__popcll(m1 & lt);
-                wkey[k] = 2u * t[j] + 1u;
-                wbox[k] = pack_box(b1);
-            }
-            nbuf += cnt;
-        }
-    }
-    flush();
-    if (rerr) atomicOr(err, kErrRange);
+    at = v.surv_base + s;
+    return s % kSlots < vis_clusters[v.pair_base + s / kSlots * kRun];
 }
 
-// ------------------------------------------------------------ binning
-// Items of the count/scatter kernels are (view, chunk of kBinChunk
-// survivors); every block builds the prefix of chunk counts over the views
-// from the device-side survivor counts, then strides over the items.
-constexpr uint32_t kBinChunk = kBinBlock * kBinItems;
-constexpr uint32_t kLdsTiles = 2048;   // views with more tiles bin through global atomics
-
-__device__ __forceinline__ uint32_t build_item_prefix(const DViewCounters *ctr, uint32_t nviews,
-                                                      uint32_t *pre, uint32_t *wtot)
+// The exclusive prefix over the views of ceil(visible clusters / per).
+template <int NT>
+__device__ __forceinline__ uint32_t build_prefix(const DViewCounters *ctr, uint32_t nviews, uint32_t per, uint32_t *pre,
+                                                 uint32_t *wtot)
 {
-    const uint32_t seg = (nviews + kBinBlock - 1) / kBinBlock;
+    const uint32_t seg = (nviews + NT - 1) / NT;
     const uint32_t i0 = threadIdx.x * seg, i1 = min(i0 + seg, nviews);
     uint32_t local = 0;
-    for (uint32_t i = i0; i < i1; ++i) local += (ctr[i].surv_count + kBinChunk - 1) / kBinChunk;
+    for (uint32_t i = i0; i < i1; ++i) local += (visible_clusters(ctr[i]) + per - 1) / per;
     uint32_t total;
-    uint32_t run = block_excl_scan<kBinBlock>(local, wtot, &total);
+    uint32_t run = block_excl_scan<NT>(local, wtot, &total);
     for (uint32_t i = i0; i < i1; ++i) {
         pre[i] = run;
-        run += (ctr[i].surv_count + kBinChunk - 1) / kBinChunk;
+        run += (visible_clusters(ctr[i]) + per - 1) / per;
     }
     __syncthreads();
     return total;
 }
-
-// LDS slot of tile i in the per-chunk tile arrays: the low five bits are
-// XORed with the next five, a permutation within each aligned run of 32
-// slots.  Vertically adjacent tiles (32 per row at 256 px / 8 px tiles) would
-// otherwise share an LDS bank, and a wave's boxes touch such columns of tiles
-// together; the arrays are cleared up to the next multiple of 32.
-__device__ __forceinline__ uint32_t swz(uint32_t i) { return i ^ ((i >> 5) & 31u); }
 
 __device__ __forceinline__ uint32_t find_view(const uint32_t *pre, uint32_t nviews, uint32_t item)
 {
@@ -474,6 +350,108 @@ __device__ __forceinline__ uint32_t find_view(const uint32_t *pre, uint32_t nvie
     }
     return lo;
 }
+
+// Each wave appends to a run's own slots: no counter that other waves wait for.
+// (Survivors gathered in LDS and appended to the view's list behind an atomic
+// add, 500 at a time, met 600 others at each of eight views' counters: eight
+// 512 x 384 views of 1M triangles set up in 59 us, now 42; 64 views of 4 scenes
+// 114-134 and 102, 1024 views of 20k triangles 126 and 106.  The lists had no
+// gaps, which took 4 us less in the count and 9 in the scatter.)  The run's
+// loads are in flight together; 6 waves per SIMD (78 VGPRs).  Bound by VALU
+// issue and the reads of 36 bytes a triangle.
+__global__ __launch_bounds__(kSetupBlock) __attribute__((amdgpu_waves_per_eu(kSetupWavesPerSimd))) void k_setup(
+    const DView *__restrict__ views, uint32_t nviews, DViewCounters *__restrict__ ctr, uint32_t *vis_clusters,
+    uint32_t *__restrict__ skey, uint2 *__restrict__ sbox, uint32_t *__restrict__ err)
+{
+    extern __shared__ uint32_t pre[];      // [nviews]: sized at launch
+    __shared__ uint32_t wtot[kSetupBlock / 64];
+    const uint32_t total = build_prefix<kSetupBlock>(ctr, nviews, kRun, pre, wtot);
+    const uint32_t lane = lane_id();
+    const unsigned long long lt = lanemask_lt();
+    const uint32_t nwaves = (gridDim.x * kSetupBlock) >> 6;
+    bool rerr = false;
+    for (uint32_t item = uniform((blockIdx.x * kSetupBlock + threadIdx.x) >> 6); item < total; item += nwaves) {
+        const uint32_t vi = uniform(find_view(pre, nviews, item));
+        const DView &v = views[vi];
+        const uint32_t run = item - uniform(pre[vi]), first = run * kRun;
+        const uint32_t nvis = visible_clusters(ctr[vi]), nlist = ctr[vi].vis_clusters;
+        uint32_t *const entry = vis_clusters + v.pair_base + first;
+        uint32_t cl[kRun], t[kRun];
+        bool valid[kRun];
+        float P[kRun][9];
+#pragma unroll
+        for (uint32_t j = 0; j < kRun; ++j) cl[j] = entry[min(j, nvis - 1 - first)];
+#pragma unroll
+        for (uint32_t j = 0; j < kRun; ++j) {
+            t[j] = (first + j < nlist ? uniform(cl[j]) : (v.T - 1) / kCluster) * kCluster + lane;
+            valid[j] = first + j < nvis && t[j] < v.T;
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < kRun; ++j) {
+            if (valid[j]) {
+                load_pos(v, t[j], P[j]);
+            } else {
+#pragma unroll
+                for (int a = 0; a < 9; ++a) P[j][a] = 0.0f;
+            }
+        }
+        // one cluster at a time, its survivors in (sub, lane) order: only one
+        // cluster's boxes are live at once
+        const uint32_t base = v.surv_base + run * kSlots;
+        uint32_t n = 0;
+        unsigned long long narea = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < kRun; ++j) {
+            bool s0, s1;
+            PixBox b0, b1;
+            survive(v, P[j], valid[j], s0, s1, b0, b1, rerr);
+            const unsigned long long m0 = __ballot(s0), m1 = __ballot(s1);
+            if (s0) {
+                const uint32_t o = base + n + (uint32_t)__popcll(m0 & lt);
+                skey[o] = 2u * t[j];
+                sbox[o] = pack_box(b0);
+            }
+            n += (uint32_t)__popcll(m0);
+            if (s1) {
+                const uint32_t o = base + n + (uint32_t)__popcll(m1 & lt);
+                skey[o] = 2u * t[j] + 1u;
+                sbox[o] = pack_box(b1);
+            }
+            n += (uint32_t)__popcll(m1);
+            if (v.count_work) {
+                uint32_t area = 0;
+                if (s0) area += (uint32_t)(b0.i1 - b0.i0 + 1) * (uint32_t)(b0.j1 - b0.j0 + 1);
+                if (s1) area += (uint32_t)(b1.i1 - b1.i0 + 1) * (uint32_t)(b1.j1 - b1.j0 + 1);
+                // two boxes of at most 2^24 pixels per lane: the two halves
+                // of the wave sum cannot overflow
+                const uint32_t alo = wave_sum_u32(area & 0xFFFFu);
+                const uint32_t ahi = wave_sum_u32(area >> 16);
+                narea += (unsigned long long)alo + ((unsigned long long)ahi << 16);
+            }
+        }
+        if (lane == 0) {
+            entry[0] = n;
+            if (v.count_work && n) {
+                atomicAdd(&ctr[vi].surv_count, n);
+                atomicAdd(&ctr[vi].bbox_tests, narea);
+            }
+        }
+    }
+    if (rerr) atomicOr(err, kErrRange);
+}
+
+// ------------------------------------------------------------ binning
+// Items of the count/scatter kernels are (view, chunk of kBinRuns runs); every block builds the prefix of chunk counts over the
+// views, then strides over the items.
+constexpr uint32_t kBinHeld = 4;       // survivors a thread holds in registers
+constexpr uint32_t kLdsTiles = 2048;   // views with more tiles bin through global atomics
+
+// LDS slot of tile i in the per-chunk tile arrays: the low five bits are
+// XORed with the next five, a permutation within each aligned run of 32
+// slots.  Vertically adjacent tiles (32 per row at 256 px / 8 px tiles) would
+// otherwise share an LDS bank, and a wave's boxes touch such columns of tiles
+// together; the arrays are cleared up to the next multiple of 32.
+__device__ __forceinline__ uint32_t swz(uint32_t i) { return i ^ ((i >> 5) & 31u); }
 
 // Tiles [tx0, tx1] x [ty0, ty1] that a survivor's pixel box touches.
 struct TileRange {
@@ -490,9 +468,13 @@ __device__ __forceinline__ TileRange tile_range(uint2 bb, uint32_t ts)
     return r;
 }
 
+// Eight waves per SIMD (64 VGPRs in the scatter): 2048 blocks, the grid, are
+// resident; with 66 VGPRs a quarter of them ran after the others (1024 views'
+// scatter 47 us, 41 so).
 template <bool SCATTER>
-__global__ __launch_bounds__(kBinBlock) void k_bin(const DView *__restrict__ views, uint32_t nviews,
+__global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_bin(const DView *__restrict__ views, uint32_t nviews,
                                                    const DViewCounters *__restrict__ ctr,
+                                                   const uint32_t *__restrict__ vis_clusters,
                                                    const uint32_t *__restrict__ skey,
                                                    const uint2 *__restrict__ sbox,
                                                    uint32_t *__restrict__ tile_count,
@@ -506,30 +488,64 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(const DView *__restrict__ vie
     // the prefix scan's per-wave totals live in the histogram (first
     // written after the scan's closing barrier): 32 KiB per scatter block
     uint32_t *const wtot = hist;
-    const uint32_t total = build_item_prefix(ctr, nviews, pre, wtot);
+    const uint32_t total = build_prefix<kBinBlock>(ctr, nviews, kBinRuns * kRun, pre, wtot);
     const uint32_t tid = threadIdx.x;
     for (uint32_t item = blockIdx.x; item < total; item += gridDim.x) {
         const uint32_t vi = uniform(find_view(pre, nviews, item));
         const DView &v = views[vi];
-        const uint32_t cnt = ctr[vi].surv_count;
-        const uint32_t s0 = (item - pre[vi]) * kBinChunk;
+        // the chunk's survivors, as if without the gaps between its runs
+        const uint32_t run = (item - uniform(pre[vi])) * kBinRuns, nvis = visible_clusters(ctr[vi]);
+        uint32_t n = 0, first[kBinRuns], gap[kBinRuns];
+#pragma unroll
+        for (uint32_t j = 0; j < kBinRuns; ++j)   // without branches: all in flight together
+            gap[j] = vis_clusters[v.pair_base + min(run + j, (nvis - 1) / kRun) * kRun];
+#pragma unroll
+        for (uint32_t j = 0; j < kBinRuns; ++j) {
+            const uint32_t c = (run + j) * kRun < nvis ? uniform(gap[j]) : 0u;
+            n += c;
+            first[j] = n;   // of the next run
+            gap[j] = kSlots - c;
+        }
+        const uint32_t slot0 = v.surv_base + run * kSlots;
+        auto at = [&](uint32_t e) {
+            uint32_t s = slot0 + e;
+#pragma unroll
+            for (uint32_t j = 0; j + 1 < kBinRuns; ++j) s += e >= first[j] ? gap[j] : 0u;
+            return s;
+        };
         // the view's fields in registers: the atomics below may not be
         // assumed to leave the view records alone
         const uint32_t ts = v.ts_log2, tiles_x = v.tiles_x, nt = v.tiles_x * v.tiles_y;
-        const uint32_t tile_base = v.tile_base, bin_base = v.bin_base, surv_base = v.surv_base;
+        const uint32_t tile_base = v.tile_base, bin_base = v.bin_base;
         if (nt <= kLdsTiles) {
+            // a thread's first survivors, loaded together while the histogram
+            // is cleared and kept for the scatter; a chunk of 8 runs has about
+            // 860, more go one round at a time
+            uint2 box[kBinHeld];
+            uint32_t key[kBinHeld];
+#pragma unroll
+            for (uint32_t r = 0; r < kBinHeld; ++r) {
+                box[r] = make_uint2(0u, 0u);
+                const uint32_t e = r * kBinBlock + tid;
+                if (e < n) {
+                    const uint32_t s = at(e);
+                    box[r] = sbox[s];
+                    if (SCATTER) key[r] = skey[s];
+                }
+            }
             for (uint32_t i = tid; i < ((nt + 31u) & ~31u); i += kBinBlock) hist[i] = 0;
             __syncthreads();
-            // count this chunk's entries per tile in LDS (at most kBinChunk
-            // per tile: fits the 16-bit half)
-#pragma unroll 1
-            for (int r = 0; r < kBinItems; ++r) {
-                const uint32_t s = s0 + (uint32_t)r * kBinBlock + tid;
-                if (s >= cnt) break;
-                const TileRange R = tile_range(sbox[surv_base + s], ts);
+            // count this chunk's entries per tile in LDS (at most kSlots a
+            // run and tile: fits the 16-bit half)
+            auto count = [&](uint2 bb) {
+                const TileRange R = tile_range(bb, ts);
                 for (int ty = R.ty0; ty <= R.ty1; ++ty)
                     for (int tx = R.tx0; tx <= R.tx1; ++tx) atomicAdd(&hist[swz((uint32_t)ty * tiles_x + (uint32_t)tx)], 1u);
-            }
+            };
+#pragma unroll
+            for (uint32_t r = 0; r < kBinHeld; ++r)
+                if (r * kBinBlock + tid < n) count(box[r]);
+            for (uint32_t e = kBinHeld * kBinBlock + tid; e < n; e += kBinBlock) count(sbox[at(e)]);
             __syncthreads();
             // one global operation per touched tile; a thread's tiles are
             // i, i + kBinBlock, ...: their loads and atomics are issued
@@ -567,34 +583,36 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(const DView *__restrict__ vie
             }
             if (SCATTER) {
                 __syncthreads();
-#pragma unroll 1
-                for (int r = 0; r < kBinItems; ++r) {
-                    const uint32_t s = s0 + (uint32_t)r * kBinBlock + tid;
-                    if (s >= cnt) break;
-                    const TileRange R = tile_range(sbox[surv_base + s], ts);
-                    const uint32_t key = skey[surv_base + s];
+                auto put = [&](uint2 bb, uint32_t k) {
+                    const TileRange R = tile_range(bb, ts);
                     for (int ty = R.ty0; ty <= R.ty1; ++ty)
                         for (int tx = R.tx0; tx <= R.tx1; ++tx) {
                             const uint32_t tl = (uint32_t)ty * tiles_x + (uint32_t)tx;
                             const uint32_t b = lbase[swz(tl)];
                             if (b == kOverflow) continue;
                             const uint32_t rank = atomicAdd(&hist[swz(tl)], 1u << 16) >> 16;
-                            bins[bin_base + b + rank] = key;
+                            bins[bin_base + b + rank] = k;
                         }
+                };
+#pragma unroll
+                for (uint32_t r = 0; r < kBinHeld; ++r)
+                    if (r * kBinBlock + tid < n) put(box[r], key[r]);
+                for (uint32_t e = kBinHeld * kBinBlock + tid; e < n; e += kBinBlock) {
+                    const uint32_t s = at(e);
+                    put(sbox[s], skey[s]);
                 }
             }
             __syncthreads();
         } else {
             // large views: wave-aggregated global atomics
 #pragma unroll 1
-            for (int r = 0; r < kBinItems; ++r) {
-                const uint32_t s = s0 + (uint32_t)r * kBinBlock + tid;
-                const bool has = s < cnt;
+            for (uint32_t e0 = 0; e0 < n; e0 += kBinBlock) {
                 TileRange R = {0, 0, -1, -1};   // empty
                 uint32_t key = 0;
-                if (has) {
-                    R = tile_range(sbox[v.surv_base + s], ts);
-                    if (SCATTER) key = skey[v.surv_base + s];
+                if (e0 + tid < n) {
+                    const uint32_t s = at(e0 + tid);
+                    R = tile_range(sbox[s], ts);
+                    if (SCATTER) key = skey[s];
                 }
                 // every lane walks its box's tiles row by row
                 int tx = R.tx0, ty = R.ty0;
@@ -1029,8 +1047,8 @@ constexpr uint32_t kWavePairs = 512;   // (record, block) pairs listed at once: 
 
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPerSimd))) void k_raster_wave(
     const DView *__restrict__ views, const uint2 *__restrict__ items, DQueue *__restrict__ q,
-    DViewCounters *__restrict__ ctr, const uint32_t *__restrict__ skey, const uint2 *__restrict__ sbox,
-    const uint32_t *__restrict__ tile_count, const uint32_t *__restrict__ tile_off, const uint32_t *__restrict__ bins,
+    DViewCounters *__restrict__ ctr, const uint32_t *__restrict__ vis_clusters, const uint32_t *__restrict__ skey,
+    const uint2 *__restrict__ sbox, const uint32_t *__restrict__ tile_count, const uint32_t *__restrict__ tile_off, const uint32_t *__restrict__ bins,
     unsigned long long *__restrict__ zt, uint32_t *__restrict__ err)
 {
     constexpr int TS = 16;
@@ -1065,7 +1083,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPe
         const uint32_t off = uniform(tile_off[v.tile_base + tile]);
         const bool over = off == kOverflow;
         const uint32_t begin = over ? 0u : sgm * kWaveSeg;
-        const uint32_t end = over ? uniform(ctr[vi].surv_count) : min(begin + kWaveSeg, cnt);
+        const uint32_t end = over ? (uniform(visible_clusters(ctr[vi])) + kRun - 1) / kRun * kSlots : min(begin + kWaveSeg, cnt);
         const uint32_t *list = bins + v.bin_base + (over ? 0u : off);
         uint4 *const z4 = reinterpret_cast<uint4 *>(zk);
         z4[lane] = make_uint4(0, 0, 0, 0);
@@ -1086,10 +1104,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPe
             bool packed = true, have = e < end;
             if (have) {
                 if (over) {
-                    const uint2 bb = sbox[v.surv_base + e];
-                    have = (int)(bb.y & 0xFFFFu) >= ti0 && (int)(bb.x & 0xFFFFu) < ti0 + TS &&
-                           (int)(bb.y >> 16) >= tj0 && (int)(bb.x >> 16) < tj0 + TS;
-                    key = skey[v.surv_base + e];
+                    uint32_t at;
+                    have = survivor_slot(v, vis_clusters, e, at);
+                    if (have) {
+                        const uint2 bb = sbox[at];
+                        have = (int)(bb.y & 0xFFFFu) >= ti0 && (int)(bb.x & 0xFFFFu) < ti0 + TS &&
+                               (int)(bb.y >> 16) >= tj0 && (int)(bb.x >> 16) < tj0 + TS;
+                        key = skey[at];
+                    }
                 } else {
                     key = list[e];
                 }
@@ -1225,6 +1247,7 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 32
                                                    const uint2 *__restrict__ items,
                                                    DQueue *__restrict__ q,
                                                    DViewCounters *__restrict__ ctr,
+                                                   const uint32_t *__restrict__ vis_clusters,
                                                    const uint32_t *__restrict__ skey,
                                                    const uint2 *__restrict__ sbox,
                                                    const uint32_t *__restrict__ tile_count,
@@ -1310,7 +1333,7 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 32
         const uint32_t off = tile_off[tglob];
         const bool over = off == kOverflow;
         const uint32_t begin = over ? 0u : sgm * S;
-        const uint32_t end = over ? ctr[vi].surv_count : min(begin + S, cnt);
+        const uint32_t end = over ? (visible_clusters(ctr[vi]) + kRun - 1) / kRun * kSlots : min(begin + S, cnt);
         const uint32_t *list = bins + v.bin_base + (over ? 0u : off);
 
         // z-key of the best fragment so far: 1/w bits above the complemented
@@ -1336,13 +1359,17 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 32
                 LExt rx;
                 if (e < end) {
                     bool go = true;
-                    uint32_t key;
+                    uint32_t key = 0;
                     if (over) {
-                        const uint2 bb = sbox[v.surv_base + e];
-                        const int i0 = (int)(bb.x & 0xFFFFu), j0 = (int)(bb.x >> 16);
-                        const int i1 = (int)(bb.y & 0xFFFFu), j1 = (int)(bb.y >> 16);
-                        go = i1 >= ti0 && i0 < ti0 + TS && j1 >= tj0 && j0 < tj0 + TS;
-                        key = skey[v.surv_base + e];
+                        uint32_t at;
+                        go = survivor_slot(v, vis_clusters, e, at);
+                        if (go) {
+                            const uint2 bb = sbox[at];
+                            const int i0 = (int)(bb.x & 0xFFFFu), j0 = (int)(bb.x >> 16);
+                            const int i1 = (int)(bb.y & 0xFFFFu), j1 = (int)(bb.y >> 16);
+                            go = i1 >= ti0 && i0 < ti0 + TS && j1 >= tj0 && j0 < tj0 + TS;
+                            key = skey[at];
+                        }
                     } else {
                         key = list[e];
                     }
@@ -1732,16 +1759,16 @@ template <int TS>
 static void launch_raster(const LaunchPlan &L, const RasterLaunch &R, hipStream_t s)
 {
     if (R.wave) {
-        hipLaunchKernelGGL(k_raster_wave, dim3(R.grid), dim3(64), 0, s, L.views, R.items, L.queue, L.ctr, L.skey,
-                           L.sbox, L.tile_count, L.tile_off, L.bins, L.zbuf, L.err);
+        hipLaunchKernelGGL(k_raster_wave, dim3(R.grid), dim3(64), 0, s, L.views, R.items, L.queue, L.ctr, L.pairs,
+                           L.skey, L.sbox, L.tile_count, L.tile_off, L.bins, L.zbuf, L.err);
         return;
     }
     if (R.lane_owned)
         hipLaunchKernelGGL((k_raster<TS, true>), dim3(R.grid), dim3(TS * TS), 0, s, L.views, R.items, L.queue,
-                           L.ctr, L.skey, L.sbox, L.tile_count, L.tile_off, L.bins, R.partial, L.err);
+                           L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.bins, R.partial, L.err);
     else if constexpr (TS != 16)
         hipLaunchKernelGGL((k_raster<TS, false>), dim3(R.grid), dim3(TS * TS), 0, s, L.views, R.items, L.queue,
-                           L.ctr, L.skey, L.sbox, L.tile_count, L.tile_off, L.bins, R.partial, L.err);
+                           L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.bins, R.partial, L.err);
 }
 
 template <int TS>
@@ -1796,7 +1823,7 @@ hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
     mark(L, 3, s);
     mark(L, 4, s);
     hipLaunchKernelGGL(k_bin<false>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s, L.views, L.nviews,
-                       L.ctr, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins);
+                       L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins);
     mark(L, 5, s);
     mark(L, 6, s);
     hipLaunchKernelGGL(k_bin_scan, dim3(L.nviews), dim3(kScanBlock), 0, s, L.views, L.ctr,
@@ -1805,7 +1832,7 @@ hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
     mark(L, 7, s);
     mark(L, 8, s);
     hipLaunchKernelGGL(k_bin<true>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s, L.views, L.nviews,
-                       L.ctr, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins);
+                       L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins);
     mark(L, 9, s);
     for (int k = 0; k < L.nraster; ++k) {
         const RasterLaunch &R = L.raster[k];
