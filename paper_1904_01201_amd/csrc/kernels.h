@@ -31,6 +31,13 @@ struct RasterLaunch {
     uint2 *partial;            // [item_cap][TS*TS] per-pixel (1/w bits, key) of each item
 };
 
+// A descriptor block small enough (four views or so) to go to the device as an
+// argument of the direct path's first kernel.
+constexpr uint32_t kInlineDesc = 2048;
+struct alignas(16) InlineDesc {
+    uint8_t bytes[kInlineDesc];
+};
+
 // Device pointers and sizes of one launch sequence.
 struct LaunchPlan {
     const DView *views;
@@ -63,6 +70,8 @@ struct LaunchPlan {
     uint32_t tile_edge;        // 16, 32 or 64
     uint32_t shares;           // blocks that share a tile's clusters (1: the block shades it)
     uint32_t tile_grid;        // tile blocks
+    uint32_t desc_bytes;       // of the descriptor block, a multiple of 256
+    const InlineDesc *desc;    // the descriptor block, if its first kernel writes it (else null: it was copied)
     hipEvent_t *prof;          // null, or kProfEvents events recorded around the kernels
     uint32_t prof_mask;        // phases whose start/stop events are recorded
 };

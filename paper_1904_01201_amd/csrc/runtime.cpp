@@ -685,6 +685,29 @@ Footprint footprint(const ViewReq *v, uint32_t n, const PlanOpts &o, hab_context
 }
 
 // ---------------------------------------------------------------- launching
+// The descriptor block (in ws.desc) on its way to the arena: into `desc`, which
+// the direct path's first kernel takes as an argument, or through a pinned slot
+// and a copy on stream s.
+static hab_status stage(Workspace &ws, Plan &plan, void *arena, hipStream_t s, bool reserved, InlineDesc &desc)
+{
+    if (plan.L.direct && plan.desc_bytes <= kInlineDesc) {
+        std::memcpy(desc.bytes, ws.desc.data(), plan.desc_bytes);
+        plan.L.desc = &desc;
+        plan.L.desc_bytes = (uint32_t)plan.desc_bytes;
+        return HAB_OK;
+    }
+    void *host;
+    int slot;
+    const hab_status st = reserved ? ws.staging_reserved(plan.desc_bytes, &host, &slot)
+                                   : ws.staging(plan.desc_bytes, &host, &slot);
+    if (st != HAB_OK) return st;
+    std::memcpy(host, ws.desc.data(), plan.desc_bytes);
+    HAB_HIP(hipMemcpyAsync(arena, host, plan.desc_bytes, hipMemcpyHostToDevice, s));
+    HAB_HIP(hipEventRecord(ws.slots[slot].ev, s));
+    ws.slots[slot].pending = true;
+    return HAB_OK;
+}
+
 hab_status render_views(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_t n,
                         const PlanOpts &opts, hipStream_t s, hab_view_stats *stats)
 {
@@ -697,14 +720,9 @@ hab_status render_views(hab_context *ctx, Workspace &ws, const ViewReq *v, uint3
     if (st != HAB_OK) return st;
     if (reinterpret_cast<uintptr_t>(ws.arena) % 256) return HAB_ERR_DEVICE;   // a misplaced region: 64-bit atomics would fault
     if (ws.has_done && ws.last_stream != s) HAB_HIP(hipStreamWaitEvent(s, ws.done, 0));
-    void *host;
-    int slot;
-    st = ws.staging(plan.desc_bytes, &host, &slot);
+    InlineDesc desc;
+    st = stage(ws, plan, ws.arena, s, false, desc);
     if (st != HAB_OK) return st;
-    std::memcpy(host, ws.desc.data(), plan.desc_bytes);
-    HAB_HIP(hipMemcpyAsync(ws.arena, host, plan.desc_bytes, hipMemcpyHostToDevice, s));
-    HAB_HIP(hipEventRecord(ws.slots[slot].ev, s));
-    ws.slots[slot].pending = true;
     bind_plan(plan, ws.arena, ctx->err);
     hab_context::ProfSet *ps = nullptr;
     if (ctx->prof_on) {
@@ -743,15 +761,9 @@ hab_status render_views(hab_context *ctx, Workspace &ws, const ViewReq *v, uint3
 hab_status stage_and_launch(hab_context *ctx, Workspace &ws, Plan &plan, void *arena, hipStream_t s,
                             bool reserved)
 {
-    void *host;
-    int slot;
-    hab_status st = reserved ? ws.staging_reserved(plan.desc_bytes, &host, &slot)
-                             : ws.staging(plan.desc_bytes, &host, &slot);
+    InlineDesc desc;
+    const hab_status st = stage(ws, plan, arena, s, reserved, desc);
     if (st != HAB_OK) return st;
-    std::memcpy(host, ws.desc.data(), plan.desc_bytes);
-    HAB_HIP(hipMemcpyAsync(arena, host, plan.desc_bytes, hipMemcpyHostToDevice, s));
-    HAB_HIP(hipEventRecord(ws.slots[slot].ev, s));
-    ws.slots[slot].pending = true;
     bind_plan(plan, arena, ctx->err);
     HAB_HIP(launch_render(plan.L, s));
     return HAB_OK;
