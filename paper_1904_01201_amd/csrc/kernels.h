@@ -9,7 +9,14 @@ namespace habmi {
 
 constexpr uint32_t kMaxViews = 4096;   // views per launch sequence
 constexpr uint32_t kSegPerTile = 4;    // a work item covers <= 4 * TS^2 list entries
-constexpr uint32_t kWaveSeg = 256;      // list entries of a work item of k_raster_wave
+// List entries of a work item of k_raster_wave, by the launch's 16-pixel tiles.
+// A wave takes about 7 us for 64 entries while it shares its SIMD with five
+// others, so the launch ends on waves with a whole item left; but each item of
+// a tile with several merges 256 keys.  Items of 256 -> of 128: eight 512 x 384
+// views (6144 tiles) rasterise in 108 -> 96 us, 32 and 64 views of 256 x 256
+// in 101 -> 90 and 170 -> 165, 256 mixed views (two launches of 57 k tiles) take
+// 1112 -> 1123; items of 64 take 110 to 150 % of the time.
+constexpr uint32_t kWaveSeg = 128, kWaveSegLarge = 256, kWaveManyTiles = 32768;
 constexpr int kWaveWavesPerSimd = 6;    // its register budget
 constexpr uint32_t kMaxSegments = 1u << 14;
 
@@ -58,7 +65,8 @@ struct LaunchPlan {
     uint2 *items[3];           // per tile size (null when unused)
     uint32_t *err;
     uint32_t bin_grid;
-    bool wave16;               // 16-pixel tiles go to k_raster_wave, their z-keys to zbuf
+    uint32_t wave_seg;         // 16-pixel tiles go to k_raster_wave, this many entries an item, their
+                               //   z-keys to zbuf (0: to k_raster)
     RasterLaunch raster[3];
     int nraster;
     // direct path (draw.hip): drawn without tile lists when `direct`

@@ -638,21 +638,21 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     }
 }
 
-// List entries of one work item: kSegPerTile * TS^2, or kWaveSeg where a wave
-// rasterises a 16-pixel tile by itself (k_raster_wave).
-__device__ __forceinline__ uint32_t seg_size(uint32_t ts_log2, bool wave16)
+// List entries of one work item: kSegPerTile * TS^2, or wave_seg (if not 0) where
+// a wave rasterises a 16-pixel tile by itself (k_raster_wave).
+__device__ __forceinline__ uint32_t seg_size(uint32_t ts_log2, uint32_t wave_seg)
 {
-    return wave16 && ts_log2 == 4 ? kWaveSeg : kSegPerTile << (2 * ts_log2);
+    return wave_seg && ts_log2 == 4 ? wave_seg : kSegPerTile << (2 * ts_log2);
 }
 
 // Number of (tile, segment) work items of a tile: none when empty, one for
 // an overflow tile (it scans the whole survivor list), else one per
 // segment of at most seg_size list entries.
-__device__ __forceinline__ uint32_t tile_segments(uint32_t c, uint32_t off, uint32_t ts_log2, bool wave16)
+__device__ __forceinline__ uint32_t tile_segments(uint32_t c, uint32_t off, uint32_t ts_log2, uint32_t wave_seg)
 {
     if (c == 0) return 0;
     if (off == kOverflow) return 1;
-    const uint32_t S = seg_size(ts_log2, wave16);
+    const uint32_t S = seg_size(ts_log2, wave_seg);
     return (c + S - 1) / S;
 }
 
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(kScanBlock) void k_bin_scan(const DView *__restrict
                                                          DQueue *__restrict__ q,
                                                          uint2 *__restrict__ items8,
                                                          uint2 *__restrict__ items16,
-                                                         uint2 *__restrict__ items32, bool wave16,
+                                                         uint2 *__restrict__ items32, uint32_t wave_seg,
                                                          unsigned long long *__restrict__ zt)
 {
     __shared__ uint32_t wtot[kScanBlock / 64];
@@ -695,9 +695,9 @@ __global__ __launch_bounds__(kScanBlock) void k_bin_scan(const DView *__restrict
         // a tile with more segments than the item encoding holds also takes
         // the (single-item) overflow path
         const bool over = c > v.tile_cap || P + e > v.bin_cap ||
-                          c > (kMaxSegments - 1) * seg_size(v.ts_log2, wave16);
+                          c > (kMaxSegments - 1) * seg_size(v.ts_log2, wave_seg);
         const uint32_t off = (c == 0) ? 0u : (over ? kOverflow : (uint32_t)P);
-        const uint32_t ns = tile_segments(c, off, v.ts_log2, wave16);
+        const uint32_t ns = tile_segments(c, off, v.ts_log2, wave_seg);
         uint32_t stot;
         const uint32_t sex = block_excl_scan<kScanBlock>(ns, wtot, &stot);
         if (i < n) {
@@ -716,17 +716,17 @@ __global__ __launch_bounds__(kScanBlock) void k_bin_scan(const DView *__restrict
     uint2 *items = cls == 0 ? items8 : cls == 1 ? items16 : items32;
     for (uint32_t i = threadIdx.x; i < n; i += kScanBlock) {
         const uint32_t c = tile_count[v.tile_base + i];
-        const uint32_t ns = tile_segments(c, tile_off[v.tile_base + i], v.ts_log2, wave16);
+        const uint32_t ns = tile_segments(c, tile_off[v.tile_base + i], v.ts_log2, wave_seg);
         const uint32_t first = qb + tile_item[v.tile_base + i];
         tile_item[v.tile_base + i] = first;
         for (uint32_t sgm = 0; sgm < ns; ++sgm) items[first + sgm] = make_uint2(vi, i | (sgm << 18));
     }
-    if (!(wave16 && cls == 1)) return;
+    if (!wave_seg || cls != 1) return;
     // the tiles whose segments merge by atomic max start from cleared keys
     for (uint32_t base = 0; base < n; base += kScanBlock) {
         const uint32_t i = base + threadIdx.x;
         const uint32_t c = i < n ? tile_count[v.tile_base + i] : 0u;
-        unsigned long long m = __ballot(i < n && tile_segments(c, tile_off[v.tile_base + i], v.ts_log2, wave16) > 1);
+        unsigned long long m = __ballot(i < n && tile_segments(c, tile_off[v.tile_base + i], v.ts_log2, wave_seg) > 1);
         for (; m; m &= m - 1) {
             const uint32_t tile = base + (threadIdx.x & ~63u) + (uint32_t)__ffsll((long long)m) - 1u;
             uint4 *z = reinterpret_cast<uint4 *>(zt + wave_tile(v, tile));
@@ -1046,7 +1046,7 @@ __device__ __forceinline__ long long join64(int hi, int lo)
 constexpr uint32_t kWavePairs = 512;   // (record, block) pairs listed at once: eight blocks a record
 
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPerSimd))) void k_raster_wave(
-    const DView *__restrict__ views, const uint2 *__restrict__ items, DQueue *__restrict__ q,
+    const DView *__restrict__ views, const uint2 *__restrict__ items, uint32_t seg, DQueue *__restrict__ q,
     DViewCounters *__restrict__ ctr, const uint32_t *__restrict__ vis_clusters, const uint32_t *__restrict__ skey,
     const uint2 *__restrict__ sbox, const uint32_t *__restrict__ tile_count, const uint32_t *__restrict__ tile_off, const uint32_t *__restrict__ bins,
     unsigned long long *__restrict__ zt, uint32_t *__restrict__ err)
@@ -1082,8 +1082,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPe
         const uint32_t cnt = uniform(tile_count[v.tile_base + tile]);
         const uint32_t off = uniform(tile_off[v.tile_base + tile]);
         const bool over = off == kOverflow;
-        const uint32_t begin = over ? 0u : sgm * kWaveSeg;
-        const uint32_t end = over ? (uniform(visible_clusters(ctr[vi])) + kRun - 1) / kRun * kSlots : min(begin + kWaveSeg, cnt);
+        const uint32_t begin = over ? 0u : sgm * seg;
+        const uint32_t end = over ? (uniform(visible_clusters(ctr[vi])) + kRun - 1) / kRun * kSlots : min(begin + seg, cnt);
         const uint32_t *list = bins + v.bin_base + (over ? 0u : off);
         uint4 *const z4 = reinterpret_cast<uint4 *>(zk);
         z4[lane] = make_uint4(0, 0, 0, 0);
@@ -1220,7 +1220,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPe
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         unsigned long long *const z = zt + wave_tile(v, tile);
-        if (over || cnt <= kWaveSeg) {
+        if (over || cnt <= seg) {
             uint4 *const zo = reinterpret_cast<uint4 *>(z);
             zo[lane] = z4[lane];
             zo[lane + 64] = z4[lane + 64];
@@ -1680,7 +1680,7 @@ __global__ __launch_bounds__(kBandThreads) void k_resolve(const DView *__restric
         const uint32_t tile = (uint32_t)(pj / TS) * v.tiles_x + (uint32_t)(pi / TS);
         const uint32_t sub = (uint32_t)(((pj % TS) / 8) * NS + (pi % TS) / 8);
         const uint32_t tglob = v.tile_base + tile;
-        const uint32_t ns = tile_segments(tile_count[tglob], tile_off[tglob], v.ts_log2, false);
+        const uint32_t ns = tile_segments(tile_count[tglob], tile_off[tglob], v.ts_log2, 0);
         const uint32_t first = tile_item[tglob];
         const uint32_t slot = sub * 64u + (uint32_t)((pj % 8) * 8 + (pi % 8));
         for (uint32_t s = 0; s < ns; ++s) {
@@ -1759,8 +1759,8 @@ template <int TS>
 static void launch_raster(const LaunchPlan &L, const RasterLaunch &R, hipStream_t s)
 {
     if (R.wave) {
-        hipLaunchKernelGGL(k_raster_wave, dim3(R.grid), dim3(64), 0, s, L.views, R.items, L.queue, L.ctr, L.pairs,
-                           L.skey, L.sbox, L.tile_count, L.tile_off, L.bins, L.zbuf, L.err);
+        hipLaunchKernelGGL(k_raster_wave, dim3(R.grid), dim3(64), 0, s, L.views, R.items, L.wave_seg, L.queue, L.ctr,
+                           L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.bins, L.zbuf, L.err);
         return;
     }
     if (R.lane_owned)
@@ -1828,7 +1828,7 @@ hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
     mark(L, 6, s);
     hipLaunchKernelGGL(k_bin_scan, dim3(L.nviews), dim3(kScanBlock), 0, s, L.views, L.ctr,
                        L.tile_count, L.tile_off, L.tile_item, L.queue, L.items[0], L.items[1],
-                       L.items[2], L.wave16, L.zbuf);
+                       L.items[2], L.wave_seg, L.zbuf);
     mark(L, 7, s);
     mark(L, 8, s);
     hipLaunchKernelGGL(k_bin<true>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s, L.views, L.nviews,

@@ -543,7 +543,7 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
     L = LaunchPlan{};
     L.nviews = n;
     L.direct = direct;
-    L.wave16 = wave16;
+    L.wave_seg = !wave16 ? 0 : wave_tiles < kWaveManyTiles ? kWaveSeg : kWaveSegLarge;
     std::vector<uint32_t> &tpre = ws.tpre;
     const int c0 = (int)dv[0].ts_log2 - 3;
     if (direct) {
