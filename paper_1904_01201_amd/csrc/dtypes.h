@@ -12,7 +12,6 @@ constexpr int kSetupWavesPerSimd = 6;         // setup's register budget; its gr
 constexpr int kBinBlock = 256;                // threads per block in count/scatter
 constexpr int kRun = 4;                       // visible clusters a setup wave takes at a time
 constexpr int kBinRuns = 8;                   // runs per block in count/scatter
-constexpr int kScanBlock = 1024;
 constexpr int kCluster = 64;                  // triangles per culling cluster (one wave)
 
 // Error bits of the sticky device error word.

@@ -468,6 +468,30 @@ __device__ __forceinline__ TileRange tile_range(uint2 bb, uint32_t ts)
     return r;
 }
 
+// List entries of one work item: kSegPerTile * TS^2, or wave_seg (if not 0) where
+// a wave rasterises a 16-pixel tile by itself (k_raster_wave).
+__device__ __forceinline__ uint32_t seg_size(uint32_t ts_log2, uint32_t wave_seg)
+{
+    return wave_seg && ts_log2 == 4 ? wave_seg : kSegPerTile << (2 * ts_log2);
+}
+
+// Number of (tile, segment) work items of a tile: none when empty, one for
+// an overflow tile (it scans the whole survivor list), else one per
+// segment of at most seg_size list entries.
+__device__ __forceinline__ uint32_t tile_segments(uint32_t c, uint32_t off, uint32_t ts_log2, uint32_t wave_seg)
+{
+    if (c == 0) return 0;
+    if (off == kOverflow) return 1;
+    const uint32_t S = seg_size(ts_log2, wave_seg);
+    return (c + S - 1) / S;
+}
+
+// First z-key of a view's 16-pixel tile (k_raster_wave): 256 keys per tile.
+__device__ __forceinline__ size_t wave_tile(const DView &v, uint32_t tile)
+{
+    return (((size_t)v.zoff_hi << 32) | v.zoff_lo) + 256u * (size_t)tile;
+}
+
 // Eight waves per SIMD (64 VGPRs in the scatter): 2048 blocks, the grid, are
 // resident; with 66 VGPRs a quarter of them ran after the others (1024 views'
 // scatter 47 us, 41 so).
@@ -480,7 +504,8 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
                                                    uint32_t *__restrict__ tile_count,
                                                    const uint32_t *__restrict__ tile_off,
                                                    uint32_t *__restrict__ tile_cursor,
-                                                   uint32_t *__restrict__ bins)
+                                                   uint32_t *__restrict__ bins, uint32_t wave_seg,
+                                                   unsigned long long *__restrict__ zt)
 {
     extern __shared__ uint32_t pre[];      // [nviews]: sized at launch
     __shared__ uint32_t hist[kLdsTiles];   // low 16 bits: count, high 16 bits: rank cursor
@@ -490,6 +515,27 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     uint32_t *const wtot = hist;
     const uint32_t total = build_prefix<kBinBlock>(ctr, nviews, kBinRuns * kRun, pre, wtot);
     const uint32_t tid = threadIdx.x;
+    if (SCATTER && wave_seg) {
+        // the 16-pixel tiles whose items merge by atomic max start from cleared
+        // keys: a share of each view's tiles per block, 16 tiles at a time per wave
+        const uint32_t shares = max(1u, gridDim.x / nviews), lane = lane_id();
+        for (uint32_t u = blockIdx.x; u < nviews * shares; u += gridDim.x) {
+            const DView &v = views[u / shares];
+            const uint32_t n = v.ts_log2 == 4 ? v.tiles_x * v.tiles_y : 0u;
+            for (uint32_t t0 = ((u % shares) * (kBinBlock / 64) + uniform(tid >> 6)) * 16u; t0 < n;
+                 t0 += shares * (kBinBlock / 64) * 16u) {
+                const uint32_t t = t0 + lane;
+                bool multi = false;
+                if (lane < 16u && t < n)
+                    multi = tile_segments(tile_count[v.tile_base + t], tile_off[v.tile_base + t], 4, wave_seg) > 1;
+                for (unsigned long long m = __ballot(multi); m; m &= m - 1) {
+                    uint4 *const z = reinterpret_cast<uint4 *>(zt + wave_tile(v, t0 + (uint32_t)__ffsll((long long)m) - 1u));
+                    z[lane] = make_uint4(0, 0, 0, 0);
+                    z[lane + 64] = make_uint4(0, 0, 0, 0);
+                }
+            }
+        }
+    }
     for (uint32_t item = blockIdx.x; item < total; item += gridDim.x) {
         const uint32_t vi = uniform(find_view(pre, nviews, item));
         const DView &v = views[vi];
@@ -638,36 +684,16 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     }
 }
 
-// List entries of one work item: kSegPerTile * TS^2, or wave_seg (if not 0) where
-// a wave rasterises a 16-pixel tile by itself (k_raster_wave).
-__device__ __forceinline__ uint32_t seg_size(uint32_t ts_log2, uint32_t wave_seg)
-{
-    return wave_seg && ts_log2 == 4 ? wave_seg : kSegPerTile << (2 * ts_log2);
-}
-
-// Number of (tile, segment) work items of a tile: none when empty, one for
-// an overflow tile (it scans the whole survivor list), else one per
-// segment of at most seg_size list entries.
-__device__ __forceinline__ uint32_t tile_segments(uint32_t c, uint32_t off, uint32_t ts_log2, uint32_t wave_seg)
-{
-    if (c == 0) return 0;
-    if (off == kOverflow) return 1;
-    const uint32_t S = seg_size(ts_log2, wave_seg);
-    return (c + S - 1) / S;
-}
-
-// First z-key of a view's 16-pixel tile (k_raster_wave): 256 keys per tile.
-__device__ __forceinline__ size_t wave_tile(const DView &v, uint32_t tile)
-{
-    return (((size_t)v.zoff_hi << 32) | v.zoff_lo) + 256u * (size_t)tile;
-}
-
 // Per view: exclusive scan of tile counts into list offsets.  A tile whose
 // count exceeds tile_cap, or whose list would end beyond the view's bin
 // capacity, is marked kOverflow.  Then the view's work items are reserved
 // in its tile size's queue and written out; tile_item gets each tile's
-// first item.
-__global__ __launch_bounds__(kScanBlock) void k_bin_scan(const DView *__restrict__ views,
+// first item.  A block per view, of 64 or 256 threads where no view has more
+// tiles (1024 views of 16 tiles: 22 us in blocks of 1024, 18 so); the tiles
+// whose items merge are cleared by the scatter's blocks, not by a view's one
+// (eight views of 768 tiles: 17 us, 9 without it).
+template <int NT>
+__global__ __launch_bounds__(NT) void k_bin_scan(const DView *__restrict__ views,
                                                          DViewCounters *__restrict__ ctr,
                                                          const uint32_t *__restrict__ tile_count,
                                                          uint32_t *__restrict__ tile_off,
@@ -675,22 +701,21 @@ __global__ __launch_bounds__(kScanBlock) void k_bin_scan(const DView *__restrict
                                                          DQueue *__restrict__ q,
                                                          uint2 *__restrict__ items8,
                                                          uint2 *__restrict__ items16,
-                                                         uint2 *__restrict__ items32, uint32_t wave_seg,
-                                                         unsigned long long *__restrict__ zt)
+                                                         uint2 *__restrict__ items32, uint32_t wave_seg)
 {
-    __shared__ uint32_t wtot[kScanBlock / 64];
+    __shared__ uint32_t wtot[NT / 64];
     __shared__ uint32_t sbase;
     const uint32_t vi = blockIdx.x;
     const DView &v = views[vi];
     const uint32_t n = v.tiles_x * v.tiles_y;
     const uint32_t cls = v.ts_log2 - 3;
     uint32_t run = 0, srun = 0;
-    for (uint32_t base = 0; base < n; base += kScanBlock) {
+    for (uint32_t base = 0; base < n; base += NT) {
         const uint32_t i = base + threadIdx.x;
         const uint32_t c = i < n ? tile_count[v.tile_base + i] : 0u;
         const uint32_t e = c <= v.tile_cap ? c : 0u;
         uint32_t tot;
-        const uint32_t ex = block_excl_scan<kScanBlock>(e, wtot, &tot);
+        const uint32_t ex = block_excl_scan<NT>(e, wtot, &tot);
         const unsigned long long P = (unsigned long long)run + ex;
         // a tile with more segments than the item encoding holds also takes
         // the (single-item) overflow path
@@ -699,7 +724,7 @@ __global__ __launch_bounds__(kScanBlock) void k_bin_scan(const DView *__restrict
         const uint32_t off = (c == 0) ? 0u : (over ? kOverflow : (uint32_t)P);
         const uint32_t ns = tile_segments(c, off, v.ts_log2, wave_seg);
         uint32_t stot;
-        const uint32_t sex = block_excl_scan<kScanBlock>(ns, wtot, &stot);
+        const uint32_t sex = block_excl_scan<NT>(ns, wtot, &stot);
         if (i < n) {
             tile_off[v.tile_base + i] = off;
             tile_item[v.tile_base + i] = srun + sex;
@@ -714,25 +739,12 @@ __global__ __launch_bounds__(kScanBlock) void k_bin_scan(const DView *__restrict
     __syncthreads();
     const uint32_t qb = sbase;
     uint2 *items = cls == 0 ? items8 : cls == 1 ? items16 : items32;
-    for (uint32_t i = threadIdx.x; i < n; i += kScanBlock) {
+    for (uint32_t i = threadIdx.x; i < n; i += NT) {
         const uint32_t c = tile_count[v.tile_base + i];
         const uint32_t ns = tile_segments(c, tile_off[v.tile_base + i], v.ts_log2, wave_seg);
         const uint32_t first = qb + tile_item[v.tile_base + i];
         tile_item[v.tile_base + i] = first;
         for (uint32_t sgm = 0; sgm < ns; ++sgm) items[first + sgm] = make_uint2(vi, i | (sgm << 18));
-    }
-    if (!wave_seg || cls != 1) return;
-    // the tiles whose segments merge by atomic max start from cleared keys
-    for (uint32_t base = 0; base < n; base += kScanBlock) {
-        const uint32_t i = base + threadIdx.x;
-        const uint32_t c = i < n ? tile_count[v.tile_base + i] : 0u;
-        unsigned long long m = __ballot(i < n && tile_segments(c, tile_off[v.tile_base + i], v.ts_log2, wave_seg) > 1);
-        for (; m; m &= m - 1) {
-            const uint32_t tile = base + (threadIdx.x & ~63u) + (uint32_t)__ffsll((long long)m) - 1u;
-            uint4 *z = reinterpret_cast<uint4 *>(zt + wave_tile(v, tile));
-            z[lane_id()] = make_uint4(0, 0, 0, 0);
-            z[lane_id() + 64] = make_uint4(0, 0, 0, 0);
-        }
     }
 }
 
@@ -1823,16 +1835,17 @@ hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
     mark(L, 3, s);
     mark(L, 4, s);
     hipLaunchKernelGGL(k_bin<false>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s, L.views, L.nviews,
-                       L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins);
+                       L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins, L.wave_seg, L.zbuf);
     mark(L, 5, s);
     mark(L, 6, s);
-    hipLaunchKernelGGL(k_bin_scan, dim3(L.nviews), dim3(kScanBlock), 0, s, L.views, L.ctr,
-                       L.tile_count, L.tile_off, L.tile_item, L.queue, L.items[0], L.items[1],
-                       L.items[2], L.wave_seg, L.zbuf);
+    const uint32_t nt = L.max_tiles <= 64 ? 64 : L.max_tiles <= 256 ? 256 : 1024;
+    auto *const scan = nt == 64 ? k_bin_scan<64> : nt == 256 ? k_bin_scan<256> : k_bin_scan<1024>;
+    hipLaunchKernelGGL(scan, dim3(L.nviews), dim3(nt), 0, s, L.views, L.ctr, L.tile_count, L.tile_off, L.tile_item,
+                       L.queue, L.items[0], L.items[1], L.items[2], L.wave_seg);
     mark(L, 7, s);
     mark(L, 8, s);
     hipLaunchKernelGGL(k_bin<true>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s, L.views, L.nviews,
-                       L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins);
+                       L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins, L.wave_seg, L.zbuf);
     mark(L, 9, s);
     for (int k = 0; k < L.nraster; ++k) {
         const RasterLaunch &R = L.raster[k];

@@ -602,6 +602,7 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
     L.setup_grid = (uint32_t)std::max<uint64_t>(
         1, std::min<uint64_t>((npairs + 15) / 16, setup_resident * (ctx ? ctx->cu_count : 256)));
     L.ntiles = (uint32_t)tile_total;
+    for (uint32_t k = 0; k < n; ++k) L.max_tiles = std::max(L.max_tiles, dv[k].tiles_x * dv[k].tiles_y);
     uint64_t ub = 0;
     for (uint32_t k = 0; k < n; ++k) ub += cdiv(dv[k].T, kCluster * kRun * kBinRuns);
     L.bin_grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(ub, 8ull * (ctx ? ctx->cu_count : 256)));
