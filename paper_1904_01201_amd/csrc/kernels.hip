@@ -175,29 +175,23 @@ __device__ __forceinline__ void survive(const DView &v, const float P[9], bool v
     const bool allin = c0.w >= zn && c1.w >= zn && c2.w >= zn;
     const bool anyin = c0.w >= zn || c1.w >= zn || c2.w >= zn;
     if (!anyin) return;
-    if (allin) {
-        // Conservative frustum rejection before any division: if all three
-        // |Xc fS| exceed (cxS + 4 px)(1 + 2^-16) w on one side, the snapped
-        // bbox is at least 3 px outside the viewport (three fp32 roundings
-        // cost < 2^-22 relative), so the exact path would cull it too.
-        const float Kx = (v.cxS + 1024.0f) * 1.0000152587890625f;
-        const float Ky = (v.cyS + 1024.0f) * 1.0000152587890625f;
-        const float x0 = c0.x * v.fS, x1 = c1.x * v.fS, x2 = c2.x * v.fS;
-        const float y0 = c0.y * v.fS, y1 = c1.y * v.fS, y2 = c2.y * v.fS;
-        const float kx0 = Kx * c0.w, kx1 = Kx * c1.w, kx2 = Kx * c2.w;
-        const float ky0 = Ky * c0.w, ky1 = Ky * c1.w, ky2 = Ky * c2.w;
-        if ((x0 > kx0 && x1 > kx1 && x2 > kx2) || (x0 < -kx0 && x1 < -kx1 && x2 < -kx2) ||
-            (y0 > ky0 && y1 > ky1 && y2 > ky2) || (y0 < -ky0 && y1 < -ky1 && y2 < -ky2))
-            return;
-    }
     SVtx<0> a, bb, c;
     if (allin) {
         // no clipping and no second sub-triangle
-        bool ok = snap(v, c0, a);
-        ok &= snap(v, c1, bb);
-        ok &= snap(v, c2, c);
-        if (!ok) {
-            rerr = true;
+        if (!snap3<true>(v, c0, c1, c2, a, bb, c)) {
+            // Beyond the fixed-point domain, an error unless the triangle is
+            // out of sight anyway: all three |Xc fS| exceed (cxS + 4 px)
+            // (1 + 2^-16) w on one side, so the snapped bbox is at least 3 px
+            // outside the viewport (three fp32 roundings cost < 2^-22
+            // relative).
+            const float Kx = (v.cxS + 1024.0f) * 1.0000152587890625f;
+            const float Ky = (v.cyS + 1024.0f) * 1.0000152587890625f;
+            const float x0 = c0.x * v.fS, x1 = c1.x * v.fS, x2 = c2.x * v.fS;
+            const float y0 = c0.y * v.fS, y1 = c1.y * v.fS, y2 = c2.y * v.fS;
+            const float kx0 = Kx * c0.w, kx1 = Kx * c1.w, kx2 = Kx * c2.w;
+            const float ky0 = Ky * c0.w, ky1 = Ky * c1.w, ky2 = Ky * c2.w;
+            rerr |= !((x0 > kx0 && x1 > kx1 && x2 > kx2) || (x0 < -kx0 && x1 < -kx1 && x2 < -kx2) ||
+                      (y0 > ky0 && y1 > ky1 && y2 > ky2) || (y0 < -ky0 && y1 < -ky1 && y2 < -ky2));
             return;
         }
         b0 = pix_box(v, a, bb, c);
@@ -856,28 +850,15 @@ __device__ __forceinline__ bool edge_rec(const DView &v, uint32_t key, int ti0, 
     cam_xform(v, P[3], P[4], P[5], c1);
     cam_xform(v, P[6], P[7], P[8], c2);
     SVtx<0> a, b, c;
-    long long A;
-    if (c0.w >= v.zn && c1.w >= v.zn && c2.w >= v.zn) {
+    long long A = 0;
+    const bool front = c0.w >= v.zn && c1.w >= v.zn && c2.w >= v.zn;
+    if (front) {
         // all three vertices in front of the near plane (the common case):
         // clipping returns them unchanged and there is no second
         // sub-triangle, so this is the setup of sub-triangle 0 without the
-        // polygon bookkeeping
+        // polygon bookkeeping, which it survived
         if (sub != 0) return false;
-        bool ok = snap(v, c0, a);
-        ok &= snap(v, c1, b);
-        ok &= snap(v, c2, c);
-        if (!ok) {
-            rerr = true;
-            return false;
-        }
-        A = area2(a, b, c);
-        if (A == 0) return false;
-        if (A < 0) {
-            const SVtx<0> tmp = b;
-            b = c;
-            c = tmp;
-            A = -A;
-        }
+        (void)snap3<false>(v, c0, c1, c2, a, b, c);
     } else if (!setup_sub(v, c0, c1, c2, sub, a, b, c, A, rerr)) {
         return false;
     }
@@ -887,6 +868,28 @@ __device__ __forceinline__ bool edge_rec(const DView &v, uint32_t key, int ti0, 
     box[2] = max(pb.j0 - tj0, 0);
     box[3] = min(pb.j1 - tj0, TS - 1);
     if (box[0] > box[1] || box[2] > box[3]) return false;
+    // the tile's first pixel centre, and whether every vertex lies within 64 px
+    // of it (|X| < 2^29: differences fit int32)
+    const int Ox = 256 * ti0 + 128, Oy = 256 * tj0 + 128;
+    constexpr int kNear = 1 << 14;
+    const bool small = abs(a.X - Ox) < kNear && abs(b.X - Ox) < kNear && abs(c.X - Ox) < kNear &&
+                       abs(a.Y - Oy) < kNear && abs(b.Y - Oy) < kNear && abs(c.Y - Oy) < kNear;
+    // twice the area, made positive by the order of b and c (a clipped piece
+    // comes oriented); its float has the same rounding from either width
+    float fA;
+    if (small) {
+        const int A32 = __mul24(b.X - a.X, c.Y - a.Y) - __mul24(b.Y - a.Y, c.X - a.X);   // |.| < 2^31
+        fA = (float)A32;
+    } else {
+        if (front) A = area2(a, b, c);
+        fA = (float)A;
+    }
+    if (fA < 0.0f) {
+        const SVtx<0> tmp = b;
+        b = c;
+        c = tmp;
+        fA = -fA;
+    }
     // edge k runs from vertex k+1 to vertex k+2
     dx[0] = c.X - b.X;
     dx[1] = a.X - c.X;
@@ -904,15 +907,11 @@ __device__ __forceinline__ bool edge_rec(const DView &v, uint32_t key, int ti0, 
     int clo[3], chi[3];
     bool fast = true;
     packed = true;
-    // edge start points relative to that centre (|X| < 2^29: fits int32)
-    const int Ox = 256 * ti0 + 128, Oy = 256 * tj0 + 128;
+    // edge start points relative to that centre
     const int rx[3] = {ax[0] - Ox, ax[1] - Ox, ax[2] - Ox};
     const int ry[3] = {ay[0] - Oy, ay[1] - Oy, ay[2] - Oy};
-    constexpr int kNear = 1 << 14;
-    const bool small = abs(rx[0]) < kNear && abs(rx[1]) < kNear && abs(rx[2]) < kNear && abs(ry[0]) < kNear &&
-                       abs(ry[1]) < kNear && abs(ry[2]) < kNear;
     if (small) {
-        // every vertex within 64 px of the tile: |d| < 2^15, 24-bit products,
+        // |d| < 2^15, 24-bit products,
         // |C| < 2^30, every pixel value of the tile < 2^31 in magnitude:
         // the packed form, without 64-bit arithmetic
 #pragma unroll
@@ -964,11 +963,6 @@ __device__ __forceinline__ bool edge_rec(const DView &v, uint32_t key, int ti0, 
     x.ny0 = -dy[0];
     x.ny1 = -dy[1];
     x.ny2 = -dy[2];
-    // (float)A: from int32 when A fits (always for small records), which is
-    // the same rounding as the int64 conversion
-    float fA;
-    if (A == (long long)(int)A) fA = (float)(int)A;
-    else fA = (float)A;
     r.invA = recip_rn(fA);
     r.rw0 = a.rw;
     r.rw1 = b.rw;

@@ -30,12 +30,14 @@ constexpr float kDomain = 536870912.0f;   // 2^29: |X|, |Y| bound in 1/256 px
 // launch_check_recip); elsewhere the division itself.
 constexpr uint32_t kRecipLo = 0x00800000u;   // 2^-126
 constexpr uint32_t kRecipHi = 0x7E800000u;   // 2^126
+__device__ __forceinline__ float recip_mid(float x)
+{
+    const float y = __builtin_amdgcn_rcpf(x);
+    return __builtin_fmaf(__builtin_fmaf(-x, y, 1.0f), y, y);
+}
 __device__ __forceinline__ float recip_rn(float x)
 {
-    if (__builtin_expect(__float_as_uint(x) - kRecipLo < kRecipHi - kRecipLo, 1)) {
-        const float y = __builtin_amdgcn_rcpf(x);
-        return __builtin_fmaf(__builtin_fmaf(-x, y, 1.0f), y, y);
-    }
+    if (__builtin_expect(__float_as_uint(x) - kRecipLo < kRecipHi - kRecipLo, 1)) return recip_mid(x);
     return 1.0f / x;
 }
 
@@ -120,6 +122,38 @@ __device__ __forceinline__ bool snap(const DView &v, const Vtx<NA> &c, SVtx<NA> 
     s.rw = rw;
 #pragma unroll
     for (int k = 0; k < NA; ++k) s.a[k] = c.a[k];
+    return ok;
+}
+
+// snap of three vertices in front of the near plane, the reciprocals' range
+// looked at once.  CHECK false: of a triangle known to lie in the domain (its
+// setup survived).
+template <bool CHECK>
+__device__ __forceinline__ bool snap3(const DView &v, const Vtx<0> &c0, const Vtx<0> &c1, const Vtx<0> &c2, SVtx<0> &a,
+                                      SVtx<0> &b, SVtx<0> &c)
+{
+    const uint32_t u0 = __float_as_uint(c0.w), u1 = __float_as_uint(c1.w), u2 = __float_as_uint(c2.w);
+    if (__builtin_expect(min(u0, min(u1, u2)) >= kRecipLo && max(u0, max(u1, u2)) < kRecipHi, 1)) {
+        a.rw = recip_mid(c0.w);
+        b.rw = recip_mid(c1.w);
+        c.rw = recip_mid(c2.w);
+    } else {
+        a.rw = recip_rn(c0.w);
+        b.rw = recip_rn(c1.w);
+        c.rw = recip_rn(c2.w);
+    }
+    bool ok = true;
+    auto place = [&](const Vtx<0> &q, SVtx<0> &s) {
+        const float xs = rintf(v.cxS + (q.x * v.fS) * s.rw);
+        const float ys = rintf(v.cyS - (q.y * v.fS) * s.rw);
+        const bool in = !CHECK || (fabsf(xs) < kDomain && fabsf(ys) < kDomain);
+        s.X = in ? (int)xs : 0;
+        s.Y = in ? (int)ys : 0;
+        ok &= in;
+    };
+    place(c0, a);
+    place(c1, b);
+    place(c2, c);
     return ok;
 }
 
