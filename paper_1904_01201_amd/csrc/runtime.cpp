@@ -11,9 +11,9 @@ namespace habmi {
 
 static constexpr float kDefaultBinFactor = 2.0f;
 static constexpr uint32_t kDefaultTile = 16;
-// Pixels + triangles / 8 up to which the direct path draws a launch, and a
+// Pixels + triangles / 4 up to which the direct path draws a launch, and a
 // half of a split batch.
-static constexpr uint64_t kDirectSize = 1200 * 1024, kDirectHalf = 640 * 1024;
+static constexpr uint64_t kDirectSize = 1150 * 1024, kDirectHalf = 740 * 1024;
 // Resolve waves that a launch keeps when a wave shades two or four bands one
 // after another (its search and start paid once): two rounds of the 8192 that
 // are resident.  1024 depth frames of 64 x 64 resolve in 32 us with one band a
@@ -328,17 +328,20 @@ static inline uint32_t ts_log2(uint32_t ts) { return ts == 8 ? 3u : ts == 16 ? 4
 // lane-owned z-test, work counters), while they are small: the tile lists
 // take eight dependent kernels whatever the size, the direct path four, but it
 // sets up a triangle once per tile its cluster meets.  Measured (us a launch,
-// tile lists against direct): one 128 x 128 view of 2k triangles 58 / 37, one
-// 256 x 256 view of 200k 105 / 56, of 1M 133 / 67, four of 1M 161 / 140, eight
-// of 200k 113 / 108, eight 512 x 384 views of 1M 296 / 348.  The two halves of
-// a split batch overlap, which helps the tile lists more: 40 views of 128 x 128
-// over 75k triangles 144 / 133, 100 of 96 x 72 161 / 215.
+// tile lists against direct, by pixels + triangles / 4 in K): one 256 x 256 view
+// of 200k triangles 89 / 49 (113), of 1M 93 / 61 (308), two of 1M 88 / 65 (616),
+// 20 of 203 x 117 over 60k 103 / 87 (757), eight of 256 x 256 over 200k 109 / 106
+// (902), 16 over 20k 118 / 113 (1102), four of 1M 119 / 133 (1232), three 512 x
+// 384 views of 1M 122 / 156 (1308), eight 128 x 96 of 1M 121 / 125 (2049).  The
+// two halves of a split batch overlap, which helps the tile lists more (size of a
+// half): 100 views of 64 x 64 over 20k 140 / 113 (439), 40 of 128 x 128 over 75k
+// 139 / 130 (686), 64 of 96 x 72 over 75k 138 / 154 (802).
 static bool direct_launch(const ViewReq *v, uint32_t n, const PlanOpts &o)
 {
     if (o.tile_lists || o.tile_size || o.bin_factor > 0.0f || o.tile_cap || o.lane_owned_z || o.count_work) return false;
     uint64_t size = 0;
     for (uint32_t k = 0; k < n; ++k)
-        size += (uint64_t)v[k].sensor.width * v[k].sensor.height + v[k].scene->T / 8;
+        size += (uint64_t)v[k].sensor.width * v[k].sensor.height + v[k].scene->T / 4;
     return size <= (o.half ? kDirectHalf : kDirectSize);
 }
 
