@@ -177,7 +177,7 @@ typedef struct {
  * without tile lists, in about half the time; a tile size, bin factor, tile
  * cap or HAB_RENDER_LANE_OWNED_Z always takes the tile lists.
  *
- * A batch of 32 or more views is rendered as two launch sequences over
+ * A large batch of 32 or more views is rendered as two launch sequences over
  * interleaved halves (views 0, 2, 4, ... and 1, 3, 5, ...): one on the
  * caller's stream, one on a second stream of the context that waits for the
  * caller's stream first, and the caller's stream then waits for it, so the

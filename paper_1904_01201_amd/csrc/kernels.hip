@@ -1044,11 +1044,12 @@ __device__ __forceinline__ long long join64(int hi, int lo)
 // Records whose edges do not fit the packed form (a vertex far from the tile)
 // are tested one after another by the whole wave.
 //
-// Bound by VALU issue (about 80% busy): 99 M wave instructions for the 64 bench
-// views, 885 per 64 list entries, half of them rebuilding the entries' setup;
-// 0.203 ms alone, against 0.222 ms with 8-pixel tiles (112 M) and 0.289 ms with
-// a 256-thread block per 16-pixel tile; eight 512 x 384 views of 1M triangles
-// 0.111 ms (0.156 ms in blocks).
+// Bound by VALU issue, half of it rebuilding the entries' setup: 76 M wave
+// instructions for the 64 bench views (99 M before the setup dropped triangles
+// that cover no pixel), 65 % busy in a launch of half of them, which ends short
+// of waves.  0.146 ms alone for the 64 views; with the same lists 8-pixel tiles
+// took 0.222 where this took 0.203, a 256-thread block per 16-pixel tile 0.289;
+// eight 512 x 384 views of 1M triangles 0.096 ms (0.156 ms in blocks).
 constexpr uint32_t kWavePairs = 512;   // (record, block) pairs listed at once: eight blocks a record
 
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPerSimd))) void k_raster_wave(

@@ -805,10 +805,31 @@ hab_status ensure_aux(hab_context *ctx)
     return HAB_OK;
 }
 
+// Measured (us a launch; one sequence, two), back to back and with a wait after
+// each, by pixels + triangles / 4 in millions: 256 views of 64 x 64 over 20k
+// triangles (2.3) 141 / 174 and 180 / 247; 64 of 100 x 80 over 50k to 400k (3.4)
+// 142 / 156 and 173 / 221; 32 of 256 x 256 over 100k to 1M (6) 198 / 205 and
+// 227 / 278; 64 of 160 x 160 over 100k to 800k (7) 239 / 239 and 271 / 307; the
+// same 48 of 256 x 256 (9) 279 / 270 and 309 / 341, 64 (12) 374 / 354 and 403 /
+// 413, 128 (24) 601 / 580 and 634 / 586.  With more views the chain of small
+// kernels grows: 120 of 96 x 72 (3.8) 177 / 172 and 208 / 253, 100 of 100 x 80
+// (5.3) 190 / 178 and 219 / 264, 128 of 64 x 64 over 60k (2.4) 135 / 139.
+bool split_batch(const ViewReq *v, uint32_t n)
+{
+    constexpr uint64_t kSplitSize = 8192 * 1024, kSplitManySize = 3072 * 1024;
+    constexpr uint32_t kSplitMany = 80, kSplitAlways = 1024;
+    if (n < kSplitViews) return false;
+    if (n > kSplitAlways) return true;
+    uint64_t size = 0;
+    for (uint32_t k = 0; k < n; ++k)
+        size += (uint64_t)v[k].sensor.width * v[k].sensor.height + v[k].scene->T / 4;
+    return size >= (n > kSplitMany ? kSplitManySize : kSplitSize);
+}
+
 hab_status render_split(hab_context *ctx, const ViewReq *v, uint32_t n, const PlanOpts &o, hipStream_t s,
                         hab_view_stats *stats)
 {
-    if (n < kSplitViews || o.one_sequence) return render_all(ctx, ctx->ws, v, n, o, s, stats);
+    if (o.one_sequence || !split_batch(v, n)) return render_all(ctx, ctx->ws, v, n, o, s, stats);
     hab_status st = ensure_aux(ctx);
     if (st != HAB_OK) return st;
     // views 0, 2, 4, ... and 1, 3, 5, ...: halves of like composition

@@ -158,11 +158,12 @@ struct Plan {
     uint32_t n = 0;
 };
 
-// Batches of at least this many views render as two interleaved halves,
-// each its own launch sequence, on the caller's stream and a second stream
-// of the context: the halves' kernels overlap, so one half's low-occupancy
-// phases (the setup's tail, binning) run beside the other's raster.
-constexpr uint32_t kSplitViews = 32;
+// Does a batch render as two interleaved halves, each its own launch sequence,
+// on the caller's stream and a second stream of the context?  The halves'
+// kernels overlap, so one half's latency-bound phases run beside the other's
+// raster, but they take twice the launches, each half as well filled.
+constexpr uint32_t kSplitViews = 32;   // never below
+bool split_batch(const ViewReq *v, uint32_t n);
 
 struct Tuned {
     uint32_t key;
@@ -251,8 +252,8 @@ void autotune_cache_load(hab_context *ctx);
 // them all.
 hab_status render_all(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_t n,
                       const PlanOpts &o, hipStream_t s, hab_view_stats *stats);
-// render_all on the context's workspace; a batch of kSplitViews or more
-// views as two interleaved halves on s and the context's second stream
+// render_all on the context's workspace; a batch that split_batch splits
+// as two interleaved halves on s and the context's second stream
 // (joined back into s before returning).
 hab_status render_split(hab_context *ctx, const ViewReq *v, uint32_t n, const PlanOpts &o, hipStream_t s,
                         hab_view_stats *stats);

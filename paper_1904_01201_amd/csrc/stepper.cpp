@@ -3,7 +3,7 @@
 // upload + the whole kernel sequence).  Each step only rewrites the poses in
 // pinned host memory and replays the graph.  Two descriptor buffers and two
 // graph instances alternate so the host can stage step k+1 while step k
-// runs.  A batch of kSplitViews or more views is planned as two interleaved
+// runs.  A batch that split_batch splits is planned as two interleaved
 // halves whose launch sequences the graph runs side by side (a fork to a
 // second capture stream and a join back), as the eager path does.
 #include <cstring>
@@ -119,13 +119,16 @@ hab_status hab_stepper_create(hab_context *ctx, const hab_view *views, uint32_t 
         st->ctx = ctx;
         st->device = ctx->device;
         st->n = n;
-        st->nh = n >= kSplitViews && !(opts && (opts->flags & HAB_RENDER_ONE_SEQUENCE)) ? 2 : 1;
         hab_status s = HAB_OK;
+        std::vector<ViewReq> req(n);
+        for (uint32_t k = 0; k < n && s == HAB_OK; ++k) s = to_view_req(views[k], req[k]);
+        // (a list capacity may be asked for that only fits the limits by halves)
+        const bool halves = n >= kSplitViews && opts && opts->bin_factor > 0.0f;
+        st->nh = s == HAB_OK && !(opts && (opts->flags & HAB_RENDER_ONE_SEQUENCE)) && (halves || split_batch(req.data(), n)) ? 2 : 1;
         for (uint32_t k = 0; k < n && s == HAB_OK; ++k) {
             StepHalf &h = st->half[st->nh == 2 ? k & 1u : 0u];
-            h.req.emplace_back();
+            h.req.push_back(req[k]);
             h.idx.push_back(k);
-            s = to_view_req(views[k], h.req.back());
         }
         PlanOpts o;
         o.half = st->nh == 2;

@@ -289,7 +289,7 @@ class Context:
     def render_batch(self, items, tile_size=0, bin_factor=0.0, tile_cap=0, stats=False, stream=None,
                      views=None, one_sequence=False, lane_owned_z=False):
         """Render a list of views (or prepared hab_view records, `views`).
-        32 or more views run as two launch sequences side by side unless
+        Large batches of 32 or more views run as two launch sequences side by side unless
         one_sequence; lane_owned_z selects the atomic-free lane-owned
         z-test (same outputs)."""
         arr = views if views is not None else self.make_views(items)
