@@ -543,7 +543,7 @@ def main():
     assert ctx.get_error() == 0
 
     # ---------------------------------------------------- roofline
-    # A step of 32 views or more is two launch sequences (halves of the
+    # A step as large as this one is two launch sequences (halves of the
     # batch) that run side by side: per-launch times are each half's own
     # kernel durations, and the work of one launch is half a step's.
     per_launch = {k: v["ms"] / max(v["launches"], 1) for k, v in phases.items()}
@@ -562,8 +562,8 @@ def main():
     if dom == "raster":
         ops = (OPS_PER_TEST * bbox_tests + OPS_PER_COVERED * covered) / lps[dom]
         ach = ops / (per_launch[dom] * 1e-3) / 1e12
-        # the default raster form: balanced steps (k_raster<TS, false>)
-        kern = "+".join(f"k_raster<{k[6:]}, false>" for k in raster)
+        # the default raster form: balanced steps, a wave per 16-pixel tile
+        kern = "+".join("k_raster_wave" if k == "raster16" else f"k_raster<{k[6:]}, false>" for k in raster)
         tr = measured_traffic(kern)
         roof = {"kernel": kern, "bound": "alu", "achieved": round(ach, 4),
                 "peak": round(ALU_PEAK_TOPS, 2), "unit": "TOP/s", "frac": round(ach / ALU_PEAK_TOPS, 5),
