@@ -10,6 +10,7 @@
 // sequence, so a result is bitwise the same alone and in any mix.  Latency
 // is stamped at submit, launch and observed completion.  Queued requests
 // can be cancelled, and time out at their deadline.
+#include <sys/prctl.h>
 #include <time.h>
 
 #include <algorithm>
@@ -115,6 +116,9 @@ static void retire(hab_server *s, Batch &b, hab_status e, uint64_t t)
 static void run_loop(hab_server *s)
 {
     (void)hipSetDevice(s->ctx->device);
+    // this thread's sleeps end when asked, not up to 50 us later (the kernel's
+    // default slack): they stand between a batch's end and the next one's launch
+    (void)prctl(PR_SET_TIMERSLACK, 1000ul, 0ul, 0ul, 0ul);
     std::vector<ViewReq> vr;
     std::vector<uint64_t> gone;
     Admission::Batch ab;
@@ -192,7 +196,7 @@ static void run_loop(hab_server *s)
         if (!launched) {
             if (any_active || s->adm->queued() != 0) {
                 g.unlock();
-                std::this_thread::sleep_for(std::chrono::microseconds(20));
+                std::this_thread::sleep_for(std::chrono::microseconds(5));
             } else {
                 s->cv_work.wait_for(g, std::chrono::milliseconds(5),
                                     [&] { return s->stop || s->adm->queued() != 0; });
