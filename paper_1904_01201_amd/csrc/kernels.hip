@@ -682,8 +682,7 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 // count exceeds tile_cap, or whose list would end beyond the view's bin
 // capacity, is marked kOverflow.  Then the view's work items are reserved
 // in its tile size's queue and written out; tile_item gets each tile's
-// first item.  A block per view, of 64 or 256 threads where no view has more
-// tiles (1024 views of 16 tiles: 22 us in blocks of 1024, 18 so); the tiles
+// first item.  A block per view, of 256 threads where no view has more tiles; the tiles
 // whose items merge are cleared by the scatter's blocks, not by a view's one
 // (eight views of 768 tiles: 17 us, 9 without it).
 template <int NT>
@@ -740,6 +739,62 @@ __global__ __launch_bounds__(NT) void k_bin_scan(const DView *__restrict__ views
         tile_item[v.tile_base + i] = first;
         for (uint32_t sgm = 0; sgm < ns; ++sgm) items[first + sgm] = make_uint2(vi, i | (sgm << 18));
     }
+}
+
+// The same for views of at most 64 tiles: a wave per view, 16 to a block, which
+// reserves its views' work items together (with a block per view the queue's
+// counter serialises them: 1024 views of 16 tiles took 18 us, 8 so).
+constexpr int kSmallScanWaves = 16;
+__global__ __launch_bounds__(64 * kSmallScanWaves) void k_bin_scan_small(
+    const DView *__restrict__ views, uint32_t nviews, DViewCounters *__restrict__ ctr,
+    const uint32_t *__restrict__ tile_count, uint32_t *__restrict__ tile_off, uint32_t *__restrict__ tile_item,
+    DQueue *__restrict__ q, uint2 *__restrict__ items8, uint2 *__restrict__ items16, uint2 *__restrict__ items32,
+    uint32_t wave_seg)
+{
+    __shared__ uint32_t wtot[kSmallScanWaves], wcls[kSmallScanWaves], base[3];
+    const uint32_t lane = lane_id(), w = uniform(threadIdx.x >> 6), vi = blockIdx.x * kSmallScanWaves + w;
+    const bool valid = vi < nviews;
+    const DView &v = views[valid ? vi : 0u];
+    const uint32_t n = valid ? v.tiles_x * v.tiles_y : 0u, cls = v.ts_log2 - 3;
+    auto excl = [&](uint32_t x, uint32_t &tot) {
+        uint32_t a = x;
+#pragma unroll
+        for (int d = 1; d < 64; d *= 2) {
+            const uint32_t b = __shfl_up(a, d);
+            if (lane >= (uint32_t)d) a += b;
+        }
+        tot = __shfl(a, 63);
+        return a - x;
+    };
+    const uint32_t c = lane < n ? tile_count[v.tile_base + lane] : 0u;
+    const uint32_t e = c <= v.tile_cap ? c : 0u;
+    uint32_t tot, stot;
+    const unsigned long long P = excl(e, tot);
+    const bool over = c > v.tile_cap || P + e > v.bin_cap || c > (kMaxSegments - 1) * seg_size(v.ts_log2, wave_seg);
+    const uint32_t off = (c == 0) ? 0u : (over ? kOverflow : (uint32_t)P);
+    const uint32_t ns = tile_segments(c, off, v.ts_log2, wave_seg);
+    const uint32_t sex = excl(ns, stot);
+    if (lane == 0) {
+        wtot[w] = stot;
+        wcls[w] = cls;
+        if (valid) ctr[vi].bin_used = min(tot, v.bin_cap);
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (int k = 0; k < kSmallScanWaves; ++k) sum += wcls[k] == threadIdx.x ? wtot[k] : 0u;
+        base[threadIdx.x] = sum ? atomicAdd(&q->total[threadIdx.x], sum) : 0u;
+    }
+    __syncthreads();
+    uint32_t first = base[cls] + sex;
+#pragma unroll
+    for (int k = 0; k < kSmallScanWaves; ++k) first += k < (int)w && wcls[k] == cls ? wtot[k] : 0u;
+    if (lane >= n) return;
+    tile_off[v.tile_base + lane] = off;
+    tile_item[v.tile_base + lane] = first;
+    uint2 *items = cls == 0 ? items8 : cls == 1 ? items16 : items32;
+    for (uint32_t sgm = 0; sgm < ns; ++sgm) items[first + sgm] = make_uint2(vi, lane | (sgm << 18));
 }
 
 // ------------------------------------------------------------ k_raster
@@ -1833,10 +1888,16 @@ hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
                        L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins, L.wave_seg, L.zbuf);
     mark(L, 5, s);
     mark(L, 6, s);
-    const uint32_t nt = L.max_tiles <= 64 ? 64 : L.max_tiles <= 256 ? 256 : 1024;
-    auto *const scan = nt == 64 ? k_bin_scan<64> : nt == 256 ? k_bin_scan<256> : k_bin_scan<1024>;
-    hipLaunchKernelGGL(scan, dim3(L.nviews), dim3(nt), 0, s, L.views, L.ctr, L.tile_count, L.tile_off, L.tile_item,
-                       L.queue, L.items[0], L.items[1], L.items[2], L.wave_seg);
+    if (L.max_tiles <= 64) {
+        hipLaunchKernelGGL(k_bin_scan_small, dim3(cdiv(L.nviews, kSmallScanWaves)), dim3(64 * kSmallScanWaves), 0, s,
+                           L.views, L.nviews, L.ctr, L.tile_count, L.tile_off, L.tile_item, L.queue, L.items[0],
+                           L.items[1], L.items[2], L.wave_seg);
+    } else {
+        const uint32_t nt = L.max_tiles <= 256 ? 256 : 1024;
+        hipLaunchKernelGGL(nt == 256 ? k_bin_scan<256> : k_bin_scan<1024>, dim3(L.nviews), dim3(nt), 0, s, L.views, L.ctr,
+                           L.tile_count, L.tile_off, L.tile_item, L.queue, L.items[0], L.items[1], L.items[2],
+                           L.wave_seg);
+    }
     mark(L, 7, s);
     mark(L, 8, s);
     hipLaunchKernelGGL(k_bin<true>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s, L.views, L.nviews,
