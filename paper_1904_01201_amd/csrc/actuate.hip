@@ -27,6 +27,7 @@
 #include <unordered_map>
 #include <vector>
 
+#include "pieces.h"
 #include "runtime.h"
 
 #pragma clang fp contract(off)
@@ -756,8 +757,11 @@ hab_status hab_actuate(hab_context *ctx, const hab_nav *const *navs, uint32_t n,
         // 64 / 8,192 / 16,384 / 65,536 agents: <64, 4> 24 / 46 / 69 / 202,
         // <32, 16> 32 / 51 / 60 / 141, <16, 32> 45 / 71 / 76 / 135.
         auto go = [&](auto kernel, uint32_t per_block) {
-            hipLaunchKernelGGL(kernel, dim3((n + per_block - 1) / per_block), dim3(kActBlock), 0, stream, dt, di, n,
-                               agents, actions, collided, poses, P);
+            in_pieces(n, per_block, kActBlock, [&](uint32_t first, uint32_t count, uint32_t blocks) {
+                hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kActBlock), 0, stream, dt, di + first, count, agents + first,
+                                   actions + first, collided ? collided + first : nullptr,
+                                   poses ? poses + 12ull * first : nullptr, P);
+            });
         };
         if (n <= 8192) go(k_actuate<64, 4>, 4u);
         else if (n <= 32768) go(k_actuate<32, 16>, 16u);
@@ -860,9 +864,10 @@ hab_status hab_nav_free(hab_context *ctx, const hab_nav *nav, const double *poin
         // 100,000 / 1M points: one lane 27 / 42 / 87, 4 lanes 10 / 18 / 71, 16
         // lanes 9 / 13 / 92.
         auto go = [&](auto kernel, uint32_t lanes) {
-            hipLaunchKernelGGL(kernel, dim3((uint32_t)(((uint64_t)n * lanes + kActBlock - 1) / kActBlock)),
-                               dim3(kActBlock), 0, stream, nav->d, reinterpret_cast<const double2 *>(points), n, radius,
-                               out_free);
+            in_pieces(n, kActBlock / lanes, kActBlock, [&](uint32_t first, uint32_t count, uint32_t blocks) {
+                hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kActBlock), 0, stream, nav->d,
+                                   reinterpret_cast<const double2 *>(points) + first, count, radius, out_free + first);
+            });
         };
         if (n <= 131072) go(k_nav_free<16>, 16u);
         else go(k_nav_free<4>, 4u);
