@@ -67,12 +67,14 @@ struct alignas(16) DView {
 static_assert(sizeof(DView) == 240, "DView layout");
 
 // Work queues of the raster stage, per tile size (8, 16, 32): `total`
-// items were appended by the scan.  The items are dealt to kQueues queues
+// items were appended by the scan (and total[kOverTotal] overflow tiles of
+// k_raster_wave).  The items are dealt to kQueues queues
 // in interleaved groups of kQueueGroup; each queue's head sits on its own
 // cache line, so the blocks that drain different queues never contend for
 // one atomic.
 constexpr uint32_t kQueues = 8;       // one per XCD when blocks are dealt round-robin
 constexpr uint32_t kQueueGroup = 4;   // consecutive items that go to one queue
+constexpr uint32_t kOverTotal = 3;
 struct alignas(128) DQueueHead {
     uint32_t next;
     uint32_t pad[31];

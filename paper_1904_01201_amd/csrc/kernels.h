@@ -33,7 +33,7 @@ struct RasterLaunch {
     uint32_t grid;             // persistent raster blocks
     bool wave;                 // 16-pixel tiles, a wave each (k_raster_wave)
     bool lane_owned;           // atomic-free lane-owned z-test (else balanced steps, z-keys in LDS)
-    uint64_t item_cap;         // work items the scratch below can hold
+    uint32_t item_cap;         // work items the scratch below can hold
     uint2 *items;              // [item_cap] (view, tile | segment << 18)
     uint2 *partial;            // [item_cap][TS*TS] per-pixel (1/w bits, key) of each item
 };

@@ -306,13 +306,18 @@ constexpr uint32_t kSlots = 2 * kRun * kCluster;
 // that is partial; it comes after the others.
 __device__ __forceinline__ uint32_t visible_clusters(const DViewCounters &c) { return c.vis_clusters + c.vis_tail; }
 
-// Place `at` of survivor s (counting kSlots per run) of view v; false if there
-// is none.
-__device__ __forceinline__ bool survivor_slot(const DView &v, const uint32_t *__restrict__ vis_clusters, uint32_t s,
-                                              uint32_t &at)
+// Survivors of a view's run (which is in sight).
+__device__ __forceinline__ uint32_t run_count(const DView &v, const uint32_t *__restrict__ vis_clusters, uint32_t run)
 {
-    at = v.surv_base + s;
-    return s % kSlots < vis_clusters[v.pair_base + s / kSlots * kRun];
+    return vis_clusters[v.pair_base + run * kRun];
+}
+
+// Does a survivor's pixel box meet the TS-pixel tile at (ti0, tj0)?
+template <int TS>
+__device__ __forceinline__ bool box_meets(uint2 bb, int ti0, int tj0)
+{
+    return (int)(bb.y & 0xFFFFu) >= ti0 && (int)(bb.x & 0xFFFFu) < ti0 + TS && (int)(bb.y >> 16) >= tj0 &&
+           (int)(bb.x >> 16) < tj0 + TS;
 }
 
 // The exclusive prefix over the views of ceil(visible clusters / per).
@@ -469,13 +474,13 @@ __device__ __forceinline__ uint32_t seg_size(uint32_t ts_log2, uint32_t wave_seg
     return wave_seg && ts_log2 == 4 ? wave_seg : kSegPerTile << (2 * ts_log2);
 }
 
-// Number of (tile, segment) work items of a tile: none when empty, one for
-// an overflow tile (it scans the whole survivor list), else one per
-// segment of at most seg_size list entries.
+// Number of (tile, segment) work items of a tile: none when empty, one per
+// segment of at most seg_size list entries; for an overflow tile, which scans
+// all survivors, one, or none where k_raster_wave takes it from a list of its own.
 __device__ __forceinline__ uint32_t tile_segments(uint32_t c, uint32_t off, uint32_t ts_log2, uint32_t wave_seg)
 {
     if (c == 0) return 0;
-    if (off == kOverflow) return 1;
+    if (off == kOverflow) return wave_seg && ts_log2 == 4 ? 0u : 1u;
     const uint32_t S = seg_size(ts_log2, wave_seg);
     return (c + S - 1) / S;
 }
@@ -520,8 +525,7 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
                  t0 += shares * (kBinBlock / 64) * 16u) {
                 const uint32_t t = t0 + lane;
                 bool multi = false;
-                if (lane < 16u && t < n)
-                    multi = tile_segments(tile_count[v.tile_base + t], tile_off[v.tile_base + t], 4, wave_seg) > 1;
+                if (lane < 16u && t < n) multi = tile_count[v.tile_base + t] > wave_seg || tile_off[v.tile_base + t] == kOverflow;
                 for (unsigned long long m = __ballot(multi); m; m &= m - 1) {
                     uint4 *const z = reinterpret_cast<uint4 *>(zt + wave_tile(v, t0 + (uint32_t)__ffsll((long long)m) - 1u));
                     z[lane] = make_uint4(0, 0, 0, 0);
@@ -538,7 +542,7 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
         uint32_t n = 0, first[kBinRuns], gap[kBinRuns];
 #pragma unroll
         for (uint32_t j = 0; j < kBinRuns; ++j)   // without branches: all in flight together
-            gap[j] = vis_clusters[v.pair_base + min(run + j, (nvis - 1) / kRun) * kRun];
+            gap[j] = run_count(v, vis_clusters, min(run + j, (nvis - 1) / kRun));
 #pragma unroll
         for (uint32_t j = 0; j < kBinRuns; ++j) {
             const uint32_t c = (run + j) * kRun < nvis ? uniform(gap[j]) : 0u;
@@ -685,6 +689,16 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 // first item.  A block per view, of 256 threads where no view has more tiles; the tiles
 // whose items merge are cleared by the scatter's blocks, not by a view's one
 // (eight views of 768 tiles: 17 us, 9 without it).
+//
+// Overflow tiles of k_raster_wave are listed from the end of its items backwards
+// (a tile takes one entry there or one per segment at the front, so the two never
+// meet): it cuts each into as many items as fill the launch.
+__device__ __forceinline__ void list_overflow(DQueue *__restrict__ q, uint2 *__restrict__ items16, uint32_t cap16,
+                                              uint32_t vi, uint32_t tile)
+{
+    items16[cap16 - 1u - atomicAdd(&q->total[kOverTotal], 1u)] = make_uint2(vi, tile);
+}
+
 template <int NT>
 __global__ __launch_bounds__(NT) void k_bin_scan(const DView *__restrict__ views,
                                                          DViewCounters *__restrict__ ctr,
@@ -694,7 +708,8 @@ __global__ __launch_bounds__(NT) void k_bin_scan(const DView *__restrict__ views
                                                          DQueue *__restrict__ q,
                                                          uint2 *__restrict__ items8,
                                                          uint2 *__restrict__ items16,
-                                                         uint2 *__restrict__ items32, uint32_t wave_seg)
+                                                         uint2 *__restrict__ items32, uint32_t wave_seg,
+                                                         uint32_t cap16)
 {
     __shared__ uint32_t wtot[NT / 64];
     __shared__ uint32_t sbase;
@@ -721,6 +736,7 @@ __global__ __launch_bounds__(NT) void k_bin_scan(const DView *__restrict__ views
         if (i < n) {
             tile_off[v.tile_base + i] = off;
             tile_item[v.tile_base + i] = srun + sex;
+            if (off == kOverflow && wave_seg && cls == 1) list_overflow(q, items16, cap16, vi, i);
         }
         run += tot;
         srun += stot;
@@ -749,7 +765,7 @@ __global__ __launch_bounds__(64 * kSmallScanWaves) void k_bin_scan_small(
     const DView *__restrict__ views, uint32_t nviews, DViewCounters *__restrict__ ctr,
     const uint32_t *__restrict__ tile_count, uint32_t *__restrict__ tile_off, uint32_t *__restrict__ tile_item,
     DQueue *__restrict__ q, uint2 *__restrict__ items8, uint2 *__restrict__ items16, uint2 *__restrict__ items32,
-    uint32_t wave_seg)
+    uint32_t wave_seg, uint32_t cap16)
 {
     __shared__ uint32_t wtot[kSmallScanWaves], wcls[kSmallScanWaves], base[3];
     const uint32_t lane = lane_id(), w = uniform(threadIdx.x >> 6), vi = blockIdx.x * kSmallScanWaves + w;
@@ -795,6 +811,7 @@ __global__ __launch_bounds__(64 * kSmallScanWaves) void k_bin_scan_small(
     tile_item[v.tile_base + lane] = first;
     uint2 *items = cls == 0 ? items8 : cls == 1 ? items16 : items32;
     for (uint32_t sgm = 0; sgm < ns; ++sgm) items[first + sgm] = make_uint2(vi, lane | (sgm << 18));
+    if (off == kOverflow && wave_seg && cls == 1) list_overflow(q, items16, cap16, vi, lane);
 }
 
 // ------------------------------------------------------------ k_raster
@@ -1099,6 +1116,12 @@ __device__ __forceinline__ long long join64(int hi, int lo)
 // Records whose edges do not fit the packed form (a vertex far from the tile)
 // are tested one after another by the whole wave.
 //
+// An overflow tile's scan is shared by several items, each gathering the survivors
+// that meet the tile a wave's lanes full before it rebuilds them: few do.  Eight
+// 256 x 256 views of 200k triangles with every tile over its cap take 0.19 ms;
+// one item a tile over the slots with their gaps took 2.0, a 256-thread block over
+// a list without gaps 0.83.
+//
 // Bound by VALU issue, half of it rebuilding the entries' setup: 76 M wave
 // instructions for the 64 bench views (99 M before the setup dropped triangles
 // that cover no pixel), 65 % busy in a launch of half of them, which ends short
@@ -1108,7 +1131,7 @@ __device__ __forceinline__ long long join64(int hi, int lo)
 constexpr uint32_t kWavePairs = 512;   // (record, block) pairs listed at once: eight blocks a record
 
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPerSimd))) void k_raster_wave(
-    const DView *__restrict__ views, const uint2 *__restrict__ items, uint32_t seg, DQueue *__restrict__ q,
+    const DView *__restrict__ views, const uint2 *__restrict__ items, uint32_t cap, uint32_t seg, DQueue *__restrict__ q,
     DViewCounters *__restrict__ ctr, const uint32_t *__restrict__ vis_clusters, const uint32_t *__restrict__ skey,
     const uint2 *__restrict__ sbox, const uint32_t *__restrict__ tile_count, const uint32_t *__restrict__ tile_off, const uint32_t *__restrict__ bins,
     unsigned long long *__restrict__ zt, uint32_t *__restrict__ err)
@@ -1125,7 +1148,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPe
     // in block 0 and its byte offset among the block's z-keys
     const uint32_t gi = lane >> 3, pxl = lane & 3u, pyl = (lane >> 2) & 1u;
     const uint32_t QPl = (256u * pyl) | ((256u * pxl) << 16), zl = (lane & 7u) * 8u;
-    const uint32_t total = q->total[cls];
+    // overflow tiles come first, each as `parts` items that share its scan by
+    // runs: about two items a resident wave in all
+    const uint32_t nover = uniform(q->total[kOverTotal]);
+    const uint32_t parts = nover ? max(1u, min(2u * gridDim.x / nover, 64u)) : 1u;
+    const uint32_t nfirst = nover * parts, total = nfirst + q->total[cls];
     const uint32_t nq = min(kQueues, gridDim.x), x = blockIdx.x % nq;
     const char *const rb = reinterpret_cast<const char *>(srec);
     bool rerr = false;
@@ -1135,18 +1162,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPe
         k = uniform(k);
         const uint32_t item = ((k / kQueueGroup) * nq + x) * kQueueGroup + k % kQueueGroup;
         if (item >= total) break;
-        const uint2 it = items[item];
+        const bool over = item < nfirst;
+        const uint2 it = items[over ? cap - 1u - item / parts : item - nfirst];
         const uint32_t vi = uniform(it.x), itile = uniform(it.y);
         const uint32_t tile = itile & 0x3FFFFu, sgm = itile >> 18;
         const DView &v = views[vi];
         const int ti0 = (int)(tile % v.tiles_x) * TS, tj0 = (int)(tile / v.tiles_x) * TS;
         const bool count = v.count_work != 0;
         const uint32_t cnt = uniform(tile_count[v.tile_base + tile]);
-        const uint32_t off = uniform(tile_off[v.tile_base + tile]);
-        const bool over = off == kOverflow;
-        const uint32_t begin = over ? 0u : sgm * seg;
-        const uint32_t end = over ? (uniform(visible_clusters(ctr[vi])) + kRun - 1) / kRun * kSlots : min(begin + seg, cnt);
-        const uint32_t *list = bins + v.bin_base + (over ? 0u : off);
         uint4 *const z4 = reinterpret_cast<uint4 *>(zk);
         z4[lane] = make_uint4(0, 0, 0, 0);
         z4[lane + 64] = make_uint4(0, 0, 0, 0);
@@ -1157,28 +1180,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPe
             atomicMax(reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(zk) + zo),
                       ((unsigned long long)__float_as_uint(rho) << 32) | (unsigned long long)nkey);
         };
-        for (uint32_t base = begin; base < end; base += 64) {
-            const uint32_t e = base + lane;
+        // test up to 64 entries, one a lane
+        auto entries = [&](bool have, uint32_t key) {
             LRec r;
             LExt rx;
             int box[4], dx[3], dy[3];
-            uint32_t notown = 0, m = 0, key = 0;
-            bool packed = true, have = e < end;
-            if (have) {
-                if (over) {
-                    uint32_t at;
-                    have = survivor_slot(v, vis_clusters, e, at);
-                    if (have) {
-                        const uint2 bb = sbox[at];
-                        have = (int)(bb.y & 0xFFFFu) >= ti0 && (int)(bb.x & 0xFFFFu) < ti0 + TS &&
-                               (int)(bb.y >> 16) >= tj0 && (int)(bb.x >> 16) < tj0 + TS;
-                        key = skey[at];
-                    }
-                } else {
-                    key = list[e];
-                }
-                have = have && edge_rec<TS>(v, key, ti0, tj0, r, rx, box, dx, dy, notown, packed, rerr);
-            }
+            uint32_t notown = 0, m = 0;
+            bool packed = true;
+            have = have && edge_rec<TS>(v, key, ti0, tj0, r, rx, box, dx, dy, notown, packed, rerr);
             if (have && packed) {
                 srec[lane] = r;
                 // the blocks that the box touches, less those that an edge
@@ -1279,10 +1288,65 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPe
                         put((uint32_t)s * 512u + lane * 8u, ((float)E0 * w0 + (float)E1 * w1) + (float)E2 * w2, ia, nkey);
                 }
             }
+        };
+        if (!over) {
+            const uint32_t begin = sgm * seg, end = min(begin + seg, cnt);
+            const uint32_t *const list = bins + v.bin_base + uniform(tile_off[v.tile_base + tile]);
+            for (uint32_t base = begin; base < end; base += 64) {
+                const uint32_t e = base + lane;
+                const bool have = e < end;
+                entries(have, have ? list[e] : 0u);
+            }
+        } else {
+            // this part's runs (their counts loaded 64 at a time); the survivors
+            // that meet the tile are gathered a wave's lanes full before they are
+            // tested
+            const uint32_t nruns = (uniform(visible_clusters(ctr[vi])) + kRun - 1) / kRun;
+            uint32_t held = 0, key = 0;
+            for (uint32_t run0 = item % parts; run0 < nruns; run0 += 64 * parts) {
+                const uint32_t mine = run0 + lane * parts;
+                const uint32_t counts = mine < nruns ? run_count(v, vis_clusters, mine) : 0u;
+                for (uint32_t j = 0; j < 64 && run0 + j * parts < nruns; ++j) {
+                    const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)counts, (int)j);
+                    const uint32_t slot0 = v.surv_base + (run0 + j * parts) * kSlots;
+                    // two steps' boxes in flight together
+                    for (uint32_t e0 = 0; e0 < n; e0 += 128) {
+                        const uint32_t ea = e0 + lane, eb = ea + 64;
+                        const uint2 ba = sbox[slot0 + min(ea, n - 1)];
+                        const uint2 bb = sbox[slot0 + min(eb, n - 1)];
+                        bool meets = ea < n && box_meets<TS>(ba, ti0, tj0);
+                        const bool next = eb < n && box_meets<TS>(bb, ti0, tj0);
+#pragma unroll 1
+                        for (uint32_t e = ea;;) {
+                            const unsigned long long mm = __ballot(meets);
+                            const uint32_t got = (uint32_t)__popcll(mm);
+                            if (got) {
+                                // hits go to the lanes behind those held, the
+                                // others' (junk) behind them: each lane gets one
+                                const uint32_t rank = (uint32_t)__popcll(mm & lt), to = held + (meets ? rank : got + lane - rank);
+                                uint32_t found = 0;
+                                if (meets) found = skey[slot0 + e];
+                                found = (uint32_t)__builtin_amdgcn_ds_permute((int)((to & 63u) << 2), (int)found);
+                                if (lane >= held) key = found;
+                                held += got;
+                                if (held >= 64) {
+                                    entries(true, key);
+                                    held -= 64;
+                                    key = found;
+                                }
+                            }
+                            if (e == eb) break;
+                            e = eb;
+                            meets = next;
+                        }
+                    }
+                }
+            }
+            if (held) entries(lane < held, key);
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         unsigned long long *const z = zt + wave_tile(v, tile);
-        if (over || cnt <= seg) {
+        if (!over && cnt <= seg) {
             uint4 *const zo = reinterpret_cast<uint4 *>(z);
             zo[lane] = z4[lane];
             zo[lane + 64] = z4[lane + 64];
@@ -1344,6 +1408,9 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 32
     // (row-major 8 x 8)
     __shared__ unsigned long long szb[NT / 64][LO ? 1 : 64];
     __shared__ uint32_t s_item;
+    // an overflow tile's scan: has a wave staged any in this step (two, in turn)
+    constexpr uint32_t NW = NT / 64;
+    __shared__ uint32_t s_more[2];
 
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const unsigned long long lt = lanemask_lt();
@@ -1372,6 +1439,7 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 32
     const uint32_t nq = min(kQueues, gridDim.x), x = blockIdx.x % nq;
     for (;;) {
         if (tid == 0) {
+            if (NW > 1) s_more[0] = s_more[1] = 0;
             const uint32_t k = atomicAdd(&q->head[cls][x].next, 1u);
             s_item = ((k / kQueueGroup) * nq + x) * kQueueGroup + k % kQueueGroup;
         }
@@ -1394,8 +1462,6 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 32
         const uint32_t cnt = tile_count[tglob];
         const uint32_t off = tile_off[tglob];
         const bool over = off == kOverflow;
-        const uint32_t begin = over ? 0u : sgm * S;
-        const uint32_t end = over ? (visible_clusters(ctr[vi]) + kRun - 1) / kRun * kSlots : min(begin + S, cnt);
         const uint32_t *list = bins + v.bin_base + (over ? 0u : off);
 
         // z-key of the best fragment so far: 1/w bits above the complemented
@@ -1412,31 +1478,44 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 32
         }
         uint32_t ncov = 0;
 
-        for (uint32_t base = begin; base < end; base += NT) {
+        // the list's segment, a block's threads at a time; of an overflow tile the
+        // survivors of all visible runs, each wave through runs of its own, 64 at
+        // a time, for the whole block
+        const uint32_t nruns = over ? (uniform(visible_clusters(ctr[vi])) + kRun - 1) / kRun : 0u;
+        uint32_t base = over ? 0u : sgm * S, stop = over ? 0u : min(base + S, cnt), run = uniform(wave);
+        for (uint32_t step = 0;; ++step) {
+            if (over) {
+                while (base >= stop && run < nruns) {
+                    base = run * kSlots;
+                    stop = base + uniform(run_count(v, vis_clusters, run));
+                    run += NW;
+                }
+                if (NW == 1 && base >= stop) break;
+                if (NW > 1 && lane == 0 && base < stop) s_more[step & 1u] = 1;
+            } else if (base >= stop) {
+                break;
+            }
             // stage: each thread rebuilds one list entry's edge setup for this tile
             {
-                const uint32_t e = base + tid;
+                const uint32_t e = base + (over ? lane : tid);
                 QM qm = 0;
                 LRec r;
                 LExt rx;
-                if (e < end) {
-                    bool go = true;
-                    uint32_t key = 0;
+                bool go = e < stop;
+                uint32_t key = 0;
+                if (go) {
                     if (over) {
-                        uint32_t at;
-                        go = survivor_slot(v, vis_clusters, e, at);
-                        if (go) {
-                            const uint2 bb = sbox[at];
-                            const int i0 = (int)(bb.x & 0xFFFFu), j0 = (int)(bb.x >> 16);
-                            const int i1 = (int)(bb.y & 0xFFFFu), j1 = (int)(bb.y >> 16);
-                            go = i1 >= ti0 && i0 < ti0 + TS && j1 >= tj0 && j0 < tj0 + TS;
-                            key = skey[at];
-                        }
+                        go = box_meets<TS>(sbox[v.surv_base + e], ti0, tj0);
+                        if (go) key = skey[v.surv_base + e];
                     } else {
                         key = list[e];
                     }
-                    if (go && !build_rec<TS>(v, key, ti0, tj0, r, rx, qm, rerr)) qm = 0;
                 }
+                if (NW == 1 && over && !__ballot(go)) {
+                    base += 64;
+                    continue;
+                }
+                if (go && !build_rec<TS>(v, key, ti0, tj0, r, rx, qm, rerr)) qm = 0;
                 sqm[tid] = qm;
                 if (qm) {
                     srec[tid] = r;
@@ -1444,7 +1523,12 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 32
                 }
             }
             __syncthreads();
-            const uint32_t m = min((uint32_t)NT, end - base);
+            const uint32_t m = over ? (uint32_t)NT : min((uint32_t)NT, stop - base);
+            base += over ? 64u : (uint32_t)NT;
+            if (NW > 1 && over) {
+                if (!s_more[step & 1u]) break;   // no wave had any
+                if (tid == 0) s_more[~step & 1u] = 0;
+            }
             if constexpr (LO) {
                 // z-test of this lane's pixel against fragment weights w_k where
                 // covered (cov) and the wave's coverage ballot cm
@@ -1821,7 +1905,7 @@ template <int TS>
 static void launch_raster(const LaunchPlan &L, const RasterLaunch &R, hipStream_t s)
 {
     if (R.wave) {
-        hipLaunchKernelGGL(k_raster_wave, dim3(R.grid), dim3(64), 0, s, L.views, R.items, L.wave_seg, L.queue, L.ctr,
+        hipLaunchKernelGGL(k_raster_wave, dim3(R.grid), dim3(64), 0, s, L.views, R.items, R.item_cap, L.wave_seg, L.queue, L.ctr,
                            L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.bins, L.zbuf, L.err);
         return;
     }
@@ -1884,24 +1968,29 @@ hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
                        L.pairs, L.skey, L.sbox, L.err);
     mark(L, 3, s);
     mark(L, 4, s);
-    hipLaunchKernelGGL(k_bin<false>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s, L.views, L.nviews,
-                       L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins, L.wave_seg, L.zbuf);
+    hipLaunchKernelGGL(k_bin<false>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s,
+                       L.views, L.nviews, L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins,
+                       L.wave_seg, L.zbuf);
     mark(L, 5, s);
     mark(L, 6, s);
+    uint32_t cap16 = 0;
+    for (int k = 0; k < L.nraster; ++k)
+        if (L.raster[k].wave) cap16 = L.raster[k].item_cap;
     if (L.max_tiles <= 64) {
         hipLaunchKernelGGL(k_bin_scan_small, dim3(cdiv(L.nviews, kSmallScanWaves)), dim3(64 * kSmallScanWaves), 0, s,
                            L.views, L.nviews, L.ctr, L.tile_count, L.tile_off, L.tile_item, L.queue, L.items[0],
-                           L.items[1], L.items[2], L.wave_seg);
+                           L.items[1], L.items[2], L.wave_seg, cap16);
     } else {
         const uint32_t nt = L.max_tiles <= 256 ? 256 : 1024;
         hipLaunchKernelGGL(nt == 256 ? k_bin_scan<256> : k_bin_scan<1024>, dim3(L.nviews), dim3(nt), 0, s, L.views, L.ctr,
                            L.tile_count, L.tile_off, L.tile_item, L.queue, L.items[0], L.items[1], L.items[2],
-                           L.wave_seg);
+                           L.wave_seg, cap16);
     }
     mark(L, 7, s);
     mark(L, 8, s);
-    hipLaunchKernelGGL(k_bin<true>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s, L.views, L.nviews,
-                       L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins, L.wave_seg, L.zbuf);
+    hipLaunchKernelGGL(k_bin<true>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s,
+                       L.views, L.nviews, L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins,
+                       L.wave_seg, L.zbuf);
     mark(L, 9, s);
     for (int k = 0; k < L.nraster; ++k) {
         const RasterLaunch &R = L.raster[k];

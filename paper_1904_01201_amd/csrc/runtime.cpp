@@ -625,10 +625,11 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         for (uint32_t k : lview[c]) R.blocks += dv[k].tiles_x * dv[k].tiles_y;
         R.bands = lpre[c].back() + cdiv(last.W, 32u) * cdiv(last.H, 2 * stack[c]);
         R.stack = stack[c];
-        R.item_cap = item_cap[c];
-        R.grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(item_cap[c], (uint64_t)cus * kBlocksPerCu[c]));
+        R.item_cap = (uint32_t)item_cap[c];
         R.lane_owned = o.lane_owned_z;
         R.wave = c == 1 && wave16;
+        // k_raster_wave may cut overflow tiles into more items than there is room for in the list
+        R.grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(item_cap[c] * (R.wave ? 4 : 1), (uint64_t)cus * kBlocksPerCu[c]));
     }
     return HAB_OK;
 }
