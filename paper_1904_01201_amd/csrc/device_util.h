@@ -55,28 +55,6 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *wtot, 
     return pre + s - x;
 }
 
-// Add 1 to counters[key] for every lane with `has`, one atomic per distinct
-// key in the wave.  Returns, per participating lane, the counter's value
-// before the wave's additions plus the lane's rank among the lanes with the
-// same key: a unique slot.
-__device__ __forceinline__ uint32_t wave_aggregated_add(uint32_t *counters, uint32_t key, bool has)
-{
-    unsigned long long pending = __ballot(has);
-    uint32_t mine = 0;
-    const uint32_t lane = lane_id();
-    while (pending) {
-        const int leader = __ffsll((long long)pending) - 1;
-        const uint32_t lk = __shfl(key, leader);
-        const unsigned long long peers = __ballot(has && key == lk);
-        uint32_t base = 0;
-        if (lane == (uint32_t)leader) base = atomicAdd(&counters[lk], (uint32_t)__popcll(peers));
-        base = __shfl(base, leader);
-        if (has && key == lk) mine = base + (uint32_t)__popcll(peers & lanemask_lt());
-        pending &= ~peers;
-    }
-    return mine;
-}
-
 __device__ __forceinline__ uint2 pack_box(const PixBox &b)
 {
     return make_uint2((uint32_t)b.i0 | ((uint32_t)b.j0 << 16), (uint32_t)b.i1 | ((uint32_t)b.j1 << 16));

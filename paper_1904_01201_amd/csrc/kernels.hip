@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kSetupBlock) __attribute__((amdgpu_waves_per_eu(kSe
 // Items of the count/scatter kernels are (view, chunk of kBinRuns runs); every block builds the prefix of chunk counts over the
 // views, then strides over the items.
 constexpr uint32_t kBinHeld = 4;       // survivors a thread holds in registers
-constexpr uint32_t kLdsTiles = 2048;   // views with more tiles bin through global atomics
+constexpr uint32_t kLdsTiles = 2048;   // of a view that are binned at once
 
 // LDS slot of tile i in the per-chunk tile arrays: the low five bits are
 // XORed with the next five, a permutation within each aligned run of 32
@@ -465,6 +465,30 @@ __device__ __forceinline__ TileRange tile_range(uint2 bb, uint32_t ts)
     r.tx1 = (int)(bb.y & 0xFFFFu) >> ts;
     r.ty1 = (int)(bb.y >> 16) >> ts;
     return r;
+}
+
+// f(tile, key) for the tiles of a range, whose rows hold tiles_x, that each lane's
+// survivor (if it has one) touches.  A large box would hold up the other lanes:
+// the whole wave walks it.
+template <class F>
+__device__ __forceinline__ void walk_tiles(bool has, const TileRange &R, uint32_t tiles_x, uint32_t key, F f)
+{
+    constexpr int kLaneTiles = 24;
+    const int nx = R.tx1 - R.tx0 + 1, area = has ? nx * (R.ty1 - R.ty0 + 1) : 0;
+    if (has && area <= kLaneTiles)
+        for (int ty = R.ty0; ty <= R.ty1; ++ty)
+            for (int tx = R.tx0; tx <= R.tx1; ++tx) f((uint32_t)ty * tiles_x + (uint32_t)tx, key);
+    for (unsigned long long m = __ballot(area > kLaneTiles); m; m &= m - 1) {
+        const int l = __ffsll((long long)m) - 1;
+        const int wx = __builtin_amdgcn_readlane(nx, l), wn = __builtin_amdgcn_readlane(area, l);
+        const int x0 = __builtin_amdgcn_readlane(R.tx0, l), y0 = __builtin_amdgcn_readlane(R.ty0, l);
+        const uint32_t wk = (uint32_t)__builtin_amdgcn_readlane((int)key, l);
+        const float iw = 1.0f / (float)wx;
+        for (int p = (int)lane_id(); p < wn; p += 64) {
+            const int y = (int)(((float)p + 0.5f) * iw);   // exact: a few thousand tiles at most
+            f((uint32_t)(y0 + y) * tiles_x + (uint32_t)(x0 + p - y * wx), wk);
+        }
+    }
 }
 
 // List entries of one work item: kSegPerTile * TS^2, or wave_seg (if not 0) where
@@ -494,7 +518,10 @@ __device__ __forceinline__ size_t wave_tile(const DView &v, uint32_t tile)
 // Eight waves per SIMD (64 VGPRs in the scatter): 2048 blocks, the grid, are
 // resident; with 66 VGPRs a quarter of them ran after the others (1024 views'
 // scatter 47 us, 41 so).
-template <bool SCATTER>
+//
+// LARGE: some view has more tiles than the histogram holds.  A launch without one
+// is spared that form's register spills (5 us of the scatter of 64 views).
+template <bool SCATTER, bool LARGE>
 __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_bin(const DView *__restrict__ views, uint32_t nviews,
                                                    const DViewCounters *__restrict__ ctr,
                                                    const uint32_t *__restrict__ vis_clusters,
@@ -561,7 +588,7 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
         // assumed to leave the view records alone
         const uint32_t ts = v.ts_log2, tiles_x = v.tiles_x, nt = v.tiles_x * v.tiles_y;
         const uint32_t tile_base = v.tile_base, bin_base = v.bin_base;
-        if (nt <= kLdsTiles) {
+        if (!LARGE || nt <= kLdsTiles) {
             // a thread's first survivors, loaded together while the histogram
             // is cleared and kept for the scatter; a chunk of 8 runs has about
             // 860, more go one round at a time
@@ -612,7 +639,7 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 #pragma unroll
                 for (int k = 0; k < kPer; ++k) {
                     const uint32_t i = tid + (uint32_t)k * kBinBlock;
-                    off[k] = c[k] ? tile_off[tile_base + i] : kOverflow;
+                    off[k] = i < nt && c[k] ? tile_off[tile_base + i] : kOverflow;   // (so written, no register spills)
                 }
 #pragma unroll
                 for (int k = 0; k < kPer; ++k) {
@@ -648,34 +675,60 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
             }
             __syncthreads();
         } else {
-            // large views: wave-aggregated global atomics
+            // more tiles than the histogram holds: in windows of whole rows, from
+            // the first to the last that the chunk touches.  A 2048 x 2048 view of a
+            // 2k-triangle room is counted and scattered in 0.11 and 0.6 ms; a global
+            // atomic per tile and survivor took 4.4 and 2.2 (a 1024 x 1024 view of 1M
+            // triangles 0.02 and 0.05; 0.13 and 0.51).
+            const uint32_t high = kLdsTiles / tiles_x;
+            uint32_t lo = v.tiles_y, hi = 0;
+            for (uint32_t e = tid; e < n; e += kBinBlock) {
+                const TileRange R = tile_range(sbox[at(e)], ts);
+                lo = min(lo, (uint32_t)R.ty0);
+                hi = max(hi, (uint32_t)R.ty1 + 1u);
+            }
+            if (tid < 2) hist[tid] = tid ? 0u : lo;
+            __syncthreads();
+            atomicMin(&hist[0], lo);
+            atomicMax(&hist[1], hi);
+            __syncthreads();
+            lo = uniform(hist[0]);
+            hi = uniform(hist[1]);
+            __syncthreads();
 #pragma unroll 1
-            for (uint32_t e0 = 0; e0 < n; e0 += kBinBlock) {
-                TileRange R = {0, 0, -1, -1};   // empty
-                uint32_t key = 0;
-                if (e0 + tid < n) {
-                    const uint32_t s = at(e0 + tid);
-                    R = tile_range(sbox[s], ts);
-                    if (SCATTER) key = skey[s];
-                }
-                // every lane walks its box's tiles row by row
-                int tx = R.tx0, ty = R.ty0;
-                while (__ballot(ty <= R.ty1)) {
-                    bool act = ty <= R.ty1;
-                    uint32_t tile = 0;
-                    if (act) tile = v.tile_base + (uint32_t)ty * v.tiles_x + (uint32_t)tx;
+            for (; lo < hi; lo += high) {
+                const uint32_t base = tile_base + lo * tiles_x, nw = min(high * tiles_x, nt - lo * tiles_x);
+                auto each = [&](auto f) {
+                    for (uint32_t e0 = 0; e0 < n; e0 += kBinBlock) {
+                        const bool has = e0 + tid < n;
+                        const uint32_t s = at(has ? e0 + tid : 0u);
+                        TileRange R = tile_range(sbox[s], ts);
+                        R.ty0 = max(R.ty0 - (int)lo, 0);
+                        R.ty1 = min(R.ty1 - (int)lo, (int)high - 1);
+                        walk_tiles(has, R, tiles_x, SCATTER ? skey[s] : 0u, f);
+                    }
+                };
+                for (uint32_t i = tid; i < ((nw + 31u) & ~31u); i += kBinBlock) hist[i] = 0;
+                __syncthreads();
+                each([&](uint32_t tl, uint32_t) { atomicAdd(&hist[swz(tl)], 1u); });
+                __syncthreads();
+                for (uint32_t i = tid; i < nw; i += kBinBlock) {
+                    const uint32_t c = hist[swz(i)];
+                    if (!c) continue;
                     if (!SCATTER) {
-                        wave_aggregated_add(tile_count, tile, act);
+                        atomicAdd(&tile_count[base + i], c);
                     } else {
-                        const uint32_t off = act ? tile_off[tile] : kOverflow;
-                        const bool put = act && off != kOverflow;
-                        const uint32_t slot = wave_aggregated_add(tile_cursor, tile, put);
-                        if (put) bins[v.bin_base + off + slot] = key;
+                        const uint32_t off = tile_off[base + i];
+                        lbase[swz(i)] = off == kOverflow ? kOverflow : off + atomicAdd(&tile_cursor[base + i], c);
                     }
-                    if (act && ++tx > R.tx1) {
-                        tx = R.tx0;
-                        ++ty;
-                    }
+                }
+                __syncthreads();
+                if (SCATTER) {
+                    each([&](uint32_t tl, uint32_t k) {
+                        const uint32_t b = lbase[swz(tl)];
+                        if (b != kOverflow) bins[bin_base + b + (atomicAdd(&hist[swz(tl)], 1u << 16) >> 16)] = k;
+                    });
+                    __syncthreads();
                 }
             }
         }
@@ -1968,7 +2021,9 @@ hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
                        L.pairs, L.skey, L.sbox, L.err);
     mark(L, 3, s);
     mark(L, 4, s);
-    hipLaunchKernelGGL(k_bin<false>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s,
+    const bool large = L.max_tiles > kLdsTiles;
+    auto *const k_count = large ? k_bin<false, true> : k_bin<false, false>;
+    hipLaunchKernelGGL(k_count, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s,
                        L.views, L.nviews, L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins,
                        L.wave_seg, L.zbuf);
     mark(L, 5, s);
@@ -1988,7 +2043,8 @@ hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
     }
     mark(L, 7, s);
     mark(L, 8, s);
-    hipLaunchKernelGGL(k_bin<true>, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s,
+    auto *const k_scatter = large ? k_bin<true, true> : k_bin<true, false>;
+    hipLaunchKernelGGL(k_scatter, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s,
                        L.views, L.nviews, L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins,
                        L.wave_seg, L.zbuf);
     mark(L, 9, s);
