@@ -72,12 +72,35 @@ hab_status hab_init(int device, hab_context **out)
 
 static size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
+// Device memory that an upload works in (a mesh's vertices as given).  The context
+// keeps up to kKeepUpload bytes of it for the next upload, and takes kMinUpload
+// (a million vertices) at once: a free makes the next launch wait for the unmapping
+// (a 200k-triangle scene's first frame took 0.42 ms instead of 0.15), which larger
+// scenes, 5 ms and more to upload, hardly notice.
+static constexpr size_t kKeepUpload = 64ull << 20, kMinUpload = 16ull << 20;
+
+static void upload_memory_free(hab_context *ctx)
+{
+    dev_free(ctx->up_mem);
+    ctx->up_mem = nullptr;
+    ctx->up_bytes = 0;
+}
+
+static bool upload_memory(hab_context *ctx, size_t bytes)
+{
+    if (bytes <= ctx->up_bytes) return true;
+    upload_memory_free(ctx);
+    bytes = std::max(bytes, kMinUpload);
+    if (!dev_alloc(&ctx->up_mem, bytes)) return false;
+    ctx->up_bytes = bytes;
+    return true;
+}
+
 // Device memory of a scene (every pointer may be null).
 static void free_scene_mem(Scene *s)
 {
     dev_free(s->tpos);
-    dev_free(s->rec);
-    dev_free(s->src);
+    dev_free(s->attr);
     dev_free(s->cbox);
     dev_free(s->inst);
     dev_free(s->tex);
@@ -95,6 +118,7 @@ hab_status hab_shutdown(hab_context *ctx)
         }
         ctx->scenes.clear();
         release_navs(ctx);
+        upload_memory_free(ctx);
         for (auto &ps : ctx->prof_sets)
             for (auto &e : ps.ev) (void)hipEventDestroy(e);
         if (ctx->fork_ev) (void)hipEventDestroy(ctx->fork_ev);
@@ -168,48 +192,53 @@ hab_status hab_scene_upload(hab_context *ctx, const hab_mesh_desc *m, hipStream_
             s->lo[a] = lo[a];
             s->hi[a] = hi[a];
         }
-        const size_t bp = 36ull * std::max<uint32_t>(T, 1), br = sizeof(TriRec) * std::max<uint32_t>(T, 1);
+        // what stays: per triangle its positions and its vertices' colours or
+        // texture coordinates.  The mesh's vertices are gathered on the device
+        // from the context's upload memory; its indices from there too, or from
+        // the place that the colours take.
+        const uint64_t t1 = std::max<uint32_t>(T, 1);
+        const size_t bp = 36 * t1, ba = (textured ? 24 : 12) * t1;
         const size_t bb = 2 * sizeof(float4) * std::max<uint32_t>(ncl, 1);
-        const size_t bs = m->instances ? std::max<size_t>(4ull * T, 4) : 0;
+        const size_t bs = m->instances ? 4 * t1 : 0;
         const size_t btex = textured ? 4ull * m->tex_width * m->tex_height : 0;
-        // the mesh as given, which the device writes the triangles out from.
-        // It stays until the scene goes: a free here makes the next launch
-        // wait for the unmapping (a 200k-triangle scene's first frame took
-        // 0.42 ms instead of 0.15).
-        const size_t sv = align_up(12ull * V), si = align_up(12ull * T), sc = m->colors ? align_up(3ull * V) : 0,
-                     su = textured ? 8ull * V : 0;
+        const size_t sv = align_up(12ull * V), si = textured ? align_up(12ull * T) : 0,
+                     sc = !textured && m->colors ? align_up(3ull * V) : 0, su = textured ? align_up(8ull * V) : 0;
         auto drop = [&]() {
             free_scene_mem(s);
             delete s;
         };
-        bool ok = dev_alloc((void **)&s->tpos, bp) && dev_alloc((void **)&s->rec, br) &&
+        bool ok = dev_alloc((void **)&s->tpos, bp) && dev_alloc((void **)&s->attr, ba) &&
                   dev_alloc((void **)&s->cbox, bb) && (!bs || dev_alloc((void **)&s->inst, bs)) &&
-                  (!btex || dev_alloc((void **)&s->tex, btex)) && dev_alloc(&s->src, sv + si + sc + su);
+                  (!btex || dev_alloc((void **)&s->tex, btex)) && upload_memory(ctx, sv + si + sc + su);
         if (!ok) {
             drop();
             return HAB_ERR_OUT_OF_MEMORY;
         }
-        s->bytes = bp + br + bb + bs + btex + sv + si + sc + su;
+        s->bytes = bp + ba + bb + bs + btex;
         if (textured) {
             s->tw = m->tex_width;
             s->th = m->tex_height;
         }
-        char *const b = static_cast<char *>(s->src);
+        char *const b = static_cast<char *>(ctx->up_mem);
+        uint32_t *const idx = textured ? reinterpret_cast<uint32_t *>(b + sv) : s->attr;
         MeshSource ms;
         ms.pos = reinterpret_cast<const float *>(b);
-        ms.idx = reinterpret_cast<const uint32_t *>(b + sv);
+        ms.idx = idx;
         ms.col = sc ? reinterpret_cast<const uint8_t *>(b + sv + si) : nullptr;
         ms.uv = su ? reinterpret_cast<const float *>(b + sv + si + sc) : nullptr;
         hipError_t e = hipMemcpyAsync(b, m->positions, 12ull * V, hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess && T) e = hipMemcpyAsync(b + sv, m->indices, 12ull * T, hipMemcpyHostToDevice, stream);
+        if (e == hipSuccess && T) e = hipMemcpyAsync(idx, m->indices, 12ull * T, hipMemcpyHostToDevice, stream);
         if (e == hipSuccess && sc) e = hipMemcpyAsync(b + sv + si, m->colors, 3ull * V, hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess && su) e = hipMemcpyAsync(b + sv + si + sc, m->uvs, su, hipMemcpyHostToDevice, stream);
+        if (e == hipSuccess && su) e = hipMemcpyAsync(b + sv + si + sc, m->uvs, 8ull * V, hipMemcpyHostToDevice, stream);
         if (e == hipSuccess && bs && T)
             e = hipMemcpyAsync(s->inst, m->instances, 4ull * T, hipMemcpyHostToDevice, stream);
         if (e == hipSuccess && btex)
             e = hipMemcpyAsync(s->tex, texels.data(), btex, hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess && T) e = launch_scene(ms, T, s->tpos, s->rec, s->cbox, stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(stream);
+        if (e == hipSuccess && T) e = launch_scene(ms, T, s->tpos, s->attr, s->cbox, stream);
+        // also after a failure: what was enqueued reads the upload memory
+        const hipError_t done = hipStreamSynchronize(stream);
+        if (e == hipSuccess) e = done;
+        if (ctx->up_bytes > kKeepUpload) upload_memory_free(ctx);
         if (e != hipSuccess) {
             drop();
             return HAB_ERR_DEVICE;

@@ -18,19 +18,6 @@ constexpr int kCluster = 64;                  // triangles per culling cluster (
 constexpr uint32_t kErrRange = 1u;            // a vertex snapped outside |X|,|Y| < 2^29
 constexpr uint32_t kErrResolve = 2u;          // a winning key could not be rebuilt
 
-// What shading needs of a triangle in one 64-byte record, half a cache line: the
-// nine coordinates of its vertices as in tpos, then their colours (packed
-// R | G << 8 | B << 16) or, in a textured scene, their texture coordinates.
-struct alignas(64) TriRec {
-    float pos[9];
-    union {
-        uint32_t col[3];
-        float uv[6];
-    };
-    uint32_t pad;
-};
-static_assert(sizeof(TriRec) == 64, "TriRec layout");
-
 // One view of a launch.  16-byte aligned; 240 bytes.
 struct alignas(16) DView {
     float p[3];
@@ -40,7 +27,8 @@ struct alignas(16) DView {
     uint32_t T;                 // triangles of the scene
     uint32_t ts_log2;           // tile size 8/16/32 -> 3/4/5
     const float *tpos;          // [T][3][3] vertex positions per triangle
-    const TriRec *rec;          // [T] records of the shading
+    const uint32_t *attr;       // [T][3] vertex colours per triangle (R | G << 8 | B << 16), or of a
+                                //   textured scene [T][3][2] texture coordinates (float bits)
     uint8_t *rgb;               // [H][W][3] or null
     float *depth;               // [H][W] or null
     uint32_t *tri;              // [H][W] or null

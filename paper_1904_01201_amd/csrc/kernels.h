@@ -106,9 +106,9 @@ struct MeshSource {
     const float *uv;
 };
 
-// Write a scene's triangles out on stream s: positions, shading records and the
-// bounding box of every kCluster consecutive ones.
-hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, TriRec *rec, float4 *cbox, hipStream_t s);
+// Write a scene's triangles out on stream s: positions, attributes (the colours may
+// overwrite the indices) and the bounding box of every kCluster consecutive ones.
+hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, uint32_t *attr, float4 *cbox, hipStream_t s);
 
 // Compare recip_rn with the IEEE division 1/x for every float whose bits
 // lie in [lo, hi) (lo < hi <= 0x7F800000), adding the number of differing

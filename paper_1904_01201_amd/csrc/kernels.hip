@@ -53,36 +53,35 @@
 namespace habmi {
 
 // ------------------------------------------------------------ k_scene
-// A wave per cluster, a lane per triangle.  Each triangle's positions go out
-// twice: alone (tpos, what setup and raster read) and in its shading record.
-__global__ __launch_bounds__(256) void k_scene(MeshSource m, uint32_t T, float *__restrict__ tpos,
-                                               TriRec *__restrict__ rec, float4 *__restrict__ cbox)
+// A wave per cluster, a lane per triangle.  A lane has read its triangle's indices
+// before it writes the colours, which may take their place.
+__global__ __launch_bounds__(256) void k_scene(MeshSource m, uint32_t T, float *__restrict__ tpos, uint32_t *attr,
+                                               float4 *__restrict__ cbox)
 {
     const uint32_t t = blockIdx.x * 256u + threadIdx.x;
     if (uniform(t & ~63u) >= T) return;
     float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
     if (t < T) {
-        TriRec r = {};
+        size_t vid[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) vid[k] = m.idx[3ull * t + k];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const size_t vid = m.idx[3ull * t + k];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const float x = m.pos[3 * vid + a];
-                r.pos[3 * k + a] = x;
+                const float x = m.pos[3 * vid[k] + a];
                 tpos[9ull * t + 3 * k + a] = x;
                 mn[a] = fminf(mn[a], x);
                 mx[a] = fmaxf(mx[a], x);
             }
             if (m.uv) {
-                r.uv[2 * k] = m.uv[2 * vid];
-                r.uv[2 * k + 1] = m.uv[2 * vid + 1];
+                attr[6ull * t + 2 * k] = __float_as_uint(m.uv[2 * vid[k]]);
+                attr[6ull * t + 2 * k + 1] = __float_as_uint(m.uv[2 * vid[k] + 1]);
             } else {
-                const uint8_t *c = m.col ? m.col + 3 * vid : nullptr;
-                r.col[k] = c ? (uint32_t)c[0] | ((uint32_t)c[1] << 8) | ((uint32_t)c[2] << 16) : 0xFFFFFFu;
+                const uint8_t *c = m.col ? m.col + 3 * vid[k] : nullptr;
+                attr[3ull * t + k] = c ? (uint32_t)c[0] | ((uint32_t)c[1] << 8) | ((uint32_t)c[2] << 16) : 0xFFFFFFu;
             }
         }
-        rec[t] = r;
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a)
@@ -1898,9 +1897,10 @@ __global__ __launch_bounds__(kBandThreads) void k_resolve(const DView *__restric
 // entries has none).  A wave shades STACK bands, one below the other: STACK is
 // 1, 2 or 4, so they lie in one row of tiles.  256 mixed 128 / 256 / 512 px
 // views, 29 M pixels: 1.25 ms a step with one band a wave and the winner read
-// as index, positions and three colours, 1.13 with four and the 64-byte record.
-// Bound by the latency of the record's read and by VALU issue (280 instructions
-// a band, 70 % busy).
+// through its indices, 1.08 with four and its attributes by triangle.  (A 64-byte
+// record of both, half a cache line, took the same and twice a scene's memory.)
+// Bound by the latency of the winner's read and by VALU issue (280 instructions a
+// band, 70 % busy).
 template <int STACK>
 __global__ __launch_bounds__(kBandThreads) void k_resolve_wave(const DView *__restrict__ views,
                                                                const uint32_t *__restrict__ lview,
@@ -1983,9 +1983,9 @@ static void launch_resolve(const LaunchPlan &L, const RasterLaunch &R, hipStream
                        R.nl, L.tile_count, L.tile_off, L.tile_item, R.partial, L.err);
 }
 
-hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, TriRec *rec, float4 *cbox, hipStream_t s)
+hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, uint32_t *attr, float4 *cbox, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_scene, dim3(cdiv(T, 256)), dim3(256), 0, s, m, T, tpos, rec, cbox);
+    hipLaunchKernelGGL(k_scene, dim3(cdiv(T, 256)), dim3(256), 0, s, m, T, tpos, attr, cbox);
     return hipGetLastError();
 }
 

@@ -413,7 +413,7 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         d.T = r.scene->T;
         d.ts_log2 = ts_log2(ts);
         d.tpos = r.scene->tpos;
-        d.rec = r.scene->rec;
+        d.attr = r.scene->attr;
         d.cbox = r.scene->cbox;
         d.rgb = r.rgb;
         d.depth = r.depth;

@@ -62,8 +62,7 @@ hab_status guarded(F &&f)
 struct Scene {
     int device = 0;
     float *tpos = nullptr;      // [T][3][3] vertex positions per triangle
-    TriRec *rec = nullptr;      // [T] records of the shading
-    void *src = nullptr;        // the mesh as uploaded (MeshSource)
+    uint32_t *attr = nullptr;   // vertex colours or texture coordinates per triangle (DView)
     float4 *cbox = nullptr;     // [ceil(T/64)][2] cluster bounding boxes
     uint32_t *inst = nullptr;   // [T] instance id per triangle, or null
     uint32_t *tex = nullptr;    // [th][tw] packed RGB texels, or null
@@ -184,6 +183,9 @@ struct hab_context {
     hipEvent_t fork_ev = nullptr, join_ev = nullptr;
     uint32_t *err = nullptr;          // device error word
     std::vector<habmi::Scene *> scenes;
+    // device memory that scene uploads work in, kept between them (bounded)
+    void *up_mem = nullptr;
+    size_t up_bytes = 0;
     std::vector<habmi::Tuned> tuned;  // autotune table
     std::mutex tune_mu;
     int cu_count = 256;

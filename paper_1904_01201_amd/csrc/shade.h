@@ -10,13 +10,11 @@
 
 namespace habmi {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// The first N 16-byte words of triangle t's record.
+// Triangle t's N attribute words.
 template <int N>
-__device__ __forceinline__ void load_rec(const DView &v, uint32_t t, u32x4 (&q)[N])
+__device__ __forceinline__ void load_attr(const DView &v, uint32_t t, uint32_t (&q)[N])
 {
-    const auto *p = gmem(reinterpret_cast<const u32x4 *>(v.rec + t));
+    const auto *p = gmem(v.attr) + (uint64_t)N * t;
 #pragma unroll
     for (int k = 0; k < N; ++k) q[k] = p[k];
 }
@@ -91,11 +89,11 @@ __device__ __forceinline__ bool resolve(const DView &v, uint32_t key, int i, int
 {
     const uint32_t t = key >> 1;
     const int sub = (int)(key & 1u);
-    u32x4 q[3];
-    load_rec(v, t, q);
-    const float P[9] = {f32(q[0].x), f32(q[0].y), f32(q[0].z), f32(q[0].w), f32(q[1].x),
-                        f32(q[1].y), f32(q[1].z), f32(q[1].w), f32(q[2].x)};
-    const uint32_t k0 = q[2].y, k1 = q[2].z, k2 = q[2].w;
+    float P[9];
+    uint32_t q[3];
+    load_pos(v, t, P);
+    load_attr(v, t, q);
+    const uint32_t k0 = q[0], k1 = q[1], k2 = q[2];
     float w0, w1, w2, x[3], num;
     bool swapped;
     if (sub == 0 && pixel_weights(v, P, i, j, w0, w1, w2, swapped)) {
@@ -184,12 +182,11 @@ __device__ __forceinline__ bool resolve_tex(const DView &v, uint32_t key, int i,
 {
     const uint32_t t = key >> 1;
     const int sub = (int)(key & 1u);
-    u32x4 q[4];
-    load_rec(v, t, q);
-    const float P[9] = {f32(q[0].x), f32(q[0].y), f32(q[0].z), f32(q[0].w), f32(q[1].x),
-                        f32(q[1].y), f32(q[1].z), f32(q[1].w), f32(q[2].x)};
-    const float a0[2] = {f32(q[2].y), f32(q[2].z)}, a1[2] = {f32(q[2].w), f32(q[3].x)},
-                a2[2] = {f32(q[3].y), f32(q[3].z)};
+    float P[9];
+    uint32_t q[6];
+    load_pos(v, t, P);
+    load_attr(v, t, q);
+    const float a0[2] = {f32(q[0]), f32(q[1])}, a1[2] = {f32(q[2]), f32(q[3])}, a2[2] = {f32(q[4]), f32(q[5])};
     float w0, w1, w2, x[2], num;
     bool swapped;
     if (sub == 0 && pixel_weights(v, P, i, j, w0, w1, w2, swapped)) {
