@@ -108,7 +108,10 @@ struct MeshSource {
 
 // Write a scene's triangles out on stream s: positions, attributes (the colours may
 // overwrite the indices) and the bounding box of every kCluster consecutive ones.
-hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, uint32_t *attr, float4 *cbox, hipStream_t s);
+// Adds to *spread, in units of 2^-24, the part of the box of edges `size` that each
+// of these takes, every side grown by `grow`.
+hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, uint32_t *attr, float4 *cbox, float3 size, float grow,
+                        unsigned long long *spread, hipStream_t s);
 
 // Compare recip_rn with the IEEE division 1/x for every float whose bits
 // lie in [lo, hi) (lo < hi <= 0x7F800000), adding the number of differing

@@ -56,7 +56,8 @@ namespace habmi {
 // A wave per cluster, a lane per triangle.  A lane has read its triangle's indices
 // before it writes the colours, which may take their place.
 __global__ __launch_bounds__(256) void k_scene(MeshSource m, uint32_t T, float *__restrict__ tpos, uint32_t *attr,
-                                               float4 *__restrict__ cbox)
+                                               float4 *__restrict__ cbox, float3 size, float grow,
+                                               unsigned long long *__restrict__ spread)
 {
     const uint32_t t = blockIdx.x * 256u + threadIdx.x;
     if (uniform(t & ~63u) >= T) return;
@@ -93,6 +94,10 @@ __global__ __launch_bounds__(256) void k_scene(MeshSource m, uint32_t T, float *
     if (lane_id() == 0) {
         cbox[2 * (t / kCluster)] = make_float4(mn[0], mn[1], mn[2], 0.0f);
         cbox[2 * (t / kCluster) + 1] = make_float4(mx[0], mx[1], mx[2], 0.0f);
+        // in whole units: the sum does not depend on the order
+        const float part = (mx[0] - mn[0] + grow) / (size.x + grow) * ((mx[1] - mn[1] + grow) / (size.y + grow)) *
+                           ((mx[2] - mn[2] + grow) / (size.z + grow));
+        atomicAdd(spread, (unsigned long long)(fminf(part, 1.0f) * 16777216.0f));
     }
 }
 
@@ -1983,9 +1988,10 @@ static void launch_resolve(const LaunchPlan &L, const RasterLaunch &R, hipStream
                        R.nl, L.tile_count, L.tile_off, L.tile_item, R.partial, L.err);
 }
 
-hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, uint32_t *attr, float4 *cbox, hipStream_t s)
+hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, uint32_t *attr, float4 *cbox, float3 size, float grow,
+                        unsigned long long *spread, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_scene, dim3(cdiv(T, 256)), dim3(256), 0, s, m, T, tpos, attr, cbox);
+    hipLaunchKernelGGL(k_scene, dim3(cdiv(T, 256)), dim3(256), 0, s, m, T, tpos, attr, cbox, size, grow, spread);
     return hipGetLastError();
 }
 

@@ -14,6 +14,8 @@ static constexpr uint32_t kDefaultTile = 16;
 // Pixels + triangles / 4 up to which the direct path draws a launch, and a
 // half of a split batch.
 static constexpr uint64_t kDirectSize = 1150 * 1024, kDirectHalf = 740 * 1024;
+// ... and the visits, spread and depth (choose_tiles) up to which it does.
+static constexpr double kVisits = 30000.0, kSpread = 0.2, kDepth = 16.0;
 // Resolve waves that a launch keeps when a wave shades two or four bands one
 // after another (its search and start paid once): two rounds of the 8192 that
 // are resident.  1024 depth frames of 64 x 64 resolve in 32 us with one band a
@@ -323,56 +325,145 @@ uint32_t choose_tile(hab_context *ctx, const Scene *sc, const hab_sensor *s, con
 // ---------------------------------------------------------------- planning
 static inline uint32_t ts_log2(uint32_t ts) { return ts == 8 ? 3u : ts == 16 ? 4u : 5u; }
 
+// How the direct path would draw a launch.
+struct DirectTiles {
+    uint32_t edge = 16, shares = 1;   // tile edge, blocks that share a tile's clusters
+    double visits = 0.0;              // (cluster, tile) pairs it sets up, an estimate
+    double depth = 0.0;               // clusters that a wave draws one after another where the whole scene
+                                      //   falls on few tiles (0: it does not)
+    double spread = 0.0;              // of the launch's triangles (Scene::spread)
+    double density = 0.0;             // pixels a triangle
+};
+
+// The part of the image that the box around a scene takes, if all of it lies in
+// front of the camera (else 1).
+static double covered(const ViewReq &r)
+{
+    const Scene &sc = *r.scene;
+    const float *p = r.pose.position, *R = r.pose.rotation;
+    if (p[0] >= sc.lo[0] && p[0] <= sc.hi[0] && p[1] >= sc.lo[1] && p[1] <= sc.hi[1] && p[2] >= sc.lo[2] && p[2] <= sc.hi[2])
+        return 1.0;
+    double x0 = INFINITY, x1 = -INFINITY, y0 = INFINITY, y1 = -INFINITY;
+    for (int c = 0; c < 8; ++c) {
+        double d[3];
+        for (int a = 0; a < 3; ++a) d[a] = (double)((c >> a) & 1 ? sc.hi[a] : sc.lo[a]) - p[a];
+        const double w = -(R[2] * d[0] + R[5] * d[1] + R[8] * d[2]);
+        if (!(w > r.sensor.near_m)) return 1.0;
+        const double x = r.sensor.f * (R[0] * d[0] + R[3] * d[1] + R[6] * d[2]) / w;
+        const double y = r.sensor.f * (R[1] * d[0] + R[4] * d[1] + R[7] * d[2]) / w;
+        x0 = std::min(x0, x), x1 = std::max(x1, x);
+        y0 = std::min(y0, y), y1 = std::max(y1, y);
+    }
+    const double W = r.sensor.width, H = r.sensor.height;
+    const double w = std::min(x1, W / 2) - std::max(x0, -W / 2), h = std::min(y1, H / 2) - std::max(y0, -H / 2);
+    return std::max(w, 0.0) * std::max(h, 0.0) / (W * H);
+}
+
+// Of a view's clusters about a quarter is in sight, each about as large as an
+// equal part of four times the image, and it meets every tile that it touches;
+// but clusters that spread over the scene (whose 64 triangles are not neighbours)
+// are in sight, and in every tile.
+//
+// The edge follows the largest scene (finer triangles, larger tiles: fewer
+// clusters meet several).  It grows where there are many tiles, but of triangles
+// of many pixels 64-pixel tiles hold too much (a frame of 512 x 512 over 20k
+// triangles: 73 us with 32-pixel tiles, 176 with 64; twelve of 256 x 256 over 60k
+// 189 and 122), and where clusters spread (four of 128 x 128 over 60k shuffled
+// triangles: 113 and 63).  The shares give each wave of a block one or two
+// clusters to draw, up to a round or two of resident blocks.  (One 256 x 256 view
+// of 200k triangles: 64-pixel tiles with 4 / 16 / 64 shares take 105 / 57 / 66 us,
+// 32-pixel tiles with 16 take 56.)
+static DirectTiles choose_tiles(const ViewReq *v, uint32_t n)
+{
+    DirectTiles t;
+    uint32_t max_t = 0;
+    double px = 0.0, tri = 0.0;
+    for (uint32_t k = 0; k < n; ++k) {
+        max_t = std::max(max_t, v[k].scene->T);
+        px += (double)v[k].sensor.width * v[k].sensor.height;
+        tri += v[k].scene->T;
+        t.spread += (double)v[k].scene->T * v[k].scene->spread;
+    }
+    t.spread /= std::max(tri, 1.0);
+    t.density = px / std::max(tri, 1.0);
+    const bool fine = max_t >= 10000;
+    double tiles = 0.0, per_tile = 0.0;   // clusters that meet a tile, over the views
+    auto count = [&]() {
+        tiles = per_tile = t.visits = 0.0;
+        double vt = 0.0, vp = 0.0, vv = 0.0;   // of the view before, often the same
+        for (uint32_t k = 0; k < n; ++k) {
+            const Scene &sc = *v[k].scene;
+            const uint32_t W = v[k].sensor.width, H = v[k].sensor.height;
+            if (!k || v[k - 1].scene != v[k].scene || v[k - 1].sensor.width != W || v[k - 1].sensor.height != H) {
+                const double ncl = cdiv(sc.T, kCluster), seen = std::max(1.0, 0.27 * ncl);
+                const double across = 1.0 + std::sqrt(4.0 * W * H / seen) / t.edge;
+                vt = (double)cdiv(W, t.edge) * cdiv(H, t.edge);
+                vp = std::min(seen * across * across / vt, seen);
+                vv = vt * (vp * (1.0 - sc.spread) + ncl * sc.spread);
+            }
+            tiles += vt;
+            per_tile += vp;
+            t.visits += vv;
+        }
+    };
+    t.edge = max_t >= 128000 || (fine && t.spread > kSpread) ? 64u : fine ? 32u : 16u;
+    for (count(); t.edge < 64 && (tiles > (fine ? 100.0 + 150.0 * t.density : 1024.0) || (t.edge < 32 && t.visits > kVisits)); count())
+        t.edge *= 2;
+    const double waves = t.edge == 64 ? 8 : 4;
+    const double want = std::min(1.5 * per_tile / n / waves, 256.0);
+    const double most = (max_t >= 500000 ? 2048.0 : 1024.0) / std::max(tiles, 1.0);
+    t.shares = (uint32_t)std::max(1.0, std::min(want, most));
+    for (uint32_t k = 0; k < n; ++k) {
+        const double part = covered(v[k]);
+        if (part >= 1.0) continue;
+        // (shares of a tile that touch only a few pixels also wait for each other)
+        const uint32_t W = v[k].sensor.width, H = v[k].sensor.height;
+        const double few = std::max(1.0, part * cdiv(W, t.edge) * cdiv(H, t.edge));
+        t.depth = std::max(t.depth, cdiv(v[k].scene->T, kCluster) / (few * t.shares * waves) +
+                                        (part * W * H < 256.0 ? t.shares / 16.0 : 0.0));
+    }
+    return t;
+}
+
 // Does the direct path draw this launch?  It serves launches that ask for
 // nothing the tile lists alone provide (a tiling, a list capacity, the
 // lane-owned z-test, work counters), while they are small: the tile lists
 // take eight dependent kernels whatever the size, the direct path four, but it
 // sets up a triangle once per tile its cluster meets.  Measured (us a launch,
 // tile lists against direct, by pixels + triangles / 4 in K): one 256 x 256 view
-// of 200k triangles 89 / 49 (113), of 1M 93 / 61 (308), two of 1M 88 / 65 (616),
-// 20 of 203 x 117 over 60k 103 / 87 (757), eight of 256 x 256 over 200k 109 / 106
-// (902), 16 over 20k 118 / 113 (1102), four of 1M 119 / 133 (1232), three 512 x
-// 384 views of 1M 122 / 156 (1308), eight 128 x 96 of 1M 121 / 125 (2049).  The
-// two halves of a split batch overlap, which helps the tile lists more (size of a
-// half): 100 views of 64 x 64 over 20k 140 / 113 (439), 40 of 128 x 128 over 75k
-// 139 / 130 (686), 64 of 96 x 72 over 75k 138 / 154 (802).
-static bool direct_launch(const ViewReq *v, uint32_t n, const PlanOpts &o)
+// of 200k triangles 92 / 61 (113), of 1M 87 / 51 (308), two of 1M 93 / 74 (616),
+// twelve of 256 x 256 over 60k 119 / 122 (943), 16 of 128 x 128 over 200k 110 / 92
+// (1044), four of 1M 119 / 133 (1232), three 512 x 384 views of 1M 122 / 156
+// (1308), eight 128 x 96 of 1M 121 / 125 (2049).  The two halves of a split batch
+// overlap, which helps the tile lists more, so theirs is the lower limit (sizes of
+// a half: 100 views of 64 x 64 over 20k 140 / 113 (439), 40 of 128 x 128 over 75k
+// 139 / 130 (686), 64 of 96 x 72 over 75k 138 / 154 (802)).
+//
+// Nor where its work is out of proportion to that size.  A visit takes about a
+// nanosecond, and the lists about 30 us more than the direct path without any,
+// and more again where a triangle has many pixels.  With each scene's triangles
+// shuffled: one 512 x 512 view of 1M 114 / 805 (966k visits), one 256 x 256 view
+// of 200k 84 / 117 (49k), eight of 128 x 128 over 60k 94 / 91 (29k), one 203 x 117
+// of 200k 79 / 75 (20k); three 512 x 512 of a 2k-triangle room, 131 pixels a
+// triangle, 190 / 83 (24k).  Spread clusters of several pixels a triangle also
+// leave whole tiles to a wave: one 256 x 256 view of 20k shuffled triangles 89 / 117.
+// A scene that falls on few tiles leaves the other tiles' blocks without work: within
+// two pixels of a 256 x 256 view 1M triangles 58 / 108 (a depth of 32), 60k 53 / 100
+// (46), in a fifteenth of a 512 x 512 one 1M 73 / 112 (23); within a fortieth of a
+// 128 x 128 view 200k 61 / 33 (8), of a 256 x 256 one 62 / 48 (25).
+static bool direct_launch(const ViewReq *v, uint32_t n, const PlanOpts &o, DirectTiles *t)
 {
     if (o.tile_lists || o.tile_size || o.bin_factor > 0.0f || o.tile_cap || o.lane_owned_z || o.count_work) return false;
     uint64_t size = 0;
-    for (uint32_t k = 0; k < n; ++k)
+    uint32_t max_t = 0;
+    for (uint32_t k = 0; k < n; ++k) {
         size += (uint64_t)v[k].sensor.width * v[k].sensor.height + v[k].scene->T / 4;
-    return size <= (o.half ? kDirectHalf : kDirectSize);
-}
-
-// Tile edge and shares of a direct launch.  The edge follows the largest
-// scene (finer triangles, larger tiles: fewer clusters meet several), and
-// grows where there are many tiles anyway.  The shares give each wave of a
-// block one or two clusters to draw, up to a round or two of resident blocks:
-// of a view's clusters about a quarter is in sight, each about as large as an
-// equal part of four times the image, and it meets every tile that it touches.
-// (One 256 x 256 view of 200k triangles: 64-pixel tiles with 4 / 16 / 64 shares
-// take 105 / 57 / 66 us, 32-pixel tiles with 16 take 56.)
-static void choose_tiles(const std::vector<DView> &dv, uint32_t max_t, uint32_t *edge, uint32_t *shares)
-{
-    const uint32_t n = (uint32_t)dv.size();
-    uint32_t e = max_t >= 128000 ? 64u : max_t >= 10000 ? 32u : 16u;
-    uint64_t tiles = 0;
-    for (;; e *= 2) {
-        tiles = 0;
-        for (const DView &d : dv) tiles += (uint64_t)cdiv(d.W, e) * cdiv(d.H, e);
-        if (e == 64 || tiles <= (max_t >= 10000 ? 200u : 1024u)) break;
+        max_t = std::max(max_t, v[k].scene->T);
     }
-    double per_tile = 0.0;   // clusters that meet a tile, over the launch
-    for (const DView &d : dv) {
-        const double seen = std::max(1.0, 0.27 * cdiv(d.T, kCluster));
-        const double across = 1.0 + std::sqrt(4.0 * d.W * d.H / seen) / e;
-        per_tile += std::min(seen * across * across / ((double)cdiv(d.W, e) * cdiv(d.H, e)), seen);
-    }
-    const double want = std::min(1.5 * per_tile / n / (e == 64 ? 8 : 4), 256.0);
-    const double most = (max_t >= 500000 ? 2048.0 : 1024.0) / (double)std::max<uint64_t>(tiles, 1);
-    *edge = e;
-    *shares = (uint32_t)std::max(1.0, std::min(want, most));
+    if (size > (o.half ? kDirectHalf : kDirectSize)) return false;
+    *t = choose_tiles(v, n);
+    if (max_t >= 10000 && t->spread > kSpread) return t->density < 1.0 && t->visits <= kVisits;
+    return t->visits <= kVisits + 8000.0 * std::sqrt(std::min(t->density, 64.0)) && t->depth <= kDepth;
 }
 
 hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_t n,
@@ -393,7 +484,8 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         lview[c].clear();
         lpre[c].clear();
     }
-    const bool direct = direct_launch(v, n, o);
+    DirectTiles dt;
+    const bool direct = direct_launch(v, n, o, &dt);
     uint64_t tile_total = 0, surv_total = 0, bin_total = 0, pair_total = 0;
     for (uint32_t k = 0; k < n; ++k) {
         const ViewReq &r = v[plan.order[k]];
@@ -561,7 +653,8 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
             d.zoff_hi = (uint32_t)(znum >> 32);
             znum += ((uint64_t)d.W * d.H + 1) & ~1ull;
         }
-        choose_tiles(dv, max_t, &L.tile_edge, &L.shares);
+        L.tile_edge = dt.edge;
+        L.shares = dt.shares;
         tpre.clear();
         uint64_t pre = 0;
         for (uint32_t k : lview[c0]) {

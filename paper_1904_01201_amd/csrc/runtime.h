@@ -67,6 +67,9 @@ struct Scene {
     uint32_t *inst = nullptr;   // [T] instance id per triangle, or null
     uint32_t *tex = nullptr;    // [th][tw] packed RGB texels, or null
     uint32_t tw = 0, th = 0;
+    // how far its clusters reach: the mean over them of the part of the scene's box
+    // that each one's box takes (sides grown by a twentieth of the longest), 0 .. 1
+    float spread = 0.0f;
     uint32_t V = 0, T = 0;
     float lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
     uint64_t bytes = 0;
