@@ -1208,6 +1208,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPe
     // overflow tiles come first, each as `parts` items that share its scan by
     // runs: about two items a resident wave in all
     const uint32_t nover = uniform(q->total[kOverTotal]);
+    if (blockIdx.x >= cap && !nover) return;
     const uint32_t parts = nover ? max(1u, min(2u * gridDim.x / nover, 64u)) : 1u;
     const uint32_t nfirst = nover * parts, total = nfirst + q->total[cls];
     const uint32_t nq = min(kQueues, gridDim.x), x = blockIdx.x % nq;
@@ -1324,25 +1325,40 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaveWavesPe
                 const int l = __ffsll((long long)u) - 1;
                 auto from = [&](int y) { return __builtin_amdgcn_readlane(y, l); };
                 auto fromf = [&](float y) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y), l)); };
-                const long long C0 = join64(from(rx.hi0), from(r.c0)), C1 = join64(from(rx.hi1), from(r.c1)),
-                                C2 = join64(from(rx.hi2), from(r.c2));
                 const int x0 = from(dx[0]), x1 = from(dx[1]), x2 = from(dx[2]);
                 const int y0 = from(dy[0]), y1 = from(dy[1]), y2 = from(dy[2]);
-                const uint32_t no = (uint32_t)from((int)notown), nkey = (uint32_t)from((int)r.nkey);
+                const uint32_t fl = (uint32_t)from((int)r.flags), nkey = (uint32_t)from((int)r.nkey);
                 const float w0 = fromf(r.rw0), w1 = fromf(r.rw1), w2 = fromf(r.rw2), ia = fromf(r.invA);
-                const int j0 = from(box[2]), j1 = from(box[3]);
+                const int s0 = from(box[2]) >> 2, s1 = from(box[3]) >> 2;   // of four rows: eight blocks
+                const int px = (int)((gi & 3u) * 4u + pxl), py = 4 * s0 + (int)((gi >> 2) * 2u + pyl);
+                // E: this lane's edge values in the first step, D: on to the next
+                auto steps = [&](auto E0, auto E1, auto E2, auto D0, auto D1, auto D2) {
 #pragma unroll 1
-                for (int s = j0 >> 2; s <= j1 >> 2; ++s) {   // four rows: eight blocks
-                    const int px = (int)((gi & 3u) * 4u + pxl), py = 4 * s + (int)((gi >> 2) * 2u + pyl);
-                    const long long E0 = C0 + (long long)x0 * (256 * py) - (long long)y0 * (256 * px);
-                    const long long E1 = C1 + (long long)x1 * (256 * py) - (long long)y1 * (256 * px);
-                    const long long E2 = C2 + (long long)x2 * (256 * py) - (long long)y2 * (256 * px);
-                    const bool cov = E0 >= (long long)(no & 0xFFu) && E1 >= (long long)((no >> 8) & 0xFFu) &&
-                                     E2 >= (long long)((no >> 16) & 0xFFu);
-                    if (count)
-                        ncov += (uint32_t)__popcll(__ballot(cov && ti0 + px < (int)v.W && tj0 + py < (int)v.H));
-                    if (cov)
-                        put((uint32_t)s * 512u + lane * 8u, ((float)E0 * w0 + (float)E1 * w1) + (float)E2 * w2, ia, nkey);
+                    for (int s = s0, y = py; s <= s1; ++s, y += 4) {
+                        const bool cov = E0 >= (int)(fl & 0xFFu) && E1 >= (int)((fl >> 8) & 0xFFu) &&
+                                         E2 >= (int)((fl >> 16) & 0xFFu);
+                        if (count) ncov += (uint32_t)__popcll(__ballot(cov && ti0 + px < (int)v.W && tj0 + y < (int)v.H));
+                        if (cov)
+                            put((uint32_t)s * 512u + lane * 8u, ((float)E0 * w0 + (float)E1 * w1) + (float)E2 * w2, ia, nkey);
+                        E0 += D0;
+                        E1 += D1;
+                        E2 += D2;
+                    }
+                };
+                const int c0 = from(r.c0), c1 = from(r.c1), c2 = from(r.c2), P = 256 * px, Q = 256 * py;
+                if (!(fl & kSlow)) {
+                    // every edge value in the tile lies within +-2^29, so a step is
+                    // less than 2^29 and the one behind the last fits as well
+                    auto at = [&](int c, int dX, int dY) {
+                        return (int)((uint32_t)c + (uint32_t)__mul24(dX, Q) - (uint32_t)__mul24(dY, P));
+                    };
+                    steps(at(c0, x0, y0), at(c1, x1, y1), at(c2, x2, y2), x0 * 1024, x1 * 1024, x2 * 1024);
+                } else {
+                    auto at = [&](int hi, int c, int dX, int dY) {
+                        return join64(hi, c) + (long long)dX * Q - (long long)dY * P;
+                    };
+                    steps(at(from(rx.hi0), c0, x0, y0), at(from(rx.hi1), c1, x1, y1), at(from(rx.hi2), c2, x2, y2),
+                          (long long)x0 * 1024, (long long)x1 * 1024, (long long)x2 * 1024);
                 }
             }
         };
