@@ -753,9 +753,13 @@ hab_status hab_actuate(hab_context *ctx, const hab_nav *const *navs, uint32_t n,
         const NavDesc *dt = static_cast<const NavDesc *>(ws.arena);
         const uint32_t *di = reinterpret_cast<const uint32_t *>(static_cast<char *>(ws.arena) + ctx->act_last_off);
         // Few agents: a wave each, the shortest way through a pass; many: fewer
-        // lanes each, so that one round of waves serves them all.  us a call at
-        // 64 / 8,192 / 16,384 / 65,536 agents: <64, 4> 24 / 46 / 69 / 202,
-        // <32, 16> 32 / 51 / 60 / 141, <16, 32> 45 / 71 / 76 / 135.
+        // lanes each, so that one round of waves serves them all, and a block's
+        // threads at work where agents only turn.  us a call against the bench
+        // meshes' cross-sections at 64 / 8,192 / 16,384 / 65,536 agents: <64, 4>
+        // 24 / 46 / 69 / 202, <32, 16> 32 / 51 / 60 / 141, <16, 32> 45 / 71 / 76 /
+        // 135.  At 131,072 / 1,048,576 agents, all forward along plain walls
+        // <16, 32> 88 / 551, <16, 128> 78 / 464, <8, 256> 69 / 310; all turning
+        // 15 / 56, 12 / 30, 12 / 29; over meshes 118 / 780, 101 / 621, 110 / 495.
         auto go = [&](auto kernel, uint32_t per_block) {
             in_pieces(n, per_block, kActBlock, [&](uint32_t first, uint32_t count, uint32_t blocks) {
                 hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kActBlock), 0, stream, dt, di + first, count, agents + first,
@@ -765,7 +769,9 @@ hab_status hab_actuate(hab_context *ctx, const hab_nav *const *navs, uint32_t n,
         };
         if (n <= 8192) go(k_actuate<64, 4>, 4u);
         else if (n <= 32768) go(k_actuate<32, 16>, 16u);
-        else go(k_actuate<16, 32>, 32u);
+        else if (n <= 65536) go(k_actuate<16, 32>, 32u);
+        else if (n <= 131072) go(k_actuate<16, 128>, 128u);
+        else go(k_actuate<8, 256>, 256u);
         HAB_HIP(hipGetLastError());
         HAB_HIP(hipEventRecord(ws.done, stream));
         ws.has_done = true;
