@@ -40,10 +40,9 @@ constexpr uint32_t kNavMaxDim = 1024;  // cells per axis (the cell grows beyond)
 
 // What the kernel needs of one obstacle set.
 struct alignas(16) NavDesc {
-    const float4 *seg;          // [n] (x0, z0, x1, z1)
     const uint32_t *cell_start; // [gx * gz + 1]
     const uint32_t *items;      // segment indices, per cell
-    const float4 *iseg;         // their segments, per cell
+    const float4 *iseg;         // their segments (x0, z0, x1, z1), per cell
     float ox, oz;               // grid origin
     float inv_h, h;             // 1 / cell edge, cell edge
     uint32_t gx, gz;            // cells per axis (0: no segments)
@@ -54,7 +53,7 @@ struct alignas(16) NavDesc {
 struct hab_nav {
     int device = 0;
     uint32_t n = 0;
-    void *mem = nullptr;        // segments, cell starts and items in one allocation
+    void *mem = nullptr;        // segments, cell starts, items and their segments in one allocation
     NavDesc d{};
 };
 
@@ -70,6 +69,14 @@ struct ActParams {
     double radius, step, tc, ts;
     float cam_h;
 };
+
+// Copies of the items' segments, cell by cell.
+__global__ __launch_bounds__(kActBlock) void k_nav_copies(const float4 *__restrict__ seg, const uint32_t *__restrict__ items,
+                                                          uint32_t n, float4 *__restrict__ iseg)
+{
+    for (uint64_t i = (uint64_t)blockIdx.x * kActBlock + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kActBlock)
+        iseg[i] = seg[items[i]];
+}
 
 // Contact of the disc at p moving by d (a = |d|^2 > 0) with segment j;
 // keeps the first contact in the order (t, 3 j + kind), kind 0 for the
@@ -588,7 +595,8 @@ static hab_status nav_build(hab_context *ctx, const float *segments, uint32_t nu
         // or a tessellated mesh's short cross-section pieces), larger when
         // the extent needs more than kNavMaxDim cells per axis
         NavDesc d{};
-        std::vector<uint32_t> start, items;
+        std::vector<uint32_t> host;   // segments, cell starts, items, as they lie in device memory
+        size_t o_start = 0, o_items = 0;
         if (num_segments) {
             double lo[2] = {INFINITY, INFINITY}, hi[2] = {-INFINITY, -INFINITY};
             for (uint32_t j = 0; j < num_segments; ++j)
@@ -625,40 +633,44 @@ static hab_status nav_build(hab_context *ctx, const float *segments, uint32_t nu
                 for (uint32_t cz = z0; cz <= z1; ++cz)
                     for (uint32_t cx = x0; cx <= x1; ++cx) lists[(size_t)cz * d.gx + cx].push_back(j);
             }
-            start.assign(lists.size() + 1, 0);
+            o_start = (4ull * num_segments + 63) & ~(size_t)63;   // in words
+            o_items = (o_start + lists.size() + 1 + 63) & ~(size_t)63;
+            host.resize(o_items);
+            std::memcpy(host.data(), segments, 16ull * num_segments);
             for (size_t c = 0; c < lists.size(); ++c) {
-                start[c + 1] = start[c] + (uint32_t)lists[c].size();
-                items.insert(items.end(), lists[c].begin(), lists[c].end());
+                host[o_start + c + 1] = host[o_start + c] + (uint32_t)lists[c].size();
+                host.insert(host.end(), lists[c].begin(), lists[c].end());
             }
         }
-        const size_t bseg = 16ull * num_segments, bstart = 4ull * start.size(), bitems = 4ull * items.size();
-        const size_t o_start = (bseg + 255) & ~(size_t)255, o_items = (o_start + bstart + 255) & ~(size_t)255;
-        const size_t o_iseg = (o_items + bitems + 255) & ~(size_t)255, biseg = 16ull * items.size();
-        std::vector<float> iseg(4 * items.size());
-        for (size_t i = 0; i < items.size(); ++i) std::memcpy(&iseg[4 * i], segments + 4ull * items[i], 16);
+        const size_t o_iseg = (host.size() + 63) & ~(size_t)63, ni = host.size() - o_items;
         DeviceGuard g(ctx->device);
         if (!g.ok) return HAB_ERR_DEVICE;
         hab_nav *n = new hab_nav();
         n->device = ctx->device;
         n->n = num_segments;
         if (num_segments) {
-            if (!dev_alloc(&n->mem, o_iseg + biseg)) {
+            if (!dev_alloc(&n->mem, 4 * o_iseg + 16 * ni)) {
                 delete n;
                 return HAB_ERR_OUT_OF_MEMORY;
             }
-            char *m = static_cast<char *>(n->mem);
-            if (hipMemcpy(m, segments, bseg, hipMemcpyHostToDevice) != hipSuccess ||
-                hipMemcpy(m + o_start, start.data(), bstart, hipMemcpyHostToDevice) != hipSuccess ||
-                (bitems && (hipMemcpy(m + o_items, items.data(), bitems, hipMemcpyHostToDevice) != hipSuccess ||
-                            hipMemcpy(m + o_iseg, iseg.data(), biseg, hipMemcpyHostToDevice) != hipSuccess))) {
+            // the device adds the items' segments
+            uint32_t *const m = static_cast<uint32_t *>(n->mem);
+            d.cell_start = m + o_start;
+            d.items = m + o_items;
+            float4 *const iseg = reinterpret_cast<float4 *>(m + o_iseg);
+            d.iseg = iseg;
+            hipError_t e = hipMemcpy(m, host.data(), 4 * host.size(), hipMemcpyHostToDevice);
+            if (e == hipSuccess) {
+                hipLaunchKernelGGL(k_nav_copies, dim3((uint32_t)std::min<size_t>(ni / kActBlock + 1, 1u << 16)), dim3(kActBlock), 0, 0,
+                                   reinterpret_cast<const float4 *>(m), d.items, (uint32_t)ni, iseg);
+                e = hipGetLastError();
+            }
+            if (e == hipSuccess) e = hipStreamSynchronize(0);
+            if (e != hipSuccess) {
                 dev_free(n->mem);
                 delete n;
                 return HAB_ERR_DEVICE;
             }
-            d.seg = reinterpret_cast<const float4 *>(m);
-            d.cell_start = reinterpret_cast<const uint32_t *>(m + o_start);
-            d.items = reinterpret_cast<const uint32_t *>(m + o_items);
-            d.iseg = reinterpret_cast<const float4 *>(m + o_iseg);
         }
         n->d = d;
         ctx->navs.push_back(n);
@@ -850,7 +862,7 @@ hab_status hab_nav_segments(hab_context *ctx, const hab_nav *nav, float *out, ui
         if (!m) return HAB_OK;
         DeviceGuard g(ctx->device);
         if (!g.ok) return HAB_ERR_DEVICE;
-        HAB_HIP(hipMemcpy(out, nav->d.seg, 16ull * m, hipMemcpyDeviceToHost));
+        HAB_HIP(hipMemcpy(out, nav->mem, 16ull * m, hipMemcpyDeviceToHost));
         return HAB_OK;
     });
 }
