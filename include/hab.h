@@ -174,8 +174,11 @@ typedef struct {
  * changes any output bit.
  *
  * A small launch with none of them set (and no statistics asked for) is drawn
- * without tile lists, in about half the time; a tile size, bin factor, tile
- * cap or HAB_RENDER_LANE_OWNED_Z always takes the tile lists.
+ * without tile lists: in about half the time for one small view, in nearly the
+ * same at the limit.  Not so a launch whose work is out of proportion to its
+ * size: triangles in an order that scatters neighbours, or a scene seen on few
+ * pixels.  A tile size, bin factor, tile cap or HAB_RENDER_LANE_OWNED_Z always
+ * takes the tile lists.
  *
  * A large batch of 32 or more views is rendered as two launch sequences over
  * interleaved halves (views 0, 2, 4, ... and 1, 3, 5, ...): one on the

@@ -435,9 +435,9 @@ static DirectTiles choose_tiles(const ViewReq *v, uint32_t n)
 // twelve of 256 x 256 over 60k 119 / 122 (943), 16 of 128 x 128 over 200k 110 / 92
 // (1044), four of 1M 119 / 133 (1232), three 512 x 384 views of 1M 122 / 156
 // (1308), eight 128 x 96 of 1M 121 / 125 (2049).  The two halves of a split batch
-// overlap, which helps the tile lists more, so theirs is the lower limit (sizes of
-// a half: 100 views of 64 x 64 over 20k 140 / 113 (439), 40 of 128 x 128 over 75k
-// 139 / 130 (686), 64 of 96 x 72 over 75k 138 / 154 (802)).
+// overlap, so theirs is the lower limit (back to back and with a wait, over 2k
+// triangles, by the size of a half: 1025 views of 24 x 20 210 / 200 and 280 / 243
+// (490), 1500 247 / 244 and 330 / 300 (718), 2048 295 / 304 and 399 / 370 (980)).
 //
 // Nor where its work is out of proportion to that size.  A visit takes about a
 // nanosecond, and the lists about 30 us more than the direct path without any,
@@ -905,9 +905,23 @@ hab_status ensure_aux(hab_context *ctx)
 // 142 / 156 and 173 / 221; 32 of 256 x 256 over 100k to 1M (6) 198 / 205 and
 // 227 / 278; 64 of 160 x 160 over 100k to 800k (7) 239 / 239 and 271 / 307; the
 // same 48 of 256 x 256 (9) 279 / 270 and 309 / 341, 64 (12) 374 / 354 and 403 /
-// 413, 128 (24) 601 / 580 and 634 / 586.  With more views the chain of small
-// kernels grows: 120 of 96 x 72 (3.8) 177 / 172 and 208 / 253, 100 of 100 x 80
-// (5.3) 190 / 178 and 219 / 264, 128 of 64 x 64 over 60k (2.4) 135 / 139.
+// 413, 128 (24) 601 / 580 and 634 / 586.
+//
+// With more views the chain of small kernels grows, and two sequences win by a
+// few percent from about 3 million on, back to back; a caller that waits for each
+// launch loses more by them until there is about three times as much to do.  The
+// line serves launches that follow each other: over 200k triangles, 81 of 128 x
+// 128 (5.3) 212 / 196 and 244 / 269; 100 of 100 x 80 (5.6) 206 / 191 and 238 /
+// 268; 120 of 96 x 72 (6.6) 237 / 233 and 269 / 296; 128 of 64 x 64 (6.8) 212 /
+// 199 and 246 / 272; but over 60k 128 of 64 x 64 (2.4) 135 / 139.
+//
+// Above 1024 views always two, right but for the smallest: over 20k triangles
+// 1100 of 64 x 64 (9.7) 420 / 380 and 543 / 509, 2048 (18) 711 / 621 and 923 /
+// 813, 2048 of 24 x 20 (11) 465 / 413 and 675 / 589; over 2k 2048 of 64 x 64
+// (9.2) 394 / 343 and 604 / 549, 4096 of 64 x 64 (18) 710 / 606 and 1117 / 970;
+// but 1100 of 64 x 64 (5) 236 / 242 and 359 / 390, 2048 of 24 x 20 (2) 248 / 316
+// and 457 / 428, and 1025 of 24 x 20 (1) 119 / 190 and 210 / 243, which the direct
+// path draws.
 bool split_batch(const ViewReq *v, uint32_t n)
 {
     constexpr uint64_t kSplitSize = 8192 * 1024, kSplitManySize = 3072 * 1024;
