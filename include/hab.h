@@ -173,10 +173,10 @@ typedef struct {
  * flags: HAB_RENDER_* bits (others: HAB_ERR_INVALID_ARG).  None of these
  * changes any output bit.
  *
- * A small launch with none of them set (and no statistics asked for) is drawn
- * without tile lists: in about half the time for one small view, in nearly the
- * same at the limit.  Not so a launch whose work is out of proportion to its
- * size: triangles in an order that scatters neighbours, or a scene seen on few
+ * A small launch with none of them set (and no statistics asked for), or one of
+ * triangles of many pixels, is drawn without tile lists: in about half the time
+ * for one small view, in nearly the same at the limit.  Not so a launch whose
+ * work is out of proportion to its size: triangles in an order that scatters neighbours, or a scene seen on few
  * pixels.  A tile size, bin factor, tile cap or HAB_RENDER_LANE_OWNED_Z always
  * takes the tile lists.
  *

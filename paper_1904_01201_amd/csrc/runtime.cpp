@@ -12,10 +12,12 @@ namespace habmi {
 static constexpr float kDefaultBinFactor = 2.0f;
 static constexpr uint32_t kDefaultTile = 16;
 // Pixels + triangles / 4 up to which the direct path draws a launch, and a
-// half of a split batch.
+// half of a split batch; above kDense pixels a triangle a launch may be larger.
 static constexpr uint64_t kDirectSize = 1150 * 1024, kDirectHalf = 740 * 1024;
 // ... and the visits, spread and depth (choose_tiles) up to which it does.
-static constexpr double kVisits = 30000.0, kSpread = 0.2, kDepth = 16.0;
+static constexpr double kVisits = 30000.0, kSpread = 0.2, kDepth = 16.0, kDense = 6.0;
+// Triangles from which the largest scene of a launch counts as fine, and its clusters, where they spread, as many.
+static constexpr uint32_t kFine = 10000, kSpreadMost = 7000;
 // Resolve waves that a launch keeps when a wave shades two or four bands one
 // after another (its search and start paid once): two rounds of the 8192 that
 // are resident.  1024 depth frames of 64 x 64 resolve in 32 us with one band a
@@ -368,7 +370,9 @@ static double covered(const ViewReq &r)
 // clusters meet several).  It grows where there are many tiles, but of triangles
 // of many pixels 64-pixel tiles hold too much (a frame of 512 x 512 over 20k
 // triangles: 73 us with 32-pixel tiles, 176 with 64; twelve of 256 x 256 over 60k
-// 189 and 122), and where clusters spread (four of 128 x 128 over 60k shuffled
+// 189 and 122; five of 512 x 512 over 2k 89 and 149), and where clusters spread
+// (one of 128 x 128 over 9.7k shuffled triangles: 70 and 52, 101 with 16-pixel
+// tiles, but with half of them in order 62 and 64; four of 128 x 128 over 60k shuffled
 // triangles: 113 and 63).  The shares give each wave of a block one or two
 // clusters to draw, up to a round or two of resident blocks.  (One 256 x 256 view
 // of 200k triangles: 64-pixel tiles with 4 / 16 / 64 shares take 105 / 57 / 66 us,
@@ -386,7 +390,7 @@ static DirectTiles choose_tiles(const ViewReq *v, uint32_t n)
     }
     t.spread /= std::max(tri, 1.0);
     t.density = px / std::max(tri, 1.0);
-    const bool fine = max_t >= 10000;
+    const bool fine = max_t >= kFine;
     double tiles = 0.0, per_tile = 0.0;   // clusters that meet a tile, over the views
     auto count = [&]() {
         tiles = per_tile = t.visits = 0.0;
@@ -406,8 +410,13 @@ static DirectTiles choose_tiles(const ViewReq *v, uint32_t n)
             t.visits += vv;
         }
     };
-    t.edge = max_t >= 128000 || (fine && t.spread > kSpread) ? 64u : fine ? 32u : 16u;
-    for (count(); t.edge < 64 && (tiles > (fine ? 100.0 + 150.0 * t.density : 1024.0) || (t.edge < 32 && t.visits > kVisits)); count())
+    auto most_tiles = [&](uint32_t edge) {
+        const double by_density = 100.0 + 150.0 * t.density;
+        return fine ? by_density : edge < 32 ? 1024.0 : std::max(1024.0, by_density);
+    };
+    const bool mixed = t.spread > kSpread && (fine || (t.spread > 4.0 * kSpread && max_t >= kSpreadMost && t.density < 8.0));
+    t.edge = max_t >= 128000 || mixed ? 64u : fine ? 32u : 16u;
+    for (count(); t.edge < 64 && (tiles > most_tiles(t.edge) || (t.edge < 32 && t.visits > kVisits)); count())
         t.edge *= 2;
     const double waves = t.edge == 64 ? 8 : 4;
     const double want = std::min(1.5 * per_tile / n / waves, 256.0);
@@ -416,11 +425,13 @@ static DirectTiles choose_tiles(const ViewReq *v, uint32_t n)
     for (uint32_t k = 0; k < n; ++k) {
         const double part = covered(v[k]);
         if (part >= 1.0) continue;
-        // (shares of a tile that touch only a few pixels also wait for each other)
-        const uint32_t W = v[k].sensor.width, H = v[k].sensor.height;
-        const double few = std::max(1.0, part * cdiv(W, t.edge) * cdiv(H, t.edge));
-        t.depth = std::max(t.depth, cdiv(v[k].scene->T, kCluster) / (few * t.shares * waves) +
-                                        (part * W * H < 256.0 ? t.shares / 16.0 : 0.0));
+        // (a cluster of triangles of half a pixel and more takes four times as long as one whose triangles mostly
+        // cover none, and the lists of a large image take longer too; shares of a tile that touch only a few pixels
+        // also wait for each other)
+        const uint32_t W = v[k].sensor.width, H = v[k].sensor.height, T = v[k].scene->T;
+        const double few = std::max(1.0, part * cdiv(W, t.edge) * cdiv(H, t.edge)), seen = part * W * H;
+        const double each = (1.0 + std::min(3.4, 6.8 * seen / std::max(T, 1u))) / (1.0 + (double)W * H / 1048576.0);
+        t.depth = std::max(t.depth, each * cdiv(T, kCluster) / (few * t.shares * waves) + (seen < 256.0 ? t.shares / 16.0 : 0.0));
     }
     return t;
 }
@@ -439,6 +450,13 @@ static DirectTiles choose_tiles(const ViewReq *v, uint32_t n)
 // triangles, by the size of a half: 1025 views of 24 x 20 210 / 200 and 280 / 243
 // (490), 1500 247 / 244 and 330 / 300 (718), 2048 295 / 304 and 399 / 370 (980)).
 //
+// Where a triangle has many pixels the lists are slow, a wave taking each 16-pixel
+// tile however long its triangles, and the limit rises with the pixels a triangle:
+// five of 512 x 512 over 2k triangles (1310) 210 / 89, 16 (4194) 301 / 186, 48 of
+// 256 x 256 (3145) 204 / 155; six of 512 x 512 over 20k (1573; 13 pixels) 211 / 160,
+// ten (2621) 255 / 220, twelve (3146) 258 / 249; but 20 of 256 x 256 over 10k (1311;
+// 6.6 pixels) 163 / 165, five of 512 x 512 over 40k (1311; 6.6) 153 / 159.
+//
 // Nor where its work is out of proportion to that size.  A visit takes about a
 // nanosecond, and the lists about 30 us more than the direct path without any,
 // and more again where a triangle has many pixels.  With each scene's triangles
@@ -446,23 +464,30 @@ static DirectTiles choose_tiles(const ViewReq *v, uint32_t n)
 // of 200k 84 / 117 (49k), eight of 128 x 128 over 60k 94 / 91 (29k), one 203 x 117
 // of 200k 79 / 75 (20k); three 512 x 512 of a 2k-triangle room, 131 pixels a
 // triangle, 190 / 83 (24k).  Spread clusters of several pixels a triangle also
-// leave whole tiles to a wave: one 256 x 256 view of 20k shuffled triangles 89 / 117.
+// leave whole tiles to a wave: one 256 x 256 view of 20k shuffled triangles 89 / 117,
+// 24 over 7.5k triangles, half of them shuffled, 167 / 222.
 // A scene that falls on few tiles leaves the other tiles' blocks without work: within
-// two pixels of a 256 x 256 view 1M triangles 58 / 108 (a depth of 32), 60k 53 / 100
-// (46), in a fifteenth of a 512 x 512 one 1M 73 / 112 (23); within a fortieth of a
-// 128 x 128 view 200k 61 / 33 (8), of a 256 x 256 one 62 / 48 (25).
+// two pixels of a 256 x 256 view 1M triangles 58 / 108 (a depth of 31), 60k 53 / 100
+// (45), within a fortieth of a 128 x 128 view 200k 61 / 33 (8), of four 512 x 512
+// views 2k 80 / 56 (16), 5k 86 / 75 (10), 20k 88 / 141 (39).
 static bool direct_launch(const ViewReq *v, uint32_t n, const PlanOpts &o, DirectTiles *t)
 {
     if (o.tile_lists || o.tile_size || o.bin_factor > 0.0f || o.tile_cap || o.lane_owned_z || o.count_work) return false;
-    uint64_t size = 0;
+    uint64_t size = 0, px = 0, tri = 0;
     uint32_t max_t = 0;
     for (uint32_t k = 0; k < n; ++k) {
-        size += (uint64_t)v[k].sensor.width * v[k].sensor.height + v[k].scene->T / 4;
+        const uint64_t view = (uint64_t)v[k].sensor.width * v[k].sensor.height;
+        size += view + v[k].scene->T / 4;
+        px += view;
+        tri += v[k].scene->T;
         max_t = std::max(max_t, v[k].scene->T);
     }
-    if (size > (o.half ? kDirectHalf : kDirectSize)) return false;
+    const double dense = std::max(1.0, (double)px / (kDense * std::max<uint64_t>(tri, 1)));
+    if ((double)size > (o.half ? (double)kDirectHalf : kDirectSize * dense)) return false;
     *t = choose_tiles(v, n);
-    if (max_t >= 10000 && t->spread > kSpread) return t->density < 1.0 && t->visits <= kVisits;
+    if (max_t >= kSpreadMost && max_t < kFine && t->spread > kSpread && t->edge == 64 && t->visits > 5000.0 * std::sqrt(t->density))
+        return false;
+    if (max_t >= kFine && t->spread > kSpread) return t->density < 1.0 && t->visits <= kVisits;
     return t->visits <= kVisits + 8000.0 * std::sqrt(std::min(t->density, 64.0)) && t->depth <= kDepth;
 }
 

@@ -22,7 +22,7 @@ def ctx():
 def scenes(ctx):
     """name -> (generated scene, its handle); *_sh: triangles in random order."""
     made = {"room": make_room(seed=11)}
-    for t in (20_000, 60_000, 200_000, 1_000_000):
+    for t in (5_000, 9_700, 20_000, 60_000, 200_000, 1_000_000):
         made[f"apt{t}"] = make_apartment(seed=21, target_T=t, jitter_sigma=0.01)
     out = {k: (s, ctx.upload_scene(s)) for k, s in made.items()}
     for k, s in made.items():
@@ -48,15 +48,22 @@ CASES = [
     ("apt200000_sh", 3, 512, 512, None, False), ("apt200000_sh", 16, 128, 128, None, False),
     ("apt60000_sh", 1, 512, 512, None, False), ("apt20000_sh", 1, 512, 512, None, False),
     ("apt60000", 1, 256, 256, 400.0, False), ("apt1000000", 1, 256, 256, 400.0, False), ("apt1000000", 1, 512, 512, 40.0, False),
-    ("apt60000", 1, 256, 256, 8.0, True), ("room", 1, 128, 128, 40.0, True)]
+    ("apt60000", 1, 256, 256, 8.0, True), ("room", 1, 128, 128, 40.0, True),
+    # many pixels a triangle: larger launches too
+    ("room", 5, 512, 512, None, True), ("room", 31, 256, 256, None, True), ("room", 16, 512, 512, None, True),
+    ("room", 1, 2048, 2048, None, True), ("apt5000", 8, 512, 512, None, True), ("apt20000", 6, 512, 512, None, True),
+    ("apt5000", 100, 128, 128, None, False), ("apt20000", 12, 512, 512, None, False), ("apt60000", 5, 512, 512, None, False),
+    ("room", 5, 512, 512, 40.0, True), ("apt9700", 5, 512, 512, 40.0, False), ("apt20000", 4, 512, 512, 40.0, False),
+    ("apt5000", 1, 2048, 2048, 400.0, True), ("apt9700_sh", 1, 128, 128, None, True), ("apt9700_sh", 4, 256, 256, None, True),
+    ("apt9700_sh", 24, 256, 256, None, False)]
 
 
 @pytest.mark.parametrize("scene,n,w,h,above,direct", CASES)
 def test_choice_outputs_and_price(ctx, scenes, scene, n, w, h, above, direct):
     import torch
     s0, sc = scenes[scene]
-    sn = ctx.sensor(w, h, 90.0, 0.01 if above is None and w <= 512 else 0.5)
-    poses = random_poses(s0, n, seed=5) if above is None else far(above)
+    sn = ctx.sensor(w, h, 90.0, 0.01 if above is None and w <= 512 else 0.5 if w <= 1000 else 1.0)
+    poses = random_poses(s0, n, seed=5) if above is None else np.repeat(far(above), n, 0)
     note(f"direct rule: {scene}, {n} of {w} x {h}, above {above}")
     outs = []
     for kw in (dict(), dict(tile_size=16)):
