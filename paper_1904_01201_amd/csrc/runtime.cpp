@@ -335,6 +335,7 @@ struct DirectTiles {
                                       //   falls on few tiles (0: it does not)
     double spread = 0.0;              // of the launch's triangles (Scene::spread)
     double density = 0.0;             // pixels a triangle
+    double ragged = 1.0;              // the tiles' pixels, of the images'
 };
 
 // The part of the image that the box around a scene takes, if all of it lies in
@@ -418,6 +419,7 @@ static DirectTiles choose_tiles(const ViewReq *v, uint32_t n)
     t.edge = max_t >= 128000 || mixed ? 64u : fine ? 32u : 16u;
     for (count(); t.edge < 64 && (tiles > most_tiles(t.edge) || (t.edge < 32 && t.visits > kVisits)); count())
         t.edge *= 2;
+    t.ragged = tiles * t.edge * t.edge / std::max(px, 1.0);
     const double waves = t.edge == 64 ? 8 : 4;
     const double want = std::min(1.5 * per_tile / n / waves, 256.0);
     const double most = (max_t >= 500000 ? 2048.0 : 1024.0) / std::max(tiles, 1.0);
@@ -456,6 +458,9 @@ static DirectTiles choose_tiles(const ViewReq *v, uint32_t n)
 // 256 x 256 (3145) 204 / 155; six of 512 x 512 over 20k (1573; 13 pixels) 211 / 160,
 // ten (2621) 255 / 220, twelve (3146) 258 / 249; but 20 of 256 x 256 over 10k (1311;
 // 6.6 pixels) 163 / 165, five of 512 x 512 over 40k (1311; 6.6) 153 / 159.
+// Images that fill little of their 64-pixel tiles share them among fewer blocks: over
+// 200k triangles 12 of 128 x 128 (790) 102 / 77, of 129 x 129 102 / 102, 16 (1065)
+// 105 / 91 and 105 / 140; 14 of 200 x 150 (1094) 111 / 141.
 //
 // Nor where its work is out of proportion to that size.  A visit takes about a
 // nanosecond, and the lists about 30 us more than the direct path without any,
@@ -483,8 +488,10 @@ static bool direct_launch(const ViewReq *v, uint32_t n, const PlanOpts &o, Direc
         max_t = std::max(max_t, v[k].scene->T);
     }
     const double dense = std::max(1.0, (double)px / (kDense * std::max<uint64_t>(tri, 1)));
-    if ((double)size > (o.half ? (double)kDirectHalf : kDirectSize * dense)) return false;
+    const double limit = o.half ? (double)kDirectHalf : kDirectSize * dense;
+    if ((double)size > limit) return false;
     *t = choose_tiles(v, n);
+    if (max_t >= kFine && t->edge == 64 && size * (1.0 + 0.35 * std::min(t->ragged - 1.0, 1.2)) > limit) return false;
     if (max_t >= kSpreadMost && max_t < kFine && t->spread > kSpread && t->edge == 64 && t->visits > 5000.0 * std::sqrt(t->density))
         return false;
     if (max_t >= kFine && t->spread > kSpread) return t->density < 1.0 && t->visits <= kVisits;

@@ -55,7 +55,9 @@ CASES = [
     ("apt5000", 100, 128, 128, None, False), ("apt20000", 12, 512, 512, None, False), ("apt60000", 5, 512, 512, None, False),
     ("room", 5, 512, 512, 40.0, True), ("apt9700", 5, 512, 512, 40.0, False), ("apt20000", 4, 512, 512, 40.0, False),
     ("apt5000", 1, 2048, 2048, 400.0, True), ("apt9700_sh", 1, 128, 128, None, True), ("apt9700_sh", 4, 256, 256, None, True),
-    ("apt9700_sh", 24, 256, 256, None, False)]
+    ("apt9700_sh", 24, 256, 256, None, False),
+    # images that fill little of their tiles
+    ("apt200000", 16, 129, 129, None, False), ("apt200000", 8, 129, 129, None, True), ("apt200000", 14, 200, 150, None, False)]
 
 
 @pytest.mark.parametrize("scene,n,w,h,above,direct", CASES)
