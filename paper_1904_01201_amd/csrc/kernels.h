@@ -9,14 +9,18 @@ namespace habmi {
 
 constexpr uint32_t kMaxViews = 4096;   // views per launch sequence
 constexpr uint32_t kSegPerTile = 4;    // a work item covers <= 4 * TS^2 list entries
-// List entries of a work item of k_raster_wave, by the launch's 16-pixel tiles.
-// A wave takes about 7 us for 64 entries while it shares its SIMD with five
-// others, so the launch ends on waves with a whole item left; but each item of
-// a tile with several merges 256 keys.  Items of 256 -> of 128: eight 512 x 384
-// views (6144 tiles) rasterise in 108 -> 96 us, 32 and 64 views of 256 x 256
-// in 101 -> 90 and 170 -> 165, 256 mixed views (two launches of 57 k tiles) take
-// 1112 -> 1123; items of 64 take 110 to 150 % of the time.
+// List entries of a work item of k_raster_wave, by the launch's 16-pixel tiles and
+// triangles.  A wave takes about 7 us for 64 entries while it shares its SIMD with
+// five others, more without, so the launch ends on waves with a whole item left;
+// but each item of a tile with several merges 256 keys.  Items of 256 -> of 128:
+// eight 512 x 384 views of 1M triangles rasterise in 108 -> 96 us, 32 and 64 views of
+// 256 x 256 in 101 -> 90 and 170 -> 165, 256 mixed views (two launches of 57 k tiles)
+// take 1112 -> 1123.  Items of 128 -> 64 -> 32, us a launch: one 512 x 512 view of 5k
+// triangles 238 -> 227 -> 224, two of 20k (40k triangles) 152 -> 143 -> 143, 16 of 256 x
+// 256 over 20k (320k) 147 -> 138 -> 138, eight over 60k (480k) 119 -> 108 -> 110, over
+// 200k (1.6M) 114 -> 110 -> 120; but 16 of them (3.2M) 142 -> 147 -> 176.
 constexpr uint32_t kWaveSeg = 128, kWaveSegLarge = 256, kWaveManyTiles = 32768;
+constexpr uint32_t kWaveSegSmall[2] = {32, 64}, kWaveTriangles[2] = {300000, 2000000};   // up to
 constexpr int kWaveWavesPerSimd = 6;    // its register budget
 constexpr uint32_t kMaxSegments = 1u << 14;
 

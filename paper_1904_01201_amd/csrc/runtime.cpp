@@ -642,7 +642,20 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
     // a wave per 16-pixel tile: smaller work items, but one set of z-keys per
     // tile whatever its items; both fit the space the block form takes
     const bool wave16 = !o.lane_owned_z;
-    uint64_t wave_tiles = 0, wave_items = 0;
+    uint64_t wave_tiles = 0, wave_items = 0, wave_tri = 0;
+    uint32_t wave_seg = 0, wave_most = 0;
+    for (uint32_t k = 0; k < n && wave16; ++k) {
+        if (dv[k].ts_log2 != 4) continue;
+        wave_tiles += (uint64_t)dv[k].tiles_x * dv[k].tiles_y;
+        wave_tri += dv[k].T;
+        wave_most = std::max(wave_most, dv[k].T);
+    }
+    if (wave16) wave_seg = wave_tiles < kWaveManyTiles ? kWaveSeg : kWaveSegLarge;
+    // (a list of more than kMaxSegments items would overflow)
+    for (int k = 1; k >= 0; --k)
+        if (wave_seg && wave_tiles < kWaveManyTiles && wave_tri <= kWaveTriangles[k] && 2ull * wave_most < (uint64_t)kWaveSegSmall[k] * (kMaxSegments - 1))
+            wave_seg = kWaveSegSmall[k];
+    wave_tiles = 0;
     for (int c = 0; c < 3; ++c) {
         plan.off_items[c] = off;
         if (c == 1 && wave16) {
@@ -652,7 +665,7 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
                 d.zoff_lo = (uint32_t)(wave_tiles * 256);
                 d.zoff_hi = (uint32_t)((wave_tiles * 256) >> 32);
                 wave_tiles += (uint64_t)d.tiles_x * d.tiles_y;
-                wave_items += (uint64_t)d.tiles_x * d.tiles_y + (d.bin_cap + kWaveSeg - 1) / kWaveSeg;
+                wave_items += (uint64_t)d.tiles_x * d.tiles_y + (d.bin_cap + wave_seg - 1) / wave_seg;
             }
             plan.off_zbuf = align256(off + 8 * wave_items);
         }
@@ -670,7 +683,7 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
     L = LaunchPlan{};
     L.nviews = n;
     L.direct = direct;
-    L.wave_seg = !wave16 ? 0 : wave_tiles < kWaveManyTiles ? kWaveSeg : kWaveSegLarge;
+    L.wave_seg = wave_seg;
     std::vector<uint32_t> &tpre = ws.tpre;
     const int c0 = (int)dv[0].ts_log2 - 3;
     if (direct) {
