@@ -10,6 +10,7 @@ constexpr uint32_t kOverflow = 0xFFFFFFFFu;   // tile offset marker: list not st
 constexpr int kSetupBlock = 256;              // threads per block in setup
 constexpr int kSetupWavesPerSimd = 6;         // setup's register budget; its grid is one round of it
 constexpr int kBinBlock = 256;                // threads per block in count/scatter
+constexpr uint32_t kLdsTiles = 2048;          // of a view that count/scatter bin at once
 constexpr int kRun = 4;                       // visible clusters a setup wave takes at a time
 constexpr int kBinRuns = 8;                   // runs per block in count/scatter
 constexpr int kCluster = 64;                  // triangles per culling cluster (one wave)

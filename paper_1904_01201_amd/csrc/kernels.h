@@ -70,6 +70,7 @@ struct LaunchPlan {
     uint32_t *err;
     uint32_t bin_grid;
     uint32_t max_tiles;        // of a view
+    bool coarse;               // triangles of many tiles (k_bin)
     uint32_t wave_seg;         // 16-pixel tiles go to k_raster_wave, this many entries an item, their
                                //   z-keys to zbuf (0: to k_raster)
     RasterLaunch raster[3];

@@ -447,7 +447,6 @@ __global__ __launch_bounds__(kSetupBlock) __attribute__((amdgpu_waves_per_eu(kSe
 // Items of the count/scatter kernels are (view, chunk of kBinRuns runs); every block builds the prefix of chunk counts over the
 // views, then strides over the items.
 constexpr uint32_t kBinHeld = 4;       // survivors a thread holds in registers
-constexpr uint32_t kLdsTiles = 2048;   // of a view that are binned at once
 
 // LDS slot of tile i in the per-chunk tile arrays: the low five bits are
 // XORed with the next five, a permutation within each aligned run of 32
@@ -523,8 +522,12 @@ __device__ __forceinline__ size_t wave_tile(const DView &v, uint32_t tile)
 // resident; with 66 VGPRs a quarter of them ran after the others (1024 views'
 // scatter 47 us, 41 so).
 //
-// LARGE: some view has more tiles than the histogram holds.  A launch without one
-// is spared that form's register spills (5 us of the scatter of 64 views).
+// LARGE: some view has more tiles than the histogram holds, or the triangles are
+// coarse, kCoarseTiles a tile or fewer: a wave then walks each large box, which held up
+// the other lanes, a lane to each.  One 512 x 512 view of a 5k-triangle apartment (lists)
+// 222 -> 173 us, eight of 20k 224 -> 176, of 200k (195 triangles a tile) 162 -> 156, but
+// two of 200k 106 -> 111 and sixteen of 1M (977) 307 -> 311.  A launch without either is
+// spared that form's register spills (5 us of the scatter of 64 views).
 template <bool SCATTER, bool LARGE>
 __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_bin(const DView *__restrict__ views, uint32_t nviews,
                                                    const DViewCounters *__restrict__ ctr,
@@ -593,11 +596,35 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
         const uint32_t ts = v.ts_log2, tiles_x = v.tiles_x, nt = v.tiles_x * v.tiles_y;
         const uint32_t tile_base = v.tile_base, bin_base = v.bin_base;
         if (!LARGE || nt <= kLdsTiles) {
+            // f(tile, key) for the tiles of every survivor of the chunk
+            auto each = [&](const uint2 *box, const uint32_t *key, auto f) {
+                auto lane = [&](uint2 bb, uint32_t k) {
+                    const TileRange R = tile_range(bb, ts);
+                    for (int ty = R.ty0; ty <= R.ty1; ++ty)
+                        for (int tx = R.tx0; tx <= R.tx1; ++tx) f((uint32_t)ty * tiles_x + (uint32_t)tx, k);
+                };
+                if constexpr (LARGE) {
+#pragma unroll
+                    for (uint32_t r = 0; r < kBinHeld; ++r) walk_tiles(r * kBinBlock + tid < n, tile_range(box[r], ts), tiles_x, key[r], f);
+                    for (uint32_t e0 = kBinHeld * kBinBlock; e0 < n; e0 += kBinBlock) {
+                        const uint32_t s = at(min(e0 + tid, n - 1u));
+                        walk_tiles(e0 + tid < n, tile_range(sbox[s], ts), tiles_x, SCATTER ? skey[s] : 0u, f);
+                    }
+                } else {
+#pragma unroll
+                    for (uint32_t r = 0; r < kBinHeld; ++r)
+                        if (r * kBinBlock + tid < n) lane(box[r], key[r]);
+                    for (uint32_t e = kBinHeld * kBinBlock + tid; e < n; e += kBinBlock) {
+                        const uint32_t s = at(e);
+                        lane(sbox[s], SCATTER ? skey[s] : 0u);
+                    }
+                }
+            };
             // a thread's first survivors, loaded together while the histogram
             // is cleared and kept for the scatter; a chunk of 8 runs has about
             // 860, more go one round at a time
             uint2 box[kBinHeld];
-            uint32_t key[kBinHeld];
+            uint32_t key[kBinHeld] = {};
 #pragma unroll
             for (uint32_t r = 0; r < kBinHeld; ++r) {
                 box[r] = make_uint2(0u, 0u);
@@ -612,15 +639,7 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
             __syncthreads();
             // count this chunk's entries per tile in LDS (at most kSlots a
             // run and tile: fits the 16-bit half)
-            auto count = [&](uint2 bb) {
-                const TileRange R = tile_range(bb, ts);
-                for (int ty = R.ty0; ty <= R.ty1; ++ty)
-                    for (int tx = R.tx0; tx <= R.tx1; ++tx) atomicAdd(&hist[swz((uint32_t)ty * tiles_x + (uint32_t)tx)], 1u);
-            };
-#pragma unroll
-            for (uint32_t r = 0; r < kBinHeld; ++r)
-                if (r * kBinBlock + tid < n) count(box[r]);
-            for (uint32_t e = kBinHeld * kBinBlock + tid; e < n; e += kBinBlock) count(sbox[at(e)]);
+            each(box, key, [&](uint32_t tl, uint32_t) { atomicAdd(&hist[swz(tl)], 1u); });
             __syncthreads();
             // one global operation per touched tile; a thread's tiles are
             // i, i + kBinBlock, ...: their loads and atomics are issued
@@ -658,24 +677,12 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
             }
             if (SCATTER) {
                 __syncthreads();
-                auto put = [&](uint2 bb, uint32_t k) {
-                    const TileRange R = tile_range(bb, ts);
-                    for (int ty = R.ty0; ty <= R.ty1; ++ty)
-                        for (int tx = R.tx0; tx <= R.tx1; ++tx) {
-                            const uint32_t tl = (uint32_t)ty * tiles_x + (uint32_t)tx;
-                            const uint32_t b = lbase[swz(tl)];
-                            if (b == kOverflow) continue;
-                            const uint32_t rank = atomicAdd(&hist[swz(tl)], 1u << 16) >> 16;
-                            bins[bin_base + b + rank] = k;
-                        }
-                };
-#pragma unroll
-                for (uint32_t r = 0; r < kBinHeld; ++r)
-                    if (r * kBinBlock + tid < n) put(box[r], key[r]);
-                for (uint32_t e = kBinHeld * kBinBlock + tid; e < n; e += kBinBlock) {
-                    const uint32_t s = at(e);
-                    put(sbox[s], skey[s]);
-                }
+                each(box, key, [&](uint32_t tl, uint32_t k) {
+                    const uint32_t b = lbase[swz(tl)];
+                    if (b == kOverflow) return;
+                    const uint32_t rank = atomicAdd(&hist[swz(tl)], 1u << 16) >> 16;
+                    bins[bin_base + b + rank] = k;
+                });
             }
             __syncthreads();
         } else {
@@ -2043,7 +2050,7 @@ hipError_t launch_render(const LaunchPlan &L, hipStream_t s)
                        L.pairs, L.skey, L.sbox, L.err);
     mark(L, 3, s);
     mark(L, 4, s);
-    const bool large = L.max_tiles > kLdsTiles;
+    const bool large = L.max_tiles > kLdsTiles || L.coarse;
     auto *const k_count = large ? k_bin<false, true> : k_bin<false, false>;
     hipLaunchKernelGGL(k_count, dim3(L.bin_grid), dim3(kBinBlock), pre_bytes, s,
                        L.views, L.nviews, L.ctr, L.pairs, L.skey, L.sbox, L.tile_count, L.tile_off, L.tile_cursor, L.bins,

@@ -11,11 +11,16 @@ namespace habmi {
 
 static constexpr float kDefaultBinFactor = 2.0f;
 static constexpr uint32_t kDefaultTile = 16;
-// Pixels + triangles / 4 up to which the direct path draws a launch, and a
-// half of a split batch; above kDense pixels a triangle a launch may be larger.
-static constexpr uint64_t kDirectSize = 1150 * 1024, kDirectHalf = 740 * 1024;
+// Pixels + triangles / 4 up to which the direct path draws a launch, a half of
+// a split batch, and a launch of fine triangles of at least a pixel; or the pixels a
+// triangle times kDirectDense (kDirectWide with a view of more tiles than are binned at
+// once), if that is more.
+static constexpr uint64_t kDirectSize = 1150 * 1024, kDirectHalf = 740 * 1024, kDirectFine = 640 * 1024;
+static constexpr uint64_t kDirectDense = 100 * 1024, kDirectWide = 190 * 1024;
 // ... and the visits, spread and depth (choose_tiles) up to which it does.
-static constexpr double kVisits = 30000.0, kSpread = 0.2, kDepth = 16.0, kDense = 6.0;
+static constexpr double kVisits = 30000.0, kSpread = 0.2, kDepth = 16.0;
+// Triangles a tile up to which the binning takes large boxes a wave at a time (k_bin has both sides).
+static constexpr uint32_t kCoarseTiles = 250;
 // Triangles from which the largest scene of a launch counts as fine, and its clusters, where they spread, as many.
 static constexpr uint32_t kFine = 10000, kSpreadMost = 7000;
 // Resolve waves that a launch keeps when a wave shades two or four bands one
@@ -452,12 +457,14 @@ static DirectTiles choose_tiles(const ViewReq *v, uint32_t n)
 // triangles, by the size of a half: 1025 views of 24 x 20 210 / 200 and 280 / 243
 // (490), 1500 247 / 244 and 330 / 300 (718), 2048 295 / 304 and 399 / 370 (980)).
 //
-// Where a triangle has many pixels the lists are slow, a wave taking each 16-pixel
-// tile however long its triangles, and the limit rises with the pixels a triangle:
-// five of 512 x 512 over 2k triangles (1310) 210 / 89, 16 (4194) 301 / 186, 48 of
-// 256 x 256 (3145) 204 / 155; six of 512 x 512 over 20k (1573; 13 pixels) 211 / 160,
-// ten (2621) 255 / 220, twelve (3146) 258 / 249; but 20 of 256 x 256 over 10k (1311;
-// 6.6 pixels) 163 / 165, five of 512 x 512 over 40k (1311; 6.6) 153 / 159.
+// The lists gain on fine triangles of a pixel and more (eight of 256 x 256 over 20k
+// (565) 108 / 120, twelve (847) 114 / 136, eight over 60k (632) 106 / 110, three of 512 x
+// 512 over 60k (813) 123 / 127) and lose again where a triangle has so many that a wave
+// to a tile is slow: four of 512 x 512 over 20k (1044; 13 pixels a triangle) 150 / 144,
+// five (1305) 161 / 164, eight (2088) 197 / 204, five over 2k (1282; 131) 179 / 95, 16
+// (4104) 235 / 186, 48 of 256 x 256 over 2k (3096; 33) 182 / 152, 20 over 5k (1305; 13)
+// 142 / 142.  Larger images are binned in windows: one of 1200 x 1000 over 100k (1196;
+// 12) 263 / 157, one of 1600 x 1200 over 60k (1890; 32) 419 / 167.
 // Images that fill little of their 64-pixel tiles share them among fewer blocks: over
 // 200k triangles 12 of 128 x 128 (790) 102 / 77, of 129 x 129 102 / 102, 16 (1065)
 // 105 / 91 and 105 / 140; 14 of 200 x 150 (1094) 111 / 141.
@@ -479,16 +486,19 @@ static bool direct_launch(const ViewReq *v, uint32_t n, const PlanOpts &o, Direc
 {
     if (o.tile_lists || o.tile_size || o.bin_factor > 0.0f || o.tile_cap || o.lane_owned_z || o.count_work) return false;
     uint64_t size = 0, px = 0, tri = 0;
-    uint32_t max_t = 0;
+    uint32_t max_t = 0, most = 0;
     for (uint32_t k = 0; k < n; ++k) {
+        most = std::max(most, cdiv(v[k].sensor.width, kDefaultTile) * cdiv(v[k].sensor.height, kDefaultTile));
         const uint64_t view = (uint64_t)v[k].sensor.width * v[k].sensor.height;
         size += view + v[k].scene->T / 4;
         px += view;
         tri += v[k].scene->T;
         max_t = std::max(max_t, v[k].scene->T);
     }
-    const double dense = std::max(1.0, (double)px / (kDense * std::max<uint64_t>(tri, 1)));
-    const double limit = o.half ? (double)kDirectHalf : kDirectSize * dense;
+    const double density = (double)px / std::max<uint64_t>(tri, 1);
+    double limit = o.half ? kDirectHalf : kDirectSize;
+    if (max_t >= kFine && density >= 1.0) limit = std::min(limit, (double)kDirectFine);
+    if (!o.half) limit = std::max(limit, (most > kLdsTiles ? kDirectWide : kDirectDense) * density);
     if ((double)size > limit) return false;
     *t = choose_tiles(v, n);
     if (max_t >= kFine && t->edge == 64 && size * (1.0 + 0.35 * std::min(t->ragged - 1.0, 1.2)) > limit) return false;
@@ -743,7 +753,12 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
     L.setup_grid = (uint32_t)std::max<uint64_t>(
         1, std::min<uint64_t>((npairs + 15) / 16, setup_resident * (ctx ? ctx->cu_count : 256)));
     L.ntiles = (uint32_t)tile_total;
-    for (uint32_t k = 0; k < n; ++k) L.max_tiles = std::max(L.max_tiles, dv[k].tiles_x * dv[k].tiles_y);
+    uint64_t tri = 0;
+    for (uint32_t k = 0; k < n; ++k) {
+        L.max_tiles = std::max(L.max_tiles, dv[k].tiles_x * dv[k].tiles_y);
+        tri += dv[k].T;
+    }
+    L.coarse = tile_total * kCoarseTiles >= tri;
     uint64_t ub = 0;
     for (uint32_t k = 0; k < n; ++k) ub += cdiv(dv[k].T, kCluster * kRun * kBinRuns);
     L.bin_grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(ub, 8ull * (ctx ? ctx->cu_count : 256)));

@@ -51,11 +51,13 @@ CASES = [
     ("apt60000", 1, 256, 256, 8.0, True), ("room", 1, 128, 128, 40.0, True),
     # many pixels a triangle: larger launches too
     ("room", 5, 512, 512, None, True), ("room", 31, 256, 256, None, True), ("room", 16, 512, 512, None, True),
-    ("room", 1, 2048, 2048, None, True), ("apt5000", 8, 512, 512, None, True), ("apt20000", 6, 512, 512, None, True),
+    ("room", 1, 2048, 2048, None, True), ("apt5000", 8, 512, 512, None, True), ("apt20000", 4, 512, 512, None, True),
     ("apt5000", 100, 128, 128, None, False), ("apt20000", 12, 512, 512, None, False), ("apt60000", 5, 512, 512, None, False),
     ("room", 5, 512, 512, 40.0, True), ("apt9700", 5, 512, 512, 40.0, False), ("apt20000", 4, 512, 512, 40.0, False),
     ("apt5000", 1, 2048, 2048, 400.0, True), ("apt9700_sh", 1, 128, 128, None, True), ("apt9700_sh", 4, 256, 256, None, True),
     ("apt9700_sh", 24, 256, 256, None, False),
+    # fine triangles of at least a pixel
+    ("apt20000", 8, 256, 256, None, True), ("apt20000", 12, 256, 256, None, False), ("apt60000", 4, 512, 512, None, False),
     # images that fill little of their tiles
     ("apt200000", 16, 129, 129, None, False), ("apt200000", 8, 129, 129, None, True), ("apt200000", 14, 200, 150, None, False)]
 
