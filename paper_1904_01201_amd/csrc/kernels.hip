@@ -596,8 +596,23 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
         const uint32_t ts = v.ts_log2, tiles_x = v.tiles_x, nt = v.tiles_x * v.tiles_y;
         const uint32_t tile_base = v.tile_base, bin_base = v.bin_base;
         if (!LARGE || nt <= kLdsTiles) {
+            // a thread's first survivors, loaded together while the histogram
+            // is cleared and kept for the scatter; a chunk of 8 runs has about
+            // 860, more go one round at a time
+            uint2 box[kBinHeld];
+            uint32_t key[kBinHeld];
+#pragma unroll
+            for (uint32_t r = 0; r < kBinHeld; ++r) {
+                box[r] = make_uint2(0u, 0u);
+                const uint32_t e = r * kBinBlock + tid;
+                if (e < n) {
+                    const uint32_t s = at(e);
+                    box[r] = sbox[s];
+                    if (SCATTER) key[r] = skey[s];
+                }
+            }
             // f(tile, key) for the tiles of every survivor of the chunk
-            auto each = [&](const uint2 *box, const uint32_t *key, auto f) {
+            auto each = [&](auto f) {
                 auto lane = [&](uint2 bb, uint32_t k) {
                     const TileRange R = tile_range(bb, ts);
                     for (int ty = R.ty0; ty <= R.ty1; ++ty)
@@ -620,26 +635,11 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
                     }
                 }
             };
-            // a thread's first survivors, loaded together while the histogram
-            // is cleared and kept for the scatter; a chunk of 8 runs has about
-            // 860, more go one round at a time
-            uint2 box[kBinHeld];
-            uint32_t key[kBinHeld] = {};
-#pragma unroll
-            for (uint32_t r = 0; r < kBinHeld; ++r) {
-                box[r] = make_uint2(0u, 0u);
-                const uint32_t e = r * kBinBlock + tid;
-                if (e < n) {
-                    const uint32_t s = at(e);
-                    box[r] = sbox[s];
-                    if (SCATTER) key[r] = skey[s];
-                }
-            }
             for (uint32_t i = tid; i < ((nt + 31u) & ~31u); i += kBinBlock) hist[i] = 0;
             __syncthreads();
             // count this chunk's entries per tile in LDS (at most kSlots a
             // run and tile: fits the 16-bit half)
-            each(box, key, [&](uint32_t tl, uint32_t) { atomicAdd(&hist[swz(tl)], 1u); });
+            each([&](uint32_t tl, uint32_t) { atomicAdd(&hist[swz(tl)], 1u); });
             __syncthreads();
             // one global operation per touched tile; a thread's tiles are
             // i, i + kBinBlock, ...: their loads and atomics are issued
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(8))) 
             }
             if (SCATTER) {
                 __syncthreads();
-                each(box, key, [&](uint32_t tl, uint32_t k) {
+                each([&](uint32_t tl, uint32_t k) {
                     const uint32_t b = lbase[swz(tl)];
                     if (b == kOverflow) return;
                     const uint32_t rank = atomicAdd(&hist[swz(tl)], 1u << 16) >> 16;
