@@ -209,7 +209,7 @@ hab_status hab_scene_upload(hab_context *ctx, const hab_mesh_desc *m, hipStream_
         };
         bool ok = dev_alloc((void **)&s->tpos, bp) && dev_alloc((void **)&s->attr, ba) &&
                   dev_alloc((void **)&s->cbox, bb) && (!bs || dev_alloc((void **)&s->inst, bs)) &&
-                  (!btex || dev_alloc((void **)&s->tex, btex)) && upload_memory(ctx, sv + si + sc + su + 8);
+                  (!btex || dev_alloc((void **)&s->tex, btex)) && upload_memory(ctx, sv + si + sc + su + sizeof(SpreadSums));
         if (!ok) {
             drop();
             return HAB_ERR_OUT_OF_MEMORY;
@@ -234,9 +234,8 @@ hab_status hab_scene_upload(hab_context *ctx, const hab_mesh_desc *m, hipStream_
             e = hipMemcpyAsync(s->inst, m->instances, 4ull * T, hipMemcpyHostToDevice, stream);
         if (e == hipSuccess && btex)
             e = hipMemcpyAsync(s->tex, texels.data(), btex, hipMemcpyHostToDevice, stream);
-        unsigned long long *const dspread = reinterpret_cast<unsigned long long *>(b + sv + si + sc + su), zero = 0;
-        unsigned long long spread = 0;
-        if (e == hipSuccess) e = hipMemcpyAsync(dspread, &zero, sizeof zero, hipMemcpyHostToDevice, stream);
+        SpreadSums *const dspread = reinterpret_cast<SpreadSums *>(b + sv + si + sc + su), spread = {};
+        if (e == hipSuccess) e = hipMemcpyAsync(dspread, &spread, sizeof spread, hipMemcpyHostToDevice, stream);
         const float3 size = make_float3(hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2]);
         const float grow = std::max(0.05f * std::max(size.x, std::max(size.y, size.z)), 1e-30f);
         if (e == hipSuccess && T) e = launch_scene(ms, T, s->tpos, s->attr, s->cbox, size, grow, dspread, stream);
@@ -249,7 +248,9 @@ hab_status hab_scene_upload(hab_context *ctx, const hab_mesh_desc *m, hipStream_
             drop();
             return HAB_ERR_DEVICE;
         }
-        s->spread = ncl ? (float)((double)spread / 16777216.0 / ncl) : 0.0f;
+        double parts = 0.0;
+        for (const auto &line : spread.sum) parts += (double)line[0];
+        s->spread = ncl ? (float)(parts / 16777216.0 / ncl) : 0.0f;
         ctx->scenes.push_back(s);
         *out = s;
         return HAB_OK;

@@ -57,7 +57,7 @@ namespace habmi {
 // before it writes the colours, which may take their place.
 __global__ __launch_bounds__(256) void k_scene(MeshSource m, uint32_t T, float *__restrict__ tpos, uint32_t *attr,
                                                float4 *__restrict__ cbox, float3 size, float grow,
-                                               unsigned long long *__restrict__ spread)
+                                               SpreadSums *__restrict__ spread)
 {
     const uint32_t t = blockIdx.x * 256u + threadIdx.x;
     if (uniform(t & ~63u) >= T) return;
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void k_scene(MeshSource m, uint32_t T, float *
         // in whole units: the sum does not depend on the order
         const float part = (mx[0] - mn[0] + grow) / (size.x + grow) * ((mx[1] - mn[1] + grow) / (size.y + grow)) *
                            ((mx[2] - mn[2] + grow) / (size.z + grow));
-        atomicAdd(spread, (unsigned long long)(fminf(part, 1.0f) * 16777216.0f));
+        atomicAdd(&spread->sum[blockIdx.x % 32u][0], (unsigned long long)(fminf(part, 1.0f) * 16777216.0f));
     }
 }
 
@@ -1186,7 +1186,7 @@ __device__ __forceinline__ long long join64(int hi, int lo)
 // one item a tile over the slots with their gaps took 2.0, a 256-thread block over
 // a list without gaps 0.83.
 //
-// Bound by VALU issue, half of it rebuilding the entries' setup: 76 M wave
+// Bound by VALU issue, half of it rebuilding the entries' setup: 79 M wave
 // instructions for the 64 bench views (99 M before the setup dropped triangles
 // that cover no pixel), 65 % busy in a launch of half of them, which ends short
 // of waves.  0.146 ms alone for the 64 views; with the same lists 8-pixel tiles
@@ -2012,7 +2012,7 @@ static void launch_resolve(const LaunchPlan &L, const RasterLaunch &R, hipStream
 }
 
 hipError_t launch_scene(const MeshSource &m, uint32_t T, float *tpos, uint32_t *attr, float4 *cbox, float3 size, float grow,
-                        unsigned long long *spread, hipStream_t s)
+                        SpreadSums *spread, hipStream_t s)
 {
     hipLaunchKernelGGL(k_scene, dim3(cdiv(T, 256)), dim3(256), 0, s, m, T, tpos, attr, cbox, size, grow, spread);
     return hipGetLastError();
