@@ -545,7 +545,10 @@ def main():
     # ---------------------------------------------------- roofline
     # A step as large as this one is two launch sequences (halves of the
     # batch) that run side by side: per-launch times are each half's own
-    # kernel durations, and the work of one launch is half a step's.
+    # kernel durations, and the work of one launch is half a step's.  The
+    # counted launches keep the triangles whose box holds up to four centres
+    # and that cover none, which the timed ones drop (a quarter of the
+    # survivors, few of the tests), so the rate is a little too high.
     per_launch = {k: v["ms"] / max(v["launches"], 1) for k, v in phases.items()}
     per_step = {k: v["ms"] / a.steps for k, v in phases.items()}
     lps = {k: v["launches"] / a.steps for k, v in phases.items()}

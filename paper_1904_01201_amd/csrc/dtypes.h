@@ -36,7 +36,6 @@ struct alignas(16) DView {
     uint32_t tiles_x, tiles_y;
     uint32_t tile_base;         // first entry in the per-tile arrays
     uint32_t surv_base;         // first entry in the survivor arrays: two slots a triangle, by run
-    uint32_t surv_cap;          // 2 T
     uint32_t bin_base;          // first entry in the bin array
     uint32_t bin_cap;           // entries available to this view
     uint32_t tile_cap;          // entries one tile may hold (else overflow)
@@ -51,7 +50,7 @@ struct alignas(16) DView {
     uint64_t noise_seed;        // key of the per-pixel depth noise
     const uint32_t *tex;        // [tex_h][tex_w] packed RGB texels, or null
     uint32_t tex_w, tex_h;      // powers of two
-    uint32_t pad[4];            // the size is part of every scratch limit
+    uint32_t pad[6];            // the size is part of every scratch limit
 };
 static_assert(sizeof(DView) == 240, "DView layout");
 

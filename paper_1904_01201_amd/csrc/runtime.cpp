@@ -564,8 +564,7 @@ hab_status build_plan(hab_context *ctx, Workspace &ws, const ViewReq *v, uint32_
         d.tile_base = (uint32_t)tile_total;
         tile_total += (uint64_t)d.tiles_x * d.tiles_y;
         d.surv_base = (uint32_t)surv_total;
-        d.surv_cap = 2u * d.T;
-        surv_total += d.surv_cap;
+        surv_total += 2ull * d.T;
         uint64_t bc = (uint64_t)std::ceil((double)bf * (double)d.T);
         bc = std::max<uint64_t>(bc, 1024);
         bc = std::min<uint64_t>(bc, kIndexLimit / 4);
