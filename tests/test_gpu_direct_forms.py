@@ -52,17 +52,19 @@ def _same(a, b, what):
         assert torch.equal(a[k], b[k]), (what, k)
 
 
-@pytest.mark.parametrize("n,two", [(24, False), (1100, True)])
+# fine triangles; tiny views in two halves; coarse triangles in images beyond the size limit of the others
+@pytest.mark.parametrize("n,two", [(24, False), (1100, True), (12, False)])
 def test_mixed_batch_and_captured_steps(ctx, n, two):
     import torch
     import paper_1904_01201_amd as P
     note(f"direct forms: {n} views")
-    tri = (20_000, 60_000) if n < 100 else (12, 500)
-    scs = [with_texture(make_apartment(seed=51, target_T=tri[0], jitter_sigma=0.01), size=128) if n < 100 else
+    scs = [with_texture(make_apartment(seed=51, target_T=20_000, jitter_sigma=0.01), size=128) if n == 24 else
            with_texture(make_room(seed=52, num_boxes=1), size=64),
-           make_apartment(seed=53, target_T=tri[1], jitter_sigma=0.01) if n < 100 else make_room(seed=54, num_boxes=0)]
+           make_apartment(seed=53, target_T=60_000, jitter_sigma=0.01) if n == 24 else
+           make_room(seed=54, num_boxes=0 if n > 24 else 20)]
     hs = [ctx.upload_scene(s) for s in scs]
-    sizes = ((128, 128), (130, 97), (160, 120), (96, 64)) if n < 100 else ((24, 20), (17, 9), (32, 12), (20, 24))
+    sizes = {24: ((128, 128), (130, 97), (160, 120), (96, 64)), 1100: ((24, 20), (17, 9), (32, 12), (20, 24)),
+             12: ((512, 512), (401, 333), (640, 481), (517, 300))}[n]
     sensors = [ctx.sensor(w, h, 90.0, 0.01, o, s) for (w, h), o, s in
                zip(sizes, (P.OUT_RGB | P.OUT_DEPTH, 11, P.OUT_DEPTH, P.OUT_RGB | P.OUT_DEPTH), (0.0, 0.0, 0.0, 0.1))]
     poses = [random_poses(s, 6, seed=55) for s in scs]
